@@ -98,8 +98,8 @@
  *              which equals X[nodes_b[j]] whenever cache row s holds X of the
  *              node whose cache_slot is s.
  * Feature rows are opaque bytes (fp32, fp16, anything): they are copied, never
- * converted.  Rows move as 16-byte vectors when row_bytes and the row base
- * pointers are multiples of 16, and by narrower words otherwise.
+ * converted.  Rows of 16 to 4096 bytes move as 16-byte vectors whatever their size
+ * and the alignment of the base pointers, other rows by narrower words.
  */
 #ifndef DG_H
 #define DG_H

@@ -24,11 +24,19 @@ __device__ __forceinline__ const char *row_source(int32_t l, const char *cache, 
   return nullptr;
 }
 
-// The rows of one batch handled by virtual block `blk` of `nblk`.
-template <int LPR, int CPL>
-__device__ __forceinline__ void assemble16_rows(const v4u *cache, int64_t cache_rows,
-                                                const v4u *packed, int64_t packed_rows,
-                                                const int32_t *loc, int64_t n, int C, v4u *out,
+// The rows of one batch handled by virtual block `blk` of `nblk`.  Bound by HBM:
+// plain loads (cache rows are read again by later batches) and, with NT,
+// nontemporal stores.  Short rows that are no multiple of 32 bytes take plain
+// stores, so that the lines that several rows share merge in L2 (4M rows, plain
+// against nontemporal: 48 B 136 / 182 us, 100 B 227 / 313, 112 B 233 / 244;
+// but 64 B 150 / 123, 96 B 192 / 184, 400 B 180 / 163 (1M rows), 1.5 KiB
+// 385 / 342).  Rows that are no multiple of 16 bytes used to go by narrower words, one
+// wave per row: 385 B 512 us, now 180; 1540 B 549, now 417; 200 B 190, now 91
+// (1M, 0.65M and 1M rows).
+template <int LPR, int CPL, bool NT>
+__device__ __forceinline__ void assemble16_rows(const char *cache, int64_t cache_rows,
+                                                const char *packed, int64_t packed_rows,
+                                                const int32_t *loc, int64_t n, int R, char *out,
                                                 int32_t *status, int64_t blk, int64_t nblk) {
   constexpr int UNROLL = rows_in_flight(CPL);
   constexpr int GPB = THREADS / LPR;  // row groups per block
@@ -49,7 +57,7 @@ __device__ __forceinline__ void assemble16_rows(const v4u *cache, int64_t cache_
     // Each row's source: the cache table or the packed chunk.  An entry outside
     // both reads the output row it would write (always allocated) instead, is
     // written as zeros, and sets status.
-    const v4u *src[UNROLL];
+    const char *src[UNROLL];
     bool ok[UNROLL];
     bool bad = false;
 #pragma unroll
@@ -59,16 +67,14 @@ __device__ __forceinline__ void assemble16_rows(const v4u *cache, int64_t cache_
       const int64_t r = cached ? -(int64_t)l[u] - 1 : (int64_t)l[u];
       ok[u] = r < (cached ? cache_rows : packed_rows);
       bad |= j0 + u < n && !ok[u];
-      src[u] = ok[u] ? (cached ? cache : packed) + r * C : out + j * C;
+      src[u] = ok[u] ? (cached ? cache : packed) + r * R : out + j * R;
     }
     v4u v[UNROLL][CPL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u)
 #pragma unroll
-      for (int c = 0; c < CPL; ++c) {
-        const int ch = sub + c * LPR;
-        v[u][c] = src[u][ch < C ? ch : C - 1];  // a lane past the row reads its last vector
-      }
+      for (int c = 0; c < CPL; ++c)  // a lane past the row reads its last vector
+        v[u][c] = ld_row(src[u] + row_vec(sub + c * LPR, R));
     if (bad && sub == 0 && status) atomicOr(status, 1);
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
@@ -77,19 +83,20 @@ __device__ __forceinline__ void assemble16_rows(const v4u *cache, int64_t cache_
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
           const int ch = sub + c * LPR;
-          if (ch < C) st_stream(ok[u] ? v[u][c] : v4u{0u, 0u, 0u, 0u}, out + j * C + ch);
+          if (row_has(ch, R))
+            st_vec<NT>(ok[u] ? v[u][c] : v4u{0u, 0u, 0u, 0u}, out + j * R + row_vec(ch, R));
         }
       }
     }
   }
 }
 
-template <int LPR, int CPL>
-__global__ __launch_bounds__(THREADS) void k_assemble16(const v4u *cache, int64_t cache_rows,
-                                                        const v4u *packed, int64_t packed_rows,
-                                                        const int32_t *loc, int64_t n, int C,
-                                                        v4u *out, int32_t *status) {
-  assemble16_rows<LPR, CPL>(cache, cache_rows, packed, packed_rows, loc, n, C, out, status,
+template <int LPR, int CPL, bool NT>
+__global__ __launch_bounds__(THREADS) void k_assemble16(const char *cache, int64_t cache_rows,
+                                                        const char *packed, int64_t packed_rows,
+                                                        const int32_t *loc, int64_t n, int R,
+                                                        char *out, int32_t *status) {
+  assemble16_rows<LPR, CPL, NT>(cache, cache_rows, packed, packed_rows, loc, n, R, out, status,
                             blockIdx.x, gridDim.x);
 }
 
@@ -100,23 +107,23 @@ constexpr int ASM_GROUP = 8;
 struct AsmGroup {
   int G;
   int64_t block0[ASM_GROUP + 1];
-  const v4u *packed[ASM_GROUP];
+  const char *packed[ASM_GROUP];
   int64_t packed_rows[ASM_GROUP];
   const int32_t *loc[ASM_GROUP];
   int64_t n[ASM_GROUP];
-  v4u *out[ASM_GROUP];
+  char *out[ASM_GROUP];
 };
 
-template <int LPR, int CPL>
-__global__ __launch_bounds__(THREADS) void k_assemble16_group(AsmGroup g, const v4u *cache,
-                                                              int64_t cache_rows, int C,
+template <int LPR, int CPL, bool NT>
+__global__ __launch_bounds__(THREADS) void k_assemble16_group(AsmGroup g, const char *cache,
+                                                              int64_t cache_rows, int R,
                                                               int32_t *status) {
   int q = 0;
 #pragma unroll
   for (int k = 1; k < ASM_GROUP; ++k)
     if (k < g.G && (int64_t)blockIdx.x >= g.block0[k]) q = k;
-  assemble16_rows<LPR, CPL>(cache, cache_rows, g.packed[q], g.packed_rows[q], g.loc[q], g.n[q],
-                            C, g.out[q], status, (int64_t)blockIdx.x - g.block0[q],
+  assemble16_rows<LPR, CPL, NT>(cache, cache_rows, g.packed[q], g.packed_rows[q], g.loc[q], g.n[q],
+                            R, g.out[q], status, (int64_t)blockIdx.x - g.block0[q],
                             g.block0[q + 1] - g.block0[q]);
 }
 
@@ -153,16 +160,32 @@ int launch_any(const void *cache, int64_t cache_rows, const void *packed, int64_
 }
 
 template <int LPR, int CPL>
-int launch16(const void *cache, int64_t cache_rows, const void *packed, int64_t packed_rows,
-             const int32_t *loc, int64_t n, int C, void *out, int32_t *status, hipStream_t s) {
+int64_t blocks16(int64_t n) {
   constexpr int GPB = THREADS / LPR;
   constexpr int UNROLL = rows_in_flight(CPL);
-  int64_t groups = (n + UNROLL - 1) / UNROLL;
-  int64_t blocks = (groups + GPB - 1) / GPB;
-  if (blocks > (1ll << 20)) blocks = 1ll << 20;
-  hipLaunchKernelGGL((k_assemble16<LPR, CPL>), dim3((unsigned)blocks), dim3(THREADS), 0, s,
-                     (const v4u *)cache, cache_rows, (const v4u *)packed, packed_rows, loc, n, C,
-                     (v4u *)out, status);
+  const int64_t groups = (n + UNROLL - 1) / UNROLL;
+  const int64_t blocks = (groups + GPB - 1) / GPB;
+  return blocks > (1ll << 20) ? (1ll << 20) : blocks;
+}
+
+// Calls f with the kind of store rows of R bytes take (see assemble16_rows).
+template <int LPR, typename F>
+void with_store(int R, F f) {
+  if constexpr (LPR <= 8) {
+    if (R < 64 || (R < 128 && R % 32 != 0)) return f(std::false_type());
+  }
+  f(std::true_type());
+}
+
+template <int LPR, int CPL>
+int launch16(const void *cache, int64_t cache_rows, const void *packed, int64_t packed_rows,
+             const int32_t *loc, int64_t n, int R, void *out, int32_t *status, hipStream_t s) {
+  with_store<LPR>(R, [&](auto nt) {
+    hipLaunchKernelGGL((k_assemble16<LPR, CPL, decltype(nt)::value>),
+                       dim3((unsigned)blocks16<LPR, CPL>(n)), dim3(THREADS), 0, s,
+                       (const char *)cache, cache_rows, (const char *)packed, packed_rows, loc, n,
+                       R, (char *)out, status);
+  });
   DG_HIP(hipGetLastError());
   return DG_OK;
 }
@@ -197,50 +220,35 @@ int check_batch(const void *cache, int64_t cache_rows, const AsmArgs &a, int64_t
   return DG_OK;
 }
 
-// The 16-byte row shape a batch runs with, if it takes that path.
-bool shape16(const void *cache, const AsmArgs &a, int64_t row_bytes, RowShape *sh) {
-  return word_bytes(row_bytes, {cache, a.packed, a.out}) == 16 && row_shape16(row_bytes / 16, sh);
-}
-
 template <int LPR, int CPL>
-int64_t blocks16(int64_t n) {
-  constexpr int GPB = THREADS / LPR;
-  constexpr int UNROLL = rows_in_flight(CPL);
-  const int64_t groups = (n + UNROLL - 1) / UNROLL;
-  const int64_t blocks = (groups + GPB - 1) / GPB;
-  return blocks > (1ll << 20) ? (1ll << 20) : blocks;
-}
-
-template <int LPR, int CPL>
-int launch16_group(const void *cache, int64_t cache_rows, const AsmArgs *a, int G, int C,
+int launch16_group(const void *cache, int64_t cache_rows, const AsmArgs *a, int G, int R,
                    int32_t *status, hipStream_t s) {
   AsmGroup g{};
   g.G = G;
   g.block0[0] = 0;
   for (int q = 0; q < G; ++q) {
-    g.packed[q] = (const v4u *)a[q].packed;
+    g.packed[q] = (const char *)a[q].packed;
     g.packed_rows[q] = a[q].packed_rows;
     g.loc[q] = a[q].loc;
     g.n[q] = a[q].n;
-    g.out[q] = (v4u *)a[q].out;
+    g.out[q] = (char *)a[q].out;
     g.block0[q + 1] = g.block0[q] + blocks16<LPR, CPL>(a[q].n);
   }
-  hipLaunchKernelGGL((k_assemble16_group<LPR, CPL>), dim3((unsigned)g.block0[G]), dim3(THREADS),
-                     0, s, g, (const v4u *)cache, cache_rows, C, status);
+  with_store<LPR>(R, [&](auto nt) {
+    hipLaunchKernelGGL((k_assemble16_group<LPR, CPL, decltype(nt)::value>),
+                       dim3((unsigned)g.block0[G]), dim3(THREADS), 0, s, g, (const char *)cache,
+                       cache_rows, R, status);
+  });
   DG_HIP(hipGetLastError());
   return DG_OK;
 }
 
 int launch_group(const void *cache, int64_t cache_rows, const AsmArgs *a, int G,
                  int64_t row_bytes, const RowShape &sh, int32_t *status, hipStream_t s) {
-  const int C = (int)(row_bytes / 16);
-  if (sh.lpr == 4) return launch16_group<4, 1>(cache, cache_rows, a, G, C, status, s);
-  if (sh.lpr == 8) return launch16_group<8, 1>(cache, cache_rows, a, G, C, status, s);
-  if (sh.lpr == 16) return launch16_group<16, 1>(cache, cache_rows, a, G, C, status, s);
-  if (sh.lpr == 32 && sh.cpl == 1) return launch16_group<32, 1>(cache, cache_rows, a, G, C, status, s);
-  if (sh.lpr == 64 && sh.cpl == 1) return launch16_group<64, 1>(cache, cache_rows, a, G, C, status, s);
-  if (sh.lpr == 64 && sh.cpl == 2) return launch16_group<64, 2>(cache, cache_rows, a, G, C, status, s);
-  return launch16_group<64, 4>(cache, cache_rows, a, G, C, status, s);
+  return with_shape(sh, [&](auto lpr, auto cpl) {
+    return launch16_group<decltype(lpr)::value, decltype(cpl)::value>(cache, cache_rows, a, G,
+                                                                      (int)row_bytes, status, s);
+  });
 }
 
 }  // namespace
@@ -262,22 +270,15 @@ extern "C" int dg_assemble_batch(const void *cache, int64_t cache_rows, const vo
       overlaps(out, out_bytes, packed_b, packed_rows_b * row_bytes) ||
       overlaps(out, out_bytes, loc_b, n_b * 4))
     return set_error(DG_EINVAL, "dg_assemble_batch: output overlaps an input");
+  RowShape sh;
+  if (row_shape16(row_bytes, &sh))
+    return with_shape(sh, [&](auto lpr, auto cpl) {
+      return launch16<decltype(lpr)::value, decltype(cpl)::value>(
+          cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, (int)row_bytes, out, status,
+          stream);
+    });
   const int w = word_bytes(row_bytes, {cache, packed_b, out});
-  if (w == 16) {
-    const int64_t C = row_bytes / 16;
-    RowShape sh;
-    if (row_shape16(C, &sh)) {
-      const int c = (int)C;
-      if (sh.lpr == 4) return launch16<4, 1>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, c, out, status, stream);
-      if (sh.lpr == 8) return launch16<8, 1>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, c, out, status, stream);
-      if (sh.lpr == 16) return launch16<16, 1>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, c, out, status, stream);
-      if (sh.lpr == 32 && sh.cpl == 1) return launch16<32, 1>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, c, out, status, stream);
-      if (sh.lpr == 64 && sh.cpl == 1) return launch16<64, 1>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, c, out, status, stream);
-      if (sh.lpr == 64 && sh.cpl == 2) return launch16<64, 2>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, c, out, status, stream);
-      if (sh.lpr == 64 && sh.cpl == 4) return launch16<64, 4>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, c, out, status, stream);
-    }
-    return launch_any<uint4>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, row_bytes, out, status, stream);
-  }
+  if (w == 16) return launch_any<uint4>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, row_bytes, out, status, stream);
   if (w == 8) return launch_any<uint2>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, row_bytes, out, status, stream);
   if (w == 4) return launch_any<uint32_t>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, row_bytes, out, status, stream);
   if (w == 2) return launch_any<uint16_t>(cache, cache_rows, packed_b, packed_rows_b, loc_b, n_b, row_bytes, out, status, stream);
@@ -299,8 +300,8 @@ extern "C" int dg_assemble_batches(const void *cache, int64_t cache_rows, const 
       return set_error(DG_EINVAL, "dg_assemble_batches: batch %d: bad chunk bounds or n_b", b);
   }
   // Consecutive batches with output buffers of their own (outs[b % n_outs]
-  // distinct and apart) share one launch, up to ASM_GROUP of them, when they
-  // take the 16-byte path: each batch is still checked as dg_assemble_batch
+  // distinct and apart) share one launch, up to ASM_GROUP of them, when their
+  // rows take the vector path: each batch is still checked as dg_assemble_batch
   // checks it, in batch order, before its launch.
   auto args_of = [&](int32_t b) {
     const int64_t p0 = packed_ptr_host[b], p1 = packed_ptr_host[b + 1];
@@ -319,12 +320,10 @@ extern "C" int dg_assemble_batches(const void *cache, int64_t cache_rows, const 
     if (rc != DG_OK) return rc;
     RowShape sh{};
     int G = 1;
-    if (a[0].n > 0 && shape16(cache, a[0], row_bytes, &sh)) {
+    if (a[0].n > 0 && row_shape16(row_bytes, &sh)) {
       while (G < ASM_GROUP && G < n_outs && b + G < B) {
         const AsmArgs c = args_of(b + G);
-        RowShape sc{};
-        bool apart = c.n > 0 && shape16(cache, c, row_bytes, &sc) && sc.lpr == sh.lpr &&
-                     sc.cpl == sh.cpl;
+        bool apart = c.n > 0;
         for (int q = 0; apart && q < G; ++q)
           apart = !overlaps(c.out, c.n * row_bytes, a[q].out, a[q].n * row_bytes) &&
                   !overlaps(c.out, c.n * row_bytes, a[q].loc, a[q].n * 4) &&

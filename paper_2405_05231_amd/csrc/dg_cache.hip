@@ -259,10 +259,16 @@ int keysort_count(KeySort &a, int64_t *totals, hipStream_t s) {
 constexpr int G_THREADS = 256;
 constexpr int G_UNROLL = 4;
 
-template <int LPR, int CPL>
-__global__ __launch_bounds__(G_THREADS) void k_gather16(const v4u *X, int64_t N,
-                                                        const int32_t *ids, int64_t n, int C,
-                                                        v4u *out, uint32_t *err) {
+// Bound by HBM.  NT: nontemporal stores, for rows that are whole 128-byte lines;
+// other rows share their first and last lines with their neighbours, and plain
+// stores let those merge in L2.  4M random rows, plain against nontemporal:
+// 48 B 148 / 291 us, 100 B 290 / 453, 160 B 315 / 389, 200 B 433 / 582 (711
+// with the 8-byte words such rows used to take); 512 B 194 / 180 (1M rows),
+// 1.5 KiB 386 / 349.
+template <int LPR, int CPL, bool NT>
+__global__ __launch_bounds__(G_THREADS) void k_gather16(const char *X, int64_t N,
+                                                        const int32_t *ids, int64_t n, int R,
+                                                        char *out, uint32_t *err) {
   constexpr int GPB = G_THREADS / LPR;
   const int sub = threadIdx.x % LPR;
   const int64_t grp = (int64_t)blockIdx.x * GPB + threadIdx.x / LPR;
@@ -275,7 +281,7 @@ __global__ __launch_bounds__(G_THREADS) void k_gather16(const v4u *X, int64_t N,
     int32_t id[G_UNROLL];
 #pragma unroll
     for (int u = 0; u < G_UNROLL; ++u) id[u] = ids[j0 + u < n ? j0 + u : n - 1];
-    const v4u *src[G_UNROLL];
+    const char *src[G_UNROLL];
     bool ok[G_UNROLL];
     bool bad = false;
 #pragma unroll
@@ -283,16 +289,14 @@ __global__ __launch_bounds__(G_THREADS) void k_gather16(const v4u *X, int64_t N,
       const int64_t j = j0 + u < n ? j0 + u : n - 1;
       ok[u] = id[u] >= 0 && (int64_t)id[u] < N;
       bad |= j0 + u < n && !ok[u];
-      src[u] = ok[u] ? X + (int64_t)id[u] * C : out + j * C;
+      src[u] = ok[u] ? X + (int64_t)id[u] * R : out + j * R;
     }
     v4u v[G_UNROLL][CPL];
 #pragma unroll
     for (int u = 0; u < G_UNROLL; ++u)
 #pragma unroll
-      for (int c = 0; c < CPL; ++c) {
-        const int ch = sub + c * LPR;
-        v[u][c] = ld_stream(src[u] + (ch < C ? ch : C - 1));
-      }
+      for (int c = 0; c < CPL; ++c)
+        v[u][c] = ld_stream(src[u] + row_vec(sub + c * LPR, R));
     if (bad && sub == 0 && err) atomicOr(err, ERR_NODE_RANGE);
 #pragma unroll
     for (int u = 0; u < G_UNROLL; ++u) {
@@ -301,7 +305,8 @@ __global__ __launch_bounds__(G_THREADS) void k_gather16(const v4u *X, int64_t N,
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
           const int ch = sub + c * LPR;
-          if (ch < C) st_stream(ok[u] ? v[u][c] : v4u{0u, 0u, 0u, 0u}, out + j * C + ch);
+          if (row_has(ch, R))
+            st_vec<NT>(ok[u] ? v[u][c] : v4u{0u, 0u, 0u, 0u}, out + j * R + row_vec(ch, R));
         }
       }
     }
@@ -325,13 +330,18 @@ __global__ __launch_bounds__(G_THREADS) void k_gather_any(const T *X, int64_t N,
 }
 
 template <int LPR, int CPL>
-void gather16(const void *X, int64_t N, const int32_t *ids, int64_t n, int C, void *out,
-              uint32_t *err, hipStream_t s) {
+int gather16(const void *X, int64_t N, const int32_t *ids, int64_t n, int R, void *out,
+             uint32_t *err, hipStream_t s) {
   constexpr int GPB = G_THREADS / LPR;
   int64_t blocks = ((n + G_UNROLL - 1) / G_UNROLL + GPB - 1) / GPB;
   if (blocks > (1ll << 20)) blocks = 1ll << 20;
-  hipLaunchKernelGGL((k_gather16<LPR, CPL>), dim3((unsigned)blocks), dim3(G_THREADS), 0, s,
-                     (const v4u *)X, N, ids, n, C, (v4u *)out, err);
+  auto go = [&](auto nt) {
+    hipLaunchKernelGGL((k_gather16<LPR, CPL, decltype(nt)::value>), dim3((unsigned)blocks),
+                       dim3(G_THREADS), 0, s, (const char *)X, N, ids, n, R, (char *)out, err);
+  };
+  if (R % 128 == 0) go(std::true_type());
+  else go(std::false_type());
+  return DG_OK;
 }
 
 template <typename T>
@@ -356,15 +366,11 @@ int launch_gather(const void *X, int64_t N, int64_t row_bytes, const int32_t *id
   if (n == 0) return DG_OK;
   const int w = word_bytes(row_bytes, {X, out});
   RowShape sh;
-  if (w == 16 && row_shape16(row_bytes / 16, &sh)) {
-    const int C = (int)(row_bytes / 16);
-    if (sh.lpr == 4) gather16<4, 1>(X, N, ids, n, C, out, err, s);
-    else if (sh.lpr == 8) gather16<8, 1>(X, N, ids, n, C, out, err, s);
-    else if (sh.lpr == 16) gather16<16, 1>(X, N, ids, n, C, out, err, s);
-    else if (sh.lpr == 32 && sh.cpl == 1) gather16<32, 1>(X, N, ids, n, C, out, err, s);
-    else if (sh.lpr == 64 && sh.cpl == 1) gather16<64, 1>(X, N, ids, n, C, out, err, s);
-    else if (sh.lpr == 64 && sh.cpl == 2) gather16<64, 2>(X, N, ids, n, C, out, err, s);
-    else gather16<64, 4>(X, N, ids, n, C, out, err, s);
+  if (row_shape16(row_bytes, &sh)) {
+    with_shape(sh, [&](auto lpr, auto cpl) {
+      return gather16<decltype(lpr)::value, decltype(cpl)::value>(X, N, ids, n, (int)row_bytes,
+                                                                  out, err, s);
+    });
   } else if (w == 16) {
     gather_any<uint4>(X, N, ids, n, row_bytes, out, err, s);
   } else if (w == 8) {

@@ -12,23 +12,29 @@ namespace {
 
 constexpr int THREADS = 256;
 
-// Fan-out gather, 16-byte path: a group of LPR lanes reads the row of one U_nc
+// Fan-out gather, vector path: a group of LPR lanes reads the row of one U_nc
 // node once and stores it into each of its destination rows.  Every U_nc node
 // has at least one destination; its first destination index is loaded together
 // with the row, so the common single-destination case needs two dependent
-// round trips (indices, then row + destination) before its stores.
+// round trips (indices, then row + destination) before its stores.  Bound by
+// HBM; nontemporal loads, and nontemporal stores (NT) where rows are whole
+// 128-byte lines: with plain stores the launch itself is up to 15% shorter
+// (512-byte rows at 1M nodes: 88 against 104 us), but the assembly that follows
+// takes that time back (whole step 1.339 against 1.332 ms).  Other rows share
+// lines with their neighbours and take plain stores (400-byte rows: packing of
+// 32 lists 550 us against 559).
 // Items n_unc .. n_unc + n_cache - 1 fill the cache table, the cache taken as
 // one more mini-batch of the same pass: item n_unc + s copies the row of
 // cache_nodes[s] into cache row s (a slot holding -1 is left as it is; an ID
 // outside [0, N) is reported and its row left as it is).
-template <int LPR, int CPL>
-__global__ __launch_bounds__(THREADS) void k_fanout16(const v4u *X, int64_t N,
+template <int LPR, int CPL, bool NT>
+__global__ __launch_bounds__(THREADS) void k_fanout16(const char *X, int64_t N,
                                                       const int32_t *unc_ids,
                                                       const int64_t *unc_off, int64_t n_unc,
                                                       int64_t n_pairs, const int64_t *pairdest,
-                                                      int C, v4u *packed,
+                                                      int R, char *packed,
                                                       const int32_t *cache_nodes,
-                                                      int64_t n_cache, v4u *cache_table,
+                                                      int64_t n_cache, char *cache_table,
                                                       uint32_t *err) {
   constexpr int UNROLL = rows_in_flight(CPL);
   constexpr int GPB = THREADS / LPR;
@@ -58,35 +64,36 @@ __global__ __launch_bounds__(THREADS) void k_fanout16(const v4u *X, int64_t N,
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       d0[u] = p1[u] > p0[u] ? pairdest[p0[u]] : -1;
-      const v4u *src = id[u] >= 0 ? X + (int64_t)id[u] * C : nullptr;
+      const char *src = id[u] >= 0 ? X + (int64_t)id[u] * R : nullptr;
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
         const int ch = sub + c * LPR;
-        v[u][c] = (src && ch < C) ? ld_stream(src + ch) : v4u{0u, 0u, 0u, 0u};
+        v[u][c] = (src && row_has(ch, R)) ? ld_stream(src + row_vec(ch, R))
+                                          : v4u{0u, 0u, 0u, 0u};
       }
     }
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       const int64_t i = i0 + u;
-      v4u *dst;
+      char *dst;
       if (i >= n_unc) {  // a cache row
         if (i >= n_items || id[u] < 0) continue;
-        dst = cache_table + (i - n_unc) * C;
+        dst = cache_table + (i - n_unc) * R;
       } else {
         if (d0[u] < 0) continue;
-        dst = packed + d0[u] * C;
+        dst = packed + d0[u] * R;
       }
 #pragma unroll
       for (int c = 0; c < CPL; ++c) {
         const int ch = sub + c * LPR;
-        if (ch < C) st_stream(v[u][c], dst + ch);
+        if (row_has(ch, R)) st_vec<NT>(v[u][c], dst + row_vec(ch, R));
       }
       for (int64_t p = p0[u] + 1; p < p1[u]; ++p) {
-        dst = packed + pairdest[p] * C;
+        dst = packed + pairdest[p] * R;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
           const int ch = sub + c * LPR;
-          if (ch < C) st_stream(v[u][c], dst + ch);
+          if (row_has(ch, R)) st_vec<NT>(v[u][c], dst + row_vec(ch, R));
         }
       }
     }
@@ -129,15 +136,21 @@ __global__ __launch_bounds__(THREADS) void k_fanout_any(const T *X, int64_t N,
 
 
 template <int LPR, int CPL>
-void launch16(const RowCopy &r, int C, hipStream_t s) {
+int launch16(const RowCopy &r, hipStream_t s) {
   constexpr int GPB = THREADS / LPR;
   constexpr int UNROLL = rows_in_flight(CPL);
   int64_t groups = (r.n + r.n_cache + UNROLL - 1) / UNROLL;
   int64_t blocks = (groups + GPB - 1) / GPB;
   if (blocks > (1ll << 20)) blocks = 1ll << 20;
-  hipLaunchKernelGGL((k_fanout16<LPR, CPL>), dim3((unsigned)blocks), dim3(THREADS), 0, s,
-                     (const v4u *)r.X, r.N, r.ids, r.off, r.n, r.pairs, r.dest, C,
-                     (v4u *)r.packed, r.cache_nodes, r.n_cache, (v4u *)r.cache_table, r.err);
+  auto go = [&](auto nt) {
+    hipLaunchKernelGGL((k_fanout16<LPR, CPL, decltype(nt)::value>), dim3((unsigned)blocks),
+                       dim3(THREADS), 0, s, (const char *)r.X, r.N, r.ids, r.off, r.n, r.pairs,
+                       r.dest, (int)r.row_bytes, (char *)r.packed, r.cache_nodes, r.n_cache,
+                       (char *)r.cache_table, r.err);
+  };
+  if (r.row_bytes % 128 == 0) go(std::true_type());
+  else go(std::false_type());
+  return DG_OK;
 }
 
 template <typename T>
@@ -156,15 +169,10 @@ int launch_fanout(const RowCopy &r, hipStream_t s) {
   if (r.n + r.n_cache == 0) return DG_OK;
   const int w = word_bytes(r.row_bytes, {r.X, r.packed, r.cache_table});
   RowShape sh;
-  if (w == 16 && row_shape16(r.row_bytes / 16, &sh)) {
-    const int C = (int)(r.row_bytes / 16);
-    if (sh.lpr == 4) launch16<4, 1>(r, C, s);
-    else if (sh.lpr == 8) launch16<8, 1>(r, C, s);
-    else if (sh.lpr == 16) launch16<16, 1>(r, C, s);
-    else if (sh.lpr == 32 && sh.cpl == 1) launch16<32, 1>(r, C, s);
-    else if (sh.lpr == 64 && sh.cpl == 1) launch16<64, 1>(r, C, s);
-    else if (sh.lpr == 64 && sh.cpl == 2) launch16<64, 2>(r, C, s);
-    else launch16<64, 4>(r, C, s);
+  if (row_shape16(r.row_bytes, &sh)) {
+    with_shape(sh, [&](auto lpr, auto cpl) {
+      return launch16<decltype(lpr)::value, decltype(cpl)::value>(r, s);
+    });
   } else if (w == 16) {
     launch_any<uint4>(r, s);
   } else if (w == 8) {
