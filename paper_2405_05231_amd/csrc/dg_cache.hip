@@ -27,16 +27,23 @@ namespace {
 constexpr int KEYS = 65;  // keys 0..64
 constexpr int CF_WAVES = 4;
 constexpr int CF_THREADS = 64 * CF_WAVES;
-constexpr int CF_ROUNDS = 16;
-constexpr int CF_BLOCK = 64 * CF_ROUNDS * CF_WAVES;
+constexpr int CF_FLIGHT = 16;  // rounds of 64 elements whose keys are loaded together
 
-// A stable counting sort of a list by a key in 0..64: per-block counts of
-// every key, a scan down each key's column, then ranks from block bases +
-// earlier waves + earlier rounds + ballot prefixes.  Two uses:
+// A stable counting sort of a list by a key in 0..64.  Each wave owns 64*R
+// consecutive elements (a column of the count matrix): it counts its keys, a
+// scan runs along each key's row, and the ranks are the wave's base of the key
+// plus earlier rounds plus the lanes below with the same key.  Two uses:
 //   FREQ:    list = nodes 0..N-1, key = access count (popcount of the
-//            membership word), ranked by count descending;
+//            membership word), ranked by count descending; key 0 (not
+//            accessed) is neither counted nor ranked;
 //   MINHASH: list = the disk-cache entries V_d, key = the entry's MinHash
 //            value (64 = in no sample), ranked ascending.
+// The count pass leaves each element's key as a byte for the place pass, where
+// the workspace has room: the membership words are read once.  Bound by HBM
+// (FREQ at 50M nodes: 400 MB of words, 2 x 50 MB of keys, 200 MB of slots; the
+// whole call 393 -> 238 us) or by the scattered words (MINHASH: 1M entries
+// 275 -> 63 us).  Counting with one step per distinct key of a round had been
+// bound by issue: 120 + 207 us for the two passes at 50M nodes, now 92 + 110.
 enum Mode { FREQ = 0, MINHASH = 1 };
 
 struct KeySort {
@@ -44,214 +51,367 @@ struct KeySort {
   uint64_t keep;      // bits of the group's batches
   int64_t N;          // nodes
   int64_t n;          // list length
-  int64_t nblk;
-  uint32_t *cnt;      // [nblk][KEYS]
-  int64_t *base;      // [nblk][KEYS] exclusive scans down each key
-  int64_t *totals;    // [KEYS]
-  int64_t first[KEYS];  // rank of the first element of each key (host-computed)
-  uint32_t *err;
+  int64_t ncol;       // waves
+  uint32_t *cnt;      // [KEYS + 1][ncol] counts, then exclusive scans along each key's
+                      // row; the last row holds each wave's error bits (MINHASH)
+  int64_t *totals;    // [KEYS + 1]: per key; the error bits
+  uint8_t *keys;      // [n] each element's key; NULL: the place pass finds it again
   // FREQ outputs
   int64_t cap;
   int32_t *cache_slot;
   int32_t *cache_nodes;
   // MINHASH input / outputs
   const int32_t *ids;    // V_d
-  const int32_t *minv;   // [64] min over hash functions of each sample's value
+  const int32_t *perms;  // [k][B]
+  int32_t k, B;
   int32_t *order;        // V_r
   int32_t *signature;    // S(v) per entry (-1: in no sample)
 };
 
+// MINHASH: the smallest value of each set of samples is found a byte of the
+// membership word at a time: s_low[q][x] = min over the bits of x of the
+// values M(8q + bit), M(i) = min_j H_j(i); 64 for no bit.
+struct LowTable {
+  uint8_t v[8][256];
+};
+
+// Fills the table (whole block); returns the block's error bits to thread 0.
 template <int MODE>
-__device__ __forceinline__ int key_of(const KeySort &a, int64_t i, const int32_t *s_minv) {
-  if (i >= a.n) return -1;
-  if (MODE == FREQ) return __popcll(a.mask[i] & a.keep);
-  const int32_t v = a.ids[i];
-  if (v < 0 || (int64_t)v >= a.N) {
-    atomicOr(a.err, ERR_NODE_RANGE);
-    return 64;
+__device__ __forceinline__ uint32_t stage_low(const KeySort &a, LowTable *t) {
+  uint32_t bad = 0;
+  if (MODE == MINHASH) {
+    __shared__ uint8_t s_min[64];
+    if (threadIdx.x < 64) {
+      const int i = threadIdx.x;
+      int m = 64;
+      if (i < a.B)
+        for (int j = 0; j < a.k; ++j) {
+          const int32_t h = a.perms[(int64_t)j * a.B + i];
+          if (h < 0 || h >= a.B) bad = ERR_ROW_RANGE;
+          else m = min(m, (int)h);
+        }
+      s_min[i] = (uint8_t)m;
+      bad = __ballot(bad != 0) ? ERR_ROW_RANGE : 0u;
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < 8 * 256; x += CF_THREADS) {
+      const int q = x >> 8;
+      int m = 64;
+#pragma unroll
+      for (int bit = 0; bit < 8; ++bit)
+        if ((x >> bit) & 1) m = min(m, (int)s_min[8 * q + bit]);
+      t->v[q][x & 255] = (uint8_t)m;
+    }
+    __syncthreads();
   }
-  uint64_t m = a.mask[v] & a.keep;
-  int key = 64;  // S(v) = inf: v is required by no sample
-  while (m) {
-    const int b = __ffsll((long long)m) - 1;
-    m &= m - 1;
-    key = min(key, s_minv[b]);
-  }
-  return key;
+  return bad;
 }
 
-template <int MODE>
+// Keys of U rounds from element t0 (-1 past the list), all their loads issued
+// before any is used.
+template <int MODE, int U>
 __device__ __forceinline__ void load_keys(const KeySort &a, int64_t t0, int lane,
-                                          const int32_t *s_minv, int (&k)[CF_ROUNDS]) {
+                                          const LowTable *low, int (&k)[U], uint32_t *bad) {
+  uint64_t m[U];
+  if (MODE == FREQ) {
 #pragma unroll
-  for (int r = 0; r < CF_ROUNDS; ++r) k[r] = key_of<MODE>(a, t0 + r * 64 + lane, s_minv);
-}
-
-// Counts of every key in one wave tile (lane k < 64 keeps key k's count; key 64
-// is returned separately).
-__device__ __forceinline__ void wave_key_counts(const int (&k)[CF_ROUNDS], int lane,
-                                                uint32_t *mine, uint32_t *k64) {
-  uint32_t c = 0, top = 0;
+    for (int r = 0; r < U; ++r) {
+      const int64_t i = t0 + r * 64 + lane;
+      m[r] = a.mask[i < a.n ? i : a.n - 1];
+    }
+  } else {
+    int32_t v[U];
 #pragma unroll
-  for (int r = 0; r < CF_ROUNDS; ++r) {
-    int key = k[r];
-    uint64_t pending = __ballot(key >= 0);
-    while (pending) {  // one iteration per distinct key present in the round
-      const int src = __ffsll((long long)pending) - 1;
-      const int kk = __shfl(key, src, 64);
-      const uint64_t bal = __ballot(key == kk);
-      pending &= ~bal;
-      if (kk == 64) top += (uint32_t)__popcll(bal);
-      else if (lane == kk) c += (uint32_t)__popcll(bal);
+    for (int r = 0; r < U; ++r) {
+      const int64_t i = t0 + r * 64 + lane;
+      v[r] = i < a.n ? a.ids[i] : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const bool ok = v[r] >= 0 && (int64_t)v[r] < a.N;
+      if (!ok) *bad |= ERR_NODE_RANGE;
+      m[r] = ok ? a.mask[v[r]] : 0ull;
     }
   }
-  *mine = c;
-  *k64 = top;
-}
-
-template <int MODE>
-__device__ __forceinline__ void stage_minv(const KeySort &a, int32_t *s_minv) {
-  if (MODE == MINHASH && threadIdx.x < 64) s_minv[threadIdx.x] = a.minv[threadIdx.x];
-  __syncthreads();
-}
-
-template <int MODE>
-__global__ __launch_bounds__(CF_THREADS) void k_key_count(KeySort a) {
-  __shared__ uint32_t s_cnt[CF_WAVES][KEYS];
-  __shared__ int32_t s_minv[64];
-  stage_minv<MODE>(a, s_minv);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t t0 = (int64_t)blockIdx.x * CF_BLOCK + (int64_t)w * 64 * CF_ROUNDS;
-  int k[CF_ROUNDS];
-  load_keys<MODE>(a, t0, lane, s_minv, k);
-  uint32_t mine, top;
-  wave_key_counts(k, lane, &mine, &top);
-  s_cnt[w][lane] = mine;
-  if (lane == 0) s_cnt[w][64] = top;
-  __syncthreads();
-  for (int i = threadIdx.x; i < KEYS; i += CF_THREADS) {
-    uint32_t v = 0;
-    for (int j = 0; j < CF_WAVES; ++j) v += s_cnt[j][i];
-    a.cnt[(size_t)blockIdx.x * KEYS + i] = v;
-  }
-}
-
-// One block per key: exclusive scan of that key's per-block counts.
-__global__ __launch_bounds__(1024) void k_key_scan(KeySort a) {
-  __shared__ int64_t s_w[16];
-  const int key = blockIdx.x;
-  int64_t carry = 0;
-  for (int64_t c0 = 0; c0 < a.nblk; c0 += 1024) {
-    const int64_t i = c0 + threadIdx.x;
-    const int64_t v = i < a.nblk ? (int64_t)a.cnt[(size_t)i * KEYS + key] : 0;
-    int64_t incl = wave_incl_sum(v);
-    if ((threadIdx.x & 63) == 63) s_w[threadIdx.x >> 6] = incl;
-    __syncthreads();
-    int64_t before = 0, sum = 0;
-    for (int j = 0; j < 16; ++j) {
-      if (j < (int)(threadIdx.x >> 6)) before += s_w[j];
-      sum += s_w[j];
-    }
-    __syncthreads();
-    if (i < a.nblk) a.base[(size_t)i * KEYS + key] = carry + before + incl - v;
-    carry += sum;
-  }
-  if (threadIdx.x == 0) a.totals[key] = carry;
-}
-
-template <int MODE>
-__global__ __launch_bounds__(CF_THREADS) void k_key_place(KeySort a) {
-  __shared__ uint32_t s_cnt[CF_WAVES][KEYS];
-  __shared__ int32_t s_minv[64];
-  stage_minv<MODE>(a, s_minv);
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t t0 = (int64_t)blockIdx.x * CF_BLOCK + (int64_t)w * 64 * CF_ROUNDS;
-  int k[CF_ROUNDS];
-  load_keys<MODE>(a, t0, lane, s_minv, k);
-  uint32_t mine, top;
-  wave_key_counts(k, lane, &mine, &top);
-  s_cnt[w][lane] = mine;
-  if (lane == 0) s_cnt[w][64] = top;
-  __syncthreads();
-  const int64_t *bb = a.base + (size_t)blockIdx.x * KEYS;
-  int64_t run = a.first[lane] + bb[lane];  // running rank of key `lane`
-  int64_t run64 = a.first[64] + bb[64];
-  for (int j = 0; j < w; ++j) {
-    run += s_cnt[j][lane];
-    run64 += s_cnt[j][64];
-  }
-  const uint64_t lt = lanes_below();
 #pragma unroll
-  for (int r = 0; r < CF_ROUNDS; ++r) {
-    const int key = k[r];
+  for (int r = 0; r < U; ++r) {
     const int64_t i = t0 + r * 64 + lane;
-    uint64_t pending = __ballot(key >= 0);
-    int64_t rank = -1;
-    while (pending) {
-      const int src = __ffsll((long long)pending) - 1;
-      const int kk = __shfl(key, src, 64);
-      const uint64_t bal = __ballot(key == kk);
-      pending &= ~bal;
-      const int64_t start = kk == 64 ? run64 : read_lane(run, kk);
-      if (key == kk) rank = start + __popcll(bal & lt);
-      if (kk == 64) run64 += __popcll(bal);
-      else if (lane == kk) run += __popcll(bal);
+    const uint64_t x = m[r] & a.keep;
+    int key;
+    if (MODE == FREQ) {
+      key = __popcll(x);
+    } else {
+      key = 64;  // S(v) = inf: v is required by no sample
+#pragma unroll
+      for (int q = 0; q < 8; ++q) key = min(key, (int)low->v[q][(x >> (8 * q)) & 255u]);
     }
-    if (key >= 0) {
+    k[r] = i < a.n ? key : -1;
+  }
+}
+
+// The lanes of `act` that hold this lane's key (for a lane of act), by one
+// ballot per key bit.
+__device__ __forceinline__ uint64_t same_key(int key, uint64_t act) {
+  uint64_t m = act;
+#pragma unroll
+  for (int bit = 0; bit < 7; ++bit) {
+    const bool one = (key >> bit) & 1;
+    const uint64_t b = __ballot(one);
+    m &= one ? b : ~b;
+  }
+  return m;
+}
+
+template <int MODE, int R>
+__global__ __launch_bounds__(CF_THREADS) void k_key_count(KeySort a) {
+  constexpr int U = R < CF_FLIGHT ? R : CF_FLIGHT;
+  __shared__ uint32_t s_cnt[CF_WAVES][KEYS + 3];
+  __shared__ LowTable s_low[1];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t bad = stage_low<MODE>(a, s_low);
+  const int64_t col = (int64_t)blockIdx.x * CF_WAVES + w;
+  uint32_t *cnt = s_cnt[w];  // this wave's own: its LDS operations run in order
+  cnt[lane] = 0u;
+  if (lane == 0) cnt[64] = 0u;
+  __builtin_amdgcn_wave_barrier();
+  for (int c = 0; c < R; c += U) {
+    const int64_t t0 = (col * R + c) * 64;
+    if (t0 >= a.n) break;  // uniform
+    int k[U];
+    load_keys<MODE, U>(a, t0, lane, s_low, k, &bad);
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const int64_t i = t0 + r * 64 + lane;
+      if (a.keys && k[r] >= 0) a.keys[i] = (uint8_t)k[r];
+      const bool counted = k[r] >= (MODE == FREQ ? 1 : 0);
+      const uint64_t act = __ballot(counted);
+      if (!act) continue;  // uniform
+      if (__popcll(act) <= 16) {  // few: one LDS add each
+        if (counted) atomicAdd(&cnt[k[r]], 1u);
+      } else {  // many, perhaps of one key: one add per key
+        const uint64_t same = same_key(k[r], act);
+        if (counted && __builtin_ctzll(same) == lane) atomicAdd(&cnt[k[r]], (uint32_t)__popcll(same));
+      }
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (col < a.ncol) {
+    a.cnt[(int64_t)lane * a.ncol + col] = cnt[lane];
+    if (lane == 0) a.cnt[64 * a.ncol + col] = cnt[64];
+    if (MODE == MINHASH) {
+      const uint32_t node = __ballot((bad & ERR_NODE_RANGE) != 0) ? (uint32_t)ERR_NODE_RANGE : 0u;
+      const uint32_t row = __ballot((bad & ERR_ROW_RANGE) != 0) ? (uint32_t)ERR_ROW_RANGE : 0u;
+      if (lane == 0) a.cnt[65 * a.ncol + col] = node | row;
+    }
+  }
+}
+
+// One block per row: exclusive scan in place of a key's counts, or (row KEYS) the
+// OR of the error bits.
+constexpr int KS_ITEMS = 8;
+__global__ __launch_bounds__(1024) void k_key_scan(KeySort a) {
+  __shared__ uint32_t s_w[KS_ITEMS][16];
+  const int row = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t *p = a.cnt + (int64_t)row * a.ncol;
+  uint32_t carry = 0;
+  for (int64_t c0 = 0; c0 < a.ncol; c0 += 1024 * KS_ITEMS) {
+    uint32_t v[KS_ITEMS], incl[KS_ITEMS];
+#pragma unroll
+    for (int q = 0; q < KS_ITEMS; ++q) {
+      const int64_t i = c0 + q * 1024 + threadIdx.x;
+      v[q] = i < a.ncol ? p[i] : 0u;
+    }
+    if (row == KEYS) {
+#pragma unroll
+      for (int q = 0; q < KS_ITEMS; ++q) carry |= v[q];
+      continue;
+    }
+#pragma unroll
+    for (int q = 0; q < KS_ITEMS; ++q) {
+      incl[q] = (uint32_t)wave_incl_sum_i32((int32_t)v[q]);
+      if (lane == 63) s_w[q][w] = incl[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < KS_ITEMS; ++q) {
+      uint32_t before = 0, sum = 0;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const uint32_t x = s_w[q][j];
+        before += j < w ? x : 0u;
+        sum += x;
+      }
+      const int64_t i = c0 + q * 1024 + threadIdx.x;
+      if (i < a.ncol) p[i] = carry + before + incl[q] - v[q];
+      carry += sum;
+    }
+    __syncthreads();
+  }
+  if (row == KEYS) {
+    const uint32_t node = __syncthreads_or((int)(carry & ERR_NODE_RANGE)) ? (uint32_t)ERR_NODE_RANGE : 0u;
+    const uint32_t hash = __syncthreads_or((int)(carry & ERR_ROW_RANGE)) ? (uint32_t)ERR_ROW_RANGE : 0u;
+    carry = node | hash;
+  }
+  if (threadIdx.x == 0) a.totals[row] = (int64_t)carry;
+}
+
+template <int MODE, int R>
+__global__ __launch_bounds__(CF_THREADS) void k_key_place(KeySort a) {
+  constexpr int U = R < CF_FLIGHT ? R : CF_FLIGHT;
+  __shared__ uint32_t s_run[CF_WAVES][KEYS + 3];  // next rank of each key
+  __shared__ LowTable s_low[1];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t bad = 0;
+  if (!a.keys) (void)stage_low<MODE>(a, s_low);
+  const int64_t col = (int64_t)blockIdx.x * CF_WAVES + w;
+  const int64_t at = col < a.ncol ? col : a.ncol - 1;
+  // rank of the first element of each key (lane k: key k), and key 64's
+  const int32_t tot = (int32_t)a.totals[lane], tot64 = (int32_t)a.totals[64];
+  const int32_t incl = wave_incl_sum_i32(tot);
+  const int32_t all = __builtin_amdgcn_readlane(incl, 63);  // keys 0..63 (FREQ: 1..63)
+  const int32_t first = MODE == FREQ ? tot64 + all - incl : incl - tot;
+  const int32_t first64 = MODE == FREQ ? 0 : all;
+  uint32_t *run = s_run[w];  // this wave's own
+  run[lane] = (uint32_t)first + a.cnt[(int64_t)lane * a.ncol + at];
+  if (lane == 0) run[64] = (uint32_t)first64 + a.cnt[64 * a.ncol + at];
+  // FREQ: keys from `cut` on have a rank below cap (first is non-increasing in
+  // the key); cut = 65: none has
+  int cut = 0;
+  if (MODE == FREQ) {
+    const uint64_t in = __ballot(lane > 0 && (int64_t)first < a.cap);
+    cut = in ? __builtin_ctzll(in) : ((int64_t)first64 < a.cap ? 64 : 65);
+    // slots no node takes
+    const int64_t used = (int64_t)tot64 + all;
+    for (int64_t r = used + (int64_t)blockIdx.x * CF_THREADS + threadIdx.x; r < a.cap;
+         r += (int64_t)gridDim.x * CF_THREADS)
+      a.cache_nodes[r] = -1;
+  }
+  __builtin_amdgcn_wave_barrier();
+  const uint64_t lt = lanes_below();
+  for (int c = 0; c < R; c += U) {
+    const int64_t t0 = (col * R + c) * 64;
+    if (t0 >= a.n) break;  // uniform
+    int k[U];
+    int32_t id[U];
+    if (a.keys) {
+#pragma unroll
+      for (int r = 0; r < U; ++r) {
+        const int64_t i = t0 + r * 64 + lane;
+        k[r] = i < a.n ? (int)a.keys[i] : -1;
+      }
+    } else {
+      load_keys<MODE, U>(a, t0, lane, s_low, k, &bad);
+    }
+    if (MODE == MINHASH) {
+#pragma unroll
+      for (int r = 0; r < U; ++r) {
+        const int64_t i = t0 + r * 64 + lane;
+        id[r] = i < a.n ? a.ids[i] : 0;
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const int64_t i = t0 + r * 64 + lane;
+      const bool cand = k[r] >= cut;  // past the list: -1, never
+      const uint64_t act = __ballot(cand);
+      int64_t rank = -1;
+      if (act) {  // uniform
+        if (__popcll(act) <= 6) {  // few: one step per key present
+          uint64_t todo = act;
+          while (todo) {
+            const int src = __builtin_ctzll(todo);
+            const int kk = __builtin_amdgcn_readlane(k[r], src);
+            const uint64_t same = __ballot(k[r] == kk);
+            todo &= ~same;
+            const uint32_t at0 = run[kk];
+            if (k[r] == kk) rank = (int64_t)at0 + __popcll(same & lt);
+            if (lane == src) run[kk] = at0 + (uint32_t)__popcll(same);
+            __builtin_amdgcn_wave_barrier();
+          }
+        } else {
+          const uint64_t same = same_key(k[r], act);
+          if (cand) {
+            const uint32_t at0 = run[k[r]];
+            rank = (int64_t)at0 + __popcll(same & lt);
+            __builtin_amdgcn_wave_barrier();
+            if (__builtin_ctzll(same) == lane) run[k[r]] = at0 + (uint32_t)__popcll(same);
+          }
+          __builtin_amdgcn_wave_barrier();
+        }
+      }
+      if (k[r] < 0) continue;
       if (MODE == FREQ) {
-        const bool cached = key > 0 && rank < a.cap;
+        const bool cached = cand && rank < a.cap;
         a.cache_slot[i] = cached ? (int32_t)rank : -1;
         if (cached) a.cache_nodes[rank] = (int32_t)i;
       } else {
-        a.order[rank] = a.ids[i];
-        if (a.signature) a.signature[i] = key == 64 ? -1 : key;
+        a.order[rank] = id[r];
+        if (a.signature) a.signature[i] = k[r] == 64 ? -1 : k[r];
       }
     }
   }
 }
 
-__global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
+// Rounds per wave: short tiles until the chip's 8192 wave slots are filled, then
+// longer ones, so that the count matrix stays small.  Count, scan and place of
+// the frequency ranking (5% of the nodes cached, 10% accessed): 20M nodes 86 us
+// with 16 rounds, 99 with 64; 50M nodes 215 and 219, and a quarter of the matrix.
+int key_rounds(int64_t n) {
+  if (n >= (int64_t)8192 * 64 * 64) return 64;
+  return n >= (int64_t)8192 * 64 * 8 ? 16 : 4;
+}
+int64_t key_cols(int64_t n, int rounds) {
+  const int64_t c = (n + 64 * rounds - 1) / (64 * rounds);
+  return c < 1 ? 1 : c;  // an empty list: one wave (MINHASH checks the permutations)
 }
 
-// M(i) = min over the k hash functions of H_j(i); values checked to lie in [0, B).
-__global__ void k_minhash_min(const int32_t *perms, int32_t k, int32_t B, int32_t *minv,
-                              uint32_t *err) {
-  const int i = threadIdx.x;
-  if (i >= 64) return;
-  int32_t m = 64;
-  if (i < B) {
-    for (int j = 0; j < k; ++j) {
-      const int32_t h = perms[(int64_t)j * B + i];
-      if (h < 0 || h >= B) atomicOr(err, ERR_ROW_RANGE);
-      else m = min(m, h);
-    }
+// with_keys: room for the key bytes, and the tile that suits n; without (a
+// workspace sized when the keys were read twice): the longest tile.
+int carve_keysort(KeySort &a, Carve &c, bool with_keys) {
+  const int rounds = with_keys ? key_rounds(a.n) : 64;
+  a.ncol = key_cols(a.n, rounds);
+  a.cnt = c.take<uint32_t>((size_t)(KEYS + 1) * (size_t)a.ncol);
+  a.totals = c.take<int64_t>(KEYS + 1);
+  a.keys = with_keys ? c.take<uint8_t>((size_t)a.n) : nullptr;
+  return rounds;
+}
+
+// Carves the larger layout if ws_bytes hold it, else the smaller one; returns the
+// rounds per wave, 0 if neither fits.
+int fit_keysort(KeySort &a, void *ws, size_t ws_bytes, size_t *need) {
+  for (bool with_keys : {true, false}) {
+    Carve c(ws);
+    const int rounds = carve_keysort(a, c, with_keys);
+    if (with_keys) *need = c.used;
+    if (c.used <= ws_bytes) return rounds;
   }
-  minv[i] = m;
+  return 0;
 }
 
-int64_t key_blocks(int64_t n) { return (n + CF_BLOCK - 1) / CF_BLOCK; }
-
-void carve_keysort(KeySort &a, Carve &c) {
-  a.nblk = key_blocks(a.n);
-  a.cnt = c.take<uint32_t>((size_t)a.nblk * KEYS);
-  a.base = c.take<int64_t>((size_t)a.nblk * KEYS);
-  a.totals = c.take<int64_t>(KEYS);
+size_t keysort_bytes(int64_t n) {
+  KeySort a;
+  memset(&a, 0, sizeof(a));
+  a.n = n;
+  Carve c(nullptr);
+  (void)carve_keysort(a, c, true);
+  return c.used;
 }
 
-// count pass + scans; returns the per-key totals on the host.
+// Count pass, scans and place pass; the totals come back to the host.
 template <int MODE>
-int keysort_count(KeySort &a, int64_t *totals, hipStream_t s) {
-  if (a.nblk == 0) {
-    for (int k = 0; k < KEYS; ++k) totals[k] = 0;
-    return DG_OK;
-  }
-  hipLaunchKernelGGL(k_key_count<MODE>, dim3((unsigned)a.nblk), dim3(CF_THREADS), 0, s, a);
-  hipLaunchKernelGGL(k_key_scan, dim3(KEYS), dim3(1024), 0, s, a);
+int keysort_run(KeySort &a, int rounds, int64_t *totals, hipStream_t s) {
+  const dim3 g((unsigned)((a.ncol + CF_WAVES - 1) / CF_WAVES)), b(CF_THREADS);
+  auto go = [&](auto r) {
+    constexpr int R = decltype(r)::value;
+    hipLaunchKernelGGL((k_key_count<MODE, R>), g, b, 0, s, a);
+    hipLaunchKernelGGL(k_key_scan, dim3(MODE == MINHASH ? KEYS + 1 : KEYS), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL((k_key_place<MODE, R>), g, b, 0, s, a);
+  };
+  if (rounds == 64) go(std::integral_constant<int, 64>());
+  else if (rounds == 16) go(std::integral_constant<int, 16>());
+  else go(std::integral_constant<int, 4>());
   DG_HIP(hipGetLastError());
-  DG_TRY(read_to_host(totals, a.totals, sizeof(int64_t) * KEYS, s));
+  DG_TRY(read_to_host(totals, a.totals, sizeof(int64_t) * (KEYS + 1), s));
   return DG_OK;
 }
 
@@ -391,13 +551,7 @@ int launch_gather(const void *X, int64_t N, int64_t row_bytes, const int32_t *id
 using namespace dg;
 
 extern "C" size_t dg_cache_workspace_bytes(int64_t num_nodes) {
-  if (num_nodes < 1) return 0;
-  KeySort a;
-  memset(&a, 0, sizeof(a));
-  a.n = num_nodes;
-  Carve c(nullptr);
-  carve_keysort(a, c);
-  return c.used;
+  return num_nodes < 1 ? 0 : keysort_bytes(num_nodes);
 }
 
 extern "C" int dg_cache_by_frequency(const uint64_t *membership, int64_t N, int32_t B,
@@ -409,51 +563,28 @@ extern "C" int dg_cache_by_frequency(const uint64_t *membership, int64_t N, int3
   if (N < 1 || N > 0x7fffffffll || B < 1 || B > DG_MAX_BATCHES || cache_rows < 0 ||
       cache_rows > N)
     return set_error(DG_EINVAL, "dg_cache_by_frequency: bad sizes");
-  const size_t need = dg_cache_workspace_bytes(N);
-  if (!ws || ws_bytes < need || ((uintptr_t)ws & 255))
-    return set_error(DG_EWORKSPACE, "dg_cache_by_frequency: workspace needs %zu bytes", need);
-  hipStream_t s = stream;
   KeySort a;
   memset(&a, 0, sizeof(a));
   a.mask = membership;
   a.keep = B == 64 ? ~0ull : ((1ull << B) - 1ull);
   a.N = N;
   a.n = N;
-  Carve c(ws);
-  carve_keysort(a, c);
   a.cap = cache_rows;
   a.cache_slot = cache_slot;
   a.cache_nodes = cache_nodes;
-  int64_t totals[KEYS];
-  int rc;
-  if ((rc = keysort_count<FREQ>(a, totals, s))) return rc;
-  // keys in rank order: 64, 63, ..., 1, then 0 (never cached)
-  int64_t run = 0;
-  for (int k = 64; k >= 1; --k) {
-    a.first[k] = run;
-    run += totals[k];
-  }
-  a.first[0] = run;
-  *cached = run < cache_rows ? run : cache_rows;
-  if (cache_rows > 0)
-    hipLaunchKernelGGL(k_fill_i32, dim3(256), dim3(256), 0, s, cache_nodes, cache_rows, -1);
-  hipLaunchKernelGGL(k_key_place<FREQ>, dim3((unsigned)a.nblk), dim3(CF_THREADS), 0, s, a);
-  DG_HIP(hipGetLastError());
-  DG_HIP(hipStreamSynchronize(s));
+  size_t need = 0;
+  const int rounds = fit_keysort(a, ws, ws_bytes, &need);
+  if (!ws || !rounds || ((uintptr_t)ws & 255))
+    return set_error(DG_EWORKSPACE, "dg_cache_by_frequency: workspace needs %zu bytes", need);
+  int64_t totals[KEYS + 1];
+  DG_TRY(keysort_run<FREQ>(a, rounds, totals, stream));
+  int64_t accessed = 0;
+  for (int k = 1; k < KEYS; ++k) accessed += totals[k];
+  *cached = accessed < cache_rows ? accessed : cache_rows;
   return DG_OK;
 }
 
-extern "C" size_t dg_minhash_workspace_bytes(int64_t m) {
-  if (m < 0) return 0;
-  KeySort a;
-  memset(&a, 0, sizeof(a));
-  a.n = m;
-  Carve c(nullptr);
-  (void)c.take<uint32_t>(64);  // error word
-  (void)c.take<int32_t>(64);   // per-sample minima
-  carve_keysort(a, c);
-  return c.used;
-}
+extern "C" size_t dg_minhash_workspace_bytes(int64_t m) { return m < 0 ? 0 : keysort_bytes(m); }
 
 extern "C" int dg_minhash_order(const uint64_t *membership, int64_t N, int32_t B,
                                 const int32_t *entries, int64_t m, const int32_t *perms,
@@ -463,40 +594,25 @@ extern "C" int dg_minhash_order(const uint64_t *membership, int64_t N, int32_t B
     return set_error(DG_EINVAL, "dg_minhash_order: null pointer argument");
   if (N < 1 || N > 0x7fffffffll || B < 1 || B > DG_MAX_BATCHES || m < 0 || k < 1)
     return set_error(DG_EINVAL, "dg_minhash_order: bad sizes");
-  const size_t need = dg_minhash_workspace_bytes(m);
-  if (!ws || ws_bytes < need || ((uintptr_t)ws & 255))
-    return set_error(DG_EWORKSPACE, "dg_minhash_order: workspace needs %zu bytes", need);
-  hipStream_t s = stream;
   KeySort a;
   memset(&a, 0, sizeof(a));
-  Carve c(ws);
-  a.err = c.take<uint32_t>(64);
-  int32_t *minv = c.take<int32_t>(64);
   a.mask = membership;
   a.keep = B == 64 ? ~0ull : ((1ull << B) - 1ull);
   a.N = N;
   a.n = m;
-  carve_keysort(a, c);
   a.ids = entries;
-  a.minv = minv;
+  a.perms = perms;
+  a.k = k;
+  a.B = B;
   a.order = order;
   a.signature = signature;
-  int rc;
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(a.err), 1, 0, s))) return rc;
-  hipLaunchKernelGGL(k_minhash_min, dim3(1), dim3(64), 0, s, perms, k, B, minv, a.err);
-  DG_HIP(hipGetLastError());
-  int64_t totals[KEYS];
-  if ((rc = keysort_count<MINHASH>(a, totals, s))) return rc;
-  int64_t run = 0;  // keys ascending; 64 (in no sample) last
-  for (int key = 0; key < KEYS; ++key) {
-    a.first[key] = run;
-    run += totals[key];
-  }
-  if (a.nblk > 0)
-    hipLaunchKernelGGL(k_key_place<MINHASH>, dim3((unsigned)a.nblk), dim3(CF_THREADS), 0, s, a);
-  DG_HIP(hipGetLastError());
-  uint32_t bits = 0;
-  DG_TRY(read_to_host(&bits, a.err, sizeof(bits), s));
+  size_t need = 0;
+  const int rounds = fit_keysort(a, ws, ws_bytes, &need);
+  if (!ws || !rounds || ((uintptr_t)ws & 255))
+    return set_error(DG_EWORKSPACE, "dg_minhash_order: workspace needs %zu bytes", need);
+  int64_t totals[KEYS + 1];
+  DG_TRY(keysort_run<MINHASH>(a, rounds, totals, stream));
+  const uint32_t bits = (uint32_t)totals[KEYS];
   if (bits & ERR_ROW_RANGE)
     return set_error(DG_EINVAL, "dg_minhash_order: a hash value is outside [0, B)");
   if (bits) return set_error(DG_EINVAL, "invalid input data: %s", describe_device_error(bits));

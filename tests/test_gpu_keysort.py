@@ -1,0 +1,113 @@
+"""The counting sort behind the frequency cache and the MinHash order, at the edges of its tiles
+and in both of its workspace layouts, against torch sorts (tolerance 0)."""
+import ctypes
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def dg():
+    import paper_2405_05231_amd as m
+    return m
+
+
+def popcount(x):
+    n = torch.zeros_like(x, dtype=torch.int32)
+    for b in range(64):
+        n += ((x >> b) & 1).int()
+    return n
+
+
+def words(n, kind, g):
+    if kind == "none":
+        return torch.zeros(n, dtype=torch.int64, device=DEV)
+    if kind == "all":
+        return torch.full((n,), -1, dtype=torch.int64, device=DEV)
+    x = torch.randint(-2**63, 2**63 - 1, (n,), device=DEV, generator=g)
+    if kind == "sparse":
+        x &= torch.randint(-2**63, 2**63 - 1, (n,), device=DEV, generator=g)
+        x &= torch.randint(-2**63, 2**63 - 1, (n,), device=DEV, generator=g)
+        x[torch.rand(n, device=DEV, generator=g) < 0.9] = 0
+    return x
+
+
+def old_bytes(n, extra):
+    """The workspace the calls asked for before they kept the keys."""
+    def up(x):
+        return (x + 255) & ~255
+    blocks = (n + 4095) // 4096
+    return extra + up(4 * 65 * blocks) + up(8 * 65 * blocks) + up(8 * 65)
+
+
+# tile edges, and both sides of the tile length's steps
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 257, 4096, 4097, 100_003, 4_194_303,
+                               4_194_304 + 70, 33_554_432 + 70])
+@pytest.mark.parametrize("kind", ["sparse", "dense", "none", "all"])
+def test_frequency_cache_every_tile(dg, n, kind):
+    if n > 4_200_000 and kind not in ("sparse", "all"):
+        pytest.skip("the large sizes run two of the distributions")
+    g = torch.Generator(device=DEV).manual_seed(n)
+    mask = words(n, kind, g)
+    for B in (64, 5):
+        keep = -1 if B == 64 else (1 << B) - 1
+        count = popcount(mask & keep)
+        order = torch.sort(count, descending=True, stable=True).indices
+        accessed = int((count > 0).sum())
+        for cap in {0, 1, min(n, 7), n // 20, n}:
+            cached = min(cap, accessed)
+            nodes = torch.full((max(cap, 1),), -1, dtype=torch.int32, device=DEV)
+            nodes[:cached] = order[:cached].int()
+            slot = torch.full((n,), -1, dtype=torch.int32, device=DEV)
+            slot[order[:cached]] = torch.arange(cached, dtype=torch.int32, device=DEV)
+            got = dg.cache_by_frequency(mask, B, cap)
+            assert got[2] == cached
+            assert torch.equal(got[0], slot) and torch.equal(got[1], nodes[:cap])
+            # the smaller workspace is still taken
+            ws = torch.empty(old_bytes(n, 0), dtype=torch.uint8, device=DEV)
+            s2, n2 = torch.full_like(slot, -7), torch.full_like(nodes, -7)
+            out = ctypes.c_int64()
+            dg.check(dg._L.dg_cache_by_frequency(
+                mask.data_ptr(), n, B, cap, s2.data_ptr(), n2.data_ptr(), ctypes.byref(out),
+                ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream))
+            assert out.value == cached
+            assert torch.equal(s2, slot) and torch.equal(n2[:cap], nodes[:cap])
+
+
+@pytest.mark.parametrize("m", [0, 1, 64, 65, 255, 1025, 50_001, 4_194_304 + 70])
+@pytest.mark.parametrize("kind", ["sparse", "dense", "all"])
+def test_minhash_every_tile(dg, m, kind):
+    g = torch.Generator(device=DEV).manual_seed(m)
+    N = 300_007
+    mask = words(N, kind, g)
+    for B, k in ((64, 2), (7, 1)):
+        perms = torch.stack([torch.randperm(B, device=DEV, generator=g)
+                             for _ in range(k)]).int().contiguous()
+        entries = torch.randint(0, N, (m,), device=DEV, generator=g).int()
+        value = torch.full((m,), 64, dtype=torch.int32, device=DEV)
+        for b in range(B):
+            has = (mask[entries.long()] >> b) & 1 == 1
+            value[has] = value[has].clamp(max=int(perms[:, b].min()))
+        want = entries[torch.sort(value, stable=True).indices] if m else entries
+        sig = torch.where(value == 64, -1, value)
+        order, signature = dg.minhash_order(mask, B, entries, perms)
+        assert torch.equal(order, want) and torch.equal(signature, sig)
+        ws = torch.empty(old_bytes(m, 512), dtype=torch.uint8, device=DEV)
+        o2 = torch.full((max(m, 1),), -7, dtype=torch.int32, device=DEV)
+        dg.check(dg._L.dg_minhash_order(
+            mask.data_ptr(), N, B, entries.data_ptr() if m else None, m, perms.data_ptr(), k,
+            o2.data_ptr(), None, ws.data_ptr(), ws.numel(),
+            torch.cuda.current_stream().cuda_stream))
+        assert torch.equal(o2[:m], want)
+        bad = perms.clone()
+        bad[-1, -1] = B
+        with pytest.raises(dg.DGError, match="hash value"):
+            dg.minhash_order(mask, B, entries, bad)
+        if m:
+            wrong = entries.clone()
+            wrong[m // 2] = N
+            with pytest.raises(dg.DGError, match="node ID"):
+                dg.minhash_order(mask, B, wrong, perms)
