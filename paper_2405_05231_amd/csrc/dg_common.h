@@ -197,14 +197,44 @@ struct SideStream {
 };
 int side_stream(SideStream **out);
 
-// ---------------------------------------------------------------- fill / scan
+// ---------------------------------------------------------------- fill, block scan
 int fill_u64(uint64_t *p, size_t n, uint64_t value, hipStream_t s);
 
-// Exclusive scan of n int64 values: out[0..n] (out[n] = total).  tile_sums needs
-// scan_tile_count(n) entries.
-size_t scan_tile_count(int64_t n);
-int scan_exclusive(const int64_t *in, int64_t *out, int64_t n, int64_t *tile_sums,
-                   hipStream_t s);
+// Zeroes several ranges (8-byte words) with one launch.
+struct ZeroRanges {
+  static constexpr int MAX = 3;
+  uint64_t *p[MAX] = {};
+  size_t n[MAX] = {};
+  void add(void *ptr, size_t words) {
+    for (int q = 0; q < MAX; ++q)
+      if (n[q] == 0) {
+        p[q] = static_cast<uint64_t *>(ptr);
+        n[q] = words;
+        return;
+      }
+  }
+};
+int zero_ranges(const ZeroRanges &z, hipStream_t s);
+
+// Block-wide exclusive scan of one value per thread; *total gets the block sum.
+template <int NT>
+__device__ __forceinline__ int64_t block_excl_scan(int64_t x, int64_t *total) {
+  __shared__ int64_t s_w[NT / 64];
+  const int lane = lane_id(), w = threadIdx.x >> 6;
+  int64_t incl = wave_incl_sum(x);
+  if (lane == 63) s_w[w] = incl;
+  __syncthreads();
+  int64_t before = 0, sum = 0;
+#pragma unroll
+  for (int i = 0; i < NT / 64; ++i) {
+    int64_t v = s_w[i];
+    if (i < w) before += v;
+    sum += v;
+  }
+  __syncthreads();
+  *total = sum;
+  return before + incl - x;
+}
 
 // ---------------------------------------------------------------- timing
 // Events are taken from a pool per host thread and device, created on first

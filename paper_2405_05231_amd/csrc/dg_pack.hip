@@ -49,18 +49,6 @@ __global__ __launch_bounds__(THREADS) void k_pack_mark(Lists L, const int32_t *n
   atomicOr((unsigned long long *)&mask[u], 1ull << b);
 }
 
-// packed_ptr from the per-batch totals of the count pass.
-__global__ void k_packed_ptr(const int64_t *totals, int B, int64_t *packed_ptr) {
-  if (threadIdx.x == 0) {
-    int64_t run = 0;
-    packed_ptr[0] = 0;
-    for (int b = 0; b < B; ++b) {
-      run += totals[b];
-      packed_ptr[b + 1] = run;
-    }
-  }
-}
-
 // loc_b[j] = -(slot+1) for a cached node, else its rank in P_b.  A non-cached
 // node's pairs start at nodeoff[u], one per batch that holds it, in batch
 // order, each naming its packed row; the entry takes the first pair whose row
@@ -117,7 +105,7 @@ __global__ __launch_bounds__(THREADS) void k_build_loc(Lists L, const int32_t *n
 
 }  // namespace
 
-void carve_pack(PackWs &w, Carve &c, int64_t N, int B, int64_t total_nodes) {
+void carve_pack(PackWs &w, Carve &c, int64_t N, int B, int64_t total_nodes, int rounds) {
   int64_t ucap = total_nodes < N ? total_nodes : N;
   w.err = c.take<uint32_t>(32);
   w.mask = c.take<uint64_t>((size_t)N);
@@ -128,7 +116,7 @@ void carve_pack(PackWs &w, Carve &c, int64_t N, int B, int64_t total_nodes) {
   w.ms = MaskScan{};
   w.ms.N = N;
   w.ms.B = B;
-  mask_scan_carve(w.ms, c);
+  mask_scan_carve(w.ms, c, rounds);
 }
 
 namespace {
@@ -152,7 +140,7 @@ size_t pack_ws_bytes(int64_t num_nodes, int32_t B, int64_t total_nodes) {
   if (num_nodes < 1 || B < 1 || B > DG_MAX_BATCHES || total_nodes < 0) return 0;
   Carve c(nullptr);
   PackWs w;
-  carve_pack(w, c, num_nodes, B, total_nodes);
+  carve_pack(w, c, num_nodes, B, total_nodes, mc_rounds(num_nodes));
   return c.used;
 }
 
@@ -230,7 +218,15 @@ int pack_impl(const void *feats, int64_t N, int64_t row_bytes, const int32_t *ca
   const int64_t total = L.start[B];
   if (packed_cap > 0 && !packed_ids)
     return set_error(DG_EINVAL, "dg_pack_group: null packed_ids");
-  const size_t need_ws = pack_ws_bytes(N, B, total);
+  // Short tiles need a larger count matrix: where it does not fit, the longest.
+  PackWs w;
+  size_t need_ws = 0;
+  for (int rounds : {mc_rounds(N), MC_ROUNDS_MAX}) {
+    Carve c(ws);
+    carve_pack(w, c, N, B, total, rounds);
+    need_ws = c.used;
+    if (need_ws <= ws_bytes) break;
+  }
   if (no_alloc && need_ws > ws_bytes)
     return set_error(DG_EWORKSPACE,
                      "dg_pack_group_noalloc: these sizes need %zu bytes of scratch, above its "
@@ -241,9 +237,6 @@ int pack_impl(const void *feats, int64_t N, int64_t row_bytes, const int32_t *ca
                      need_ws);
 
   hipStream_t s = stream;
-  PackWs w;
-  Carve c(ws);
-  carve_pack(w, c, N, B, total);
   w.ms.err = w.err;
   memset(sizes, 0, sizeof(*sizes));
   sizes->max_batch_nodes = sizes->max_batch_edges = sizes->total_edges = -1;
@@ -254,11 +247,13 @@ int pack_impl(const void *feats, int64_t N, int64_t row_bytes, const int32_t *ca
 
   int rc;
   const int e0 = tm.mark();
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(w.err), 16, 0, s))) return rc;
+  ZeroRanges z;
+  z.add(w.err, 16);
+  if (!membership) z.add(w.mask, (size_t)N);
+  if ((rc = zero_ranges(z, s))) return rc;
   if (membership) {
     w.mask = membership;  // written only with DG_PACK_CLEAR_MEMBERSHIP
   } else {
-    if ((rc = fill_u64(w.mask, (size_t)N, 0, s))) return rc;
     if (total > 0) {
       hipLaunchKernelGGL(k_pack_mark, dim3(blocks_for(total)), dim3(THREADS), 0, s, L, nodes, N,
                          w.mask, w.err);
@@ -298,7 +293,8 @@ int pack_impl(const void *feats, int64_t N, int64_t row_bytes, const int32_t *ca
     return set_error(DG_ECAPACITY,
                      "dg_pack_group: need packed_cap >= %lld and unique_cap >= %lld",
                      (long long)rows, (long long)sizes->unique_nodes);
-  hipLaunchKernelGGL(k_packed_ptr, dim3(1), dim3(64), 0, s, w.ms.totals, B, packed_ptr);
+  w.ms.ptr_out = packed_ptr;
+  w.ms.ptr_end = rows;
   for (int b = 0; b < B; ++b) w.ms.seg_base[b] = packed_ptr_host[b];
   w.ms.seg_out = packed_ids;
   w.ms.uniq_out = group_unique;

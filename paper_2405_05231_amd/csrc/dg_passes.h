@@ -9,24 +9,28 @@ namespace dg {
 
 // ---------------------------------------------------------------- mask compaction
 // A node-major membership mask: bit b of mask[u] says that node u belongs to
-// mini-batch b.  A block of MC_WAVES waves owns MC_BLOCK_NODES consecutive
-// nodes; wave w owns the w-th run of MC_TILE of them, and round r of a wave
-// covers nodes tile0 + r*64 + lane, so (wave, round, lane) order is node order.
+// mini-batch b.  A wave owns a tile of 64*R consecutive nodes, R = 16, 4 or 1
+// rounds of 64 (mc_rounds); a block of MC_WAVES waves owns MC_WAVES consecutive
+// tiles, and round r of a wave covers nodes tile0 + r*64 + lane, so (wave, round,
+// lane) order is node order.
 constexpr int MC_WAVES = 4;
 constexpr int MC_THREADS = 64 * MC_WAVES;
-constexpr int MC_ROUNDS = 16;
-constexpr int MC_TILE = 64 * MC_ROUNDS;
-constexpr int MC_BLOCK_NODES = MC_TILE * MC_WAVES;
-constexpr int MC_CHUNK = 64;  // blocks per chunk of the row scan
+constexpr int MC_ROUNDS_MAX = 16;
+constexpr int MC_PAD = 64 * MC_ROUNDS_MAX * MC_WAVES;  // per-node arrays are padded to this
 // Touched marks: one byte per 2^MC_TOUCH_SHIFT consecutive nodes (one 64-byte
 // line of the mask).
 constexpr int MC_TOUCH_SHIFT = 3;
 
-__host__ __device__ inline int64_t mc_blocks(int64_t N) { return (N + MC_BLOCK_NODES - 1) / MC_BLOCK_NODES; }
-__host__ __device__ inline int64_t mc_chunks(int64_t nblk) { return (nblk + MC_CHUNK - 1) / MC_CHUNK; }
-__host__ __device__ inline int64_t mc_touch_bytes(int64_t N) {
-  return mc_blocks(N) * (MC_BLOCK_NODES >> MC_TOUCH_SHIFT);
+__host__ __device__ inline int64_t mc_pad_nodes(int64_t N) { return (N + MC_PAD - 1) / MC_PAD * MC_PAD; }
+__host__ __device__ inline int64_t mc_blocks(int64_t N, int rounds) {
+  const int64_t n = (int64_t)64 * rounds * MC_WAVES;
+  return (N + n - 1) / n;
 }
+__host__ __device__ inline int64_t mc_touch_bytes(int64_t N) { return mc_pad_nodes(N) >> MC_TOUCH_SHIFT; }
+// Rounds per tile.  A tile's rounds are one serial chain in the write passes, so
+// short tiles until about 1000 blocks (four per CU) are there, then longer ones,
+// which keep the count matrix and each block's own cost small.
+inline int mc_rounds(int64_t N) { return N >= 4000000 ? 16 : N >= 500000 ? 4 : 1; }
 
 // Count-matrix rows: [0,B) per batch (non-cached members), then:
 __host__ __device__ inline int row_all(int B) { return B; }        // nodes with any bit set (U)
@@ -40,14 +44,14 @@ struct MaskScan {
   const int32_t *cache_slot;  // nullable: no node is cached
   int64_t N;
   int B;
-  int64_t nblk;        // blocks of MC_BLOCK_NODES nodes
-  uint32_t *cnt;       // [nblk][rows] per-block counts
+  int rounds;          // per tile
+  int64_t nblk;        // mc_blocks(N, rounds)
+  uint32_t *cnt;       // [rows][nblk] per-block counts
   uint32_t *wpre;      // [nblk][MC_WAVES][rows] each wave's exclusive prefix in its block
   uint32_t *wcnt;      // [nblk][MC_WAVES] non-empty words of each wave's tile
-  uint64_t *cw_mask;   // [nblk][MC_WAVES][MC_TILE] those words (count pass -> write pass)
+  uint64_t *cw_mask;   // [tile][64*rounds] those words (count pass -> write pass)
   uint16_t *cw_off;    // ... their node offsets in the tile; bit 15 = cached
-  int64_t *base;       // [nblk][rows] exclusive scans down each row
-  int64_t *chunk_sum;  // [chunks][rows]
+  int64_t *base;       // [rows][nblk] exclusive scans along each row
   int64_t *totals;     // [rows]
   uint32_t *err;
   int64_t *err_stage;  // nullable: receives *err after the count pass (for the read-back)
@@ -79,6 +83,10 @@ struct MaskScan {
   const uint8_t *touched;            // nullable: a byte per 2^MC_TOUCH_SHIFT nodes
                                      // (mc_touch_bytes(N) in all); nodes whose byte
                                      // is 0 hold no bit to list (not read)
+  uint8_t *touched_clear;            // nullable: = touched, whose marks are zeroed once read
+  int64_t *ptr_out;                  // packing, nullable: packed_ptr (B+1 entries), written
+                                     // from seg_base and ...
+  int64_t ptr_end;                   // ... its last entry
   // sampling only (both or neither): for each listed pair, the address-table
   // entry at the same index as its seg_out slot: -(loc_slot[u]+1) for a cached
   // node, DG_LOC_PENDING otherwise
@@ -91,8 +99,7 @@ struct MaskScan {
 };
 
 
-size_t mask_scan_ws_bytes(int64_t N, int B);
-void mask_scan_carve(MaskScan &m, Carve &c);
+void mask_scan_carve(MaskScan &m, Carve &c, int rounds);
 // Count pass + per-row scans (asynchronous); m.totals[row] receives each row's
 // total (B+4 values) on the device.
 int mask_scan_count(MaskScan &m, hipStream_t s);
@@ -100,8 +107,6 @@ int mask_scan_count(MaskScan &m, hipStream_t s);
 int mask_scan_write(const MaskScan &m, hipStream_t s);
 // Member lines of the whole mask (mc_touch_bytes(N) bytes), by a pass of its own.
 int member_lines_pass(const uint64_t *mask, int64_t N, int B, uint8_t *out, hipStream_t s);
-// The row scans of a count matrix filled by a count pass (part of mask_scan_count).
-int mask_scan_rows(MaskScan &m, hipStream_t s);
 
 // ---------------------------------------------------------------- fused compaction
 // The last sampling hop's count and write passes doing batched packing's pass
@@ -128,6 +133,7 @@ struct FuseScan {
   const int32_t *cache_slot;
   int64_t N;
   int B;
+  int rounds;
   int64_t nblk;
   bool clear_prev;
   uint32_t *err;
@@ -148,7 +154,8 @@ struct FuseScan {
   int32_t *loc_out;    // [B*node_cap] address tables (cached entries written here)
   int32_t *local_out;  // nullable: [N][B] local indices of the hop's pairs
   // write pass, packing
-  const int64_t *packed_ptr;  // device [B+1], from the p view's totals
+  const int64_t *totals_p;    // device [rows]: the p view's totals
+  int64_t *packed_ptr;        // device [B+1] out, from those totals
   int64_t packed_cap;         // entries of pinfo
   uint64_t *pinfo;            // per packed row: node ID (low half) and the pair's
                               // list slot if new at this hop, else -1 (high half)
@@ -163,10 +170,8 @@ struct FuseScan {
 };
 // Count pass + the row scans of both views (asynchronous).
 int fuse_scan_count(const FuseScan &f, MaskScan &vs, MaskScan &vp, hipStream_t s);
-// Write pass (after the count pass): first packed_ptr (= f.packed_ptr, B+1
-// entries) from the p view's per-batch totals, then the pass itself.
-int fuse_scan_write(const FuseScan &f, const int64_t *totals_p, int64_t *packed_ptr,
-                    hipStream_t s);
+// Write pass (after the count pass).
+int fuse_scan_write(const FuseScan &f, hipStream_t s);
 
 // ---------------------------------------------------------------- packing state
 // Workspace of batched packing (also carved by dg_sample_pack_group).
@@ -179,7 +184,7 @@ struct PackWs {
   int64_t *pairdest;
   MaskScan ms;
 };
-void carve_pack(PackWs &w, Carve &c, int64_t N, int B, int64_t total_nodes);
+void carve_pack(PackWs &w, Carve &c, int64_t N, int B, int64_t total_nodes, int rounds);
 size_t pack_ws_bytes(int64_t num_nodes, int32_t B, int64_t total_nodes);
 // dg_pack_group's body (no_alloc: dg_pack_group_noalloc's rules).
 int pack_impl(const void *feats, int64_t N, int64_t row_bytes, const int32_t *cache_slot,

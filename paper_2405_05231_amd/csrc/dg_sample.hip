@@ -36,12 +36,15 @@ __host__ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 }
 constexpr uint64_t GAMMA = 0x9E3779B97F4A7C15ull;
 
-// Per-hop description of the frontier, passed by value.
+// Per-hop description of the frontier, passed by value.  It is cut into tiles of
+// F_TILE entries of one batch each, so that a block's batch is the same for all
+// its threads.
+constexpr int F_TILE = THREADS;
 struct Hop {
   int B;
   int32_t f;        // fan-out of this hop (< 0: all)
   int32_t k;        // hop number, 1-based (RNG key)
-  int64_t ftot;     // frontier entries over all batches
+  int32_t tstart[DG_MAX_BATCHES + 1];  // prefix of the batches' tiles
   int64_t fstart[DG_MAX_BATCHES + 1];  // prefix of frontier sizes
   int64_t fpos[DG_MAX_BATCHES];        // local position of b's first frontier node
   int64_t ebase[DG_MAX_BATCHES];       // edges of b before this hop
@@ -49,6 +52,15 @@ struct Hop {
   uint8_t *touched;                    // nullable: a byte per 2^MC_TOUCH_SHIFT nodes, set
                                        // for every node that gains a membership bit
 };
+
+__device__ __forceinline__ int tile_batch(const Hop &h, int32_t t) {
+  int lo = 0, hi = h.B;  // invariant tstart[lo] <= t < tstart[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (h.tstart[mid] <= t) lo = mid; else hi = mid;
+  }
+  return lo;
+}
 
 // Flattened (batch, position) ranges, for passes over all edge lists, with
 // each batch's node count.
@@ -58,57 +70,80 @@ struct Lists {
   int64_t n[DG_MAX_BATCHES];
 };
 
-// Seeds -> node lists, membership bits and local indices; with loc, also the
-// seeds' address-table entries (final for cached seeds, pending otherwise).
-__global__ __launch_bounds__(THREADS) void k_seed_init(const int32_t *seeds, int B, int S,
-                                                       int64_t N, int64_t node_cap,
-                                                       int32_t *nodes, uint64_t *visited,
-                                                       uint64_t *prev, uint8_t *plines,
-                                                       int32_t *local, const int32_t *cache_slot,
-                                                       int32_t *loc, uint32_t *err) {
-  int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x;
-  if (i >= (int64_t)B * S) return;
-  int b = (int)(i / S);
-  int64_t j = i - (int64_t)b * S;
-  int32_t v = seeds[i];
-  nodes[(int64_t)b * node_cap + j] = v;
-  if (v < 0 || (int64_t)v >= N) {
-    atomicOr(err, ERR_NODE_RANGE);
-    return;
-  }
-  if (loc) {
-    const int32_t sl = cache_slot[v];
-    if (sl < -1) atomicOr(err, ERR_CACHE_SLOT);
-    loc[(int64_t)b * node_cap + j] = sl >= 0 ? -(sl + 1) : (int32_t)DG_LOC_PENDING;
-  }
-  unsigned long long bit = 1ull << b;
-  unsigned long long old = atomicOr((unsigned long long *)&visited[v], bit);
-  if (old & bit) atomicOr(err, ERR_DUP_NODE);
-  atomicOr((unsigned long long *)&prev[v], bit);  // seeds are not new at hop 1
-  plines[v >> MC_TOUCH_SHIFT] = 1;
-  if (local) local[(int64_t)v * B + b] = (int32_t)j;
-}
+// What the seeds need before the first hop.
+struct SeedInit {
+  const int32_t *seeds;
+  int S;
+  int32_t *nodes;
+  uint64_t *visited, *prev;
+  uint8_t *plines;
+  int32_t *local;  // nullable: the direct table
+  const int32_t *cache_slot;
+  int32_t *loc;  // nullable
+};
 
-__global__ __launch_bounds__(THREADS) void k_frontier_degree(
-    Hop h, const int32_t *nodes, int64_t node_cap, const int64_t *off, int64_t N, int64_t E,
-    int64_t *f_off, int64_t *f_deg, int64_t *f_cnt, uint32_t *err) {
-  int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x;
-  if (i >= h.ftot) return;
-  int b = find_batch_wave(h.fstart, h.B, i);
-  int32_t v = nodes[(int64_t)b * node_cap + h.fpos[b] + (i - h.fstart[b])];
+// Frontier pass: each entry's CSR row and degree, its edge slots' exclusive scan
+// within its tile, and each tile's sum.  The draw kernel adds the sums of its
+// batch's earlier tiles itself, so the scan costs no launch of its own (three
+// scan kernels and one for the batch bounds went: 16 to 20 us a hop on short
+// frontiers, 39 us at 3.2M entries).
+// SEEDS: the first hop's frontier, straight from the seeds; each also enters its
+// node list, the membership words and the local indices, with loc its address-
+// table entry (final for a cached seed, pending otherwise).  degree = false: that
+// part alone.
+template <bool SEEDS>
+__global__ __launch_bounds__(THREADS) void k_frontier(Hop h, SeedInit sd, bool degree,
+                                                      const int32_t *nodes, int64_t node_cap,
+                                                      const int64_t *off, int64_t N, int64_t E,
+                                                      int64_t *f_off, int64_t *f_deg,
+                                                      int64_t *f_eoff, int64_t *tile_sum,
+                                                      uint32_t *err) {
+  const int32_t t = blockIdx.x;
+  const int b = tile_batch(h, t);
+  const int64_t j = (int64_t)(t - h.tstart[b]) * F_TILE + threadIdx.x;
+  const int64_t i = h.fstart[b] + j;
+  const bool valid = i < h.fstart[b + 1];
+  int32_t v = -1;
+  if (valid) v = SEEDS ? sd.seeds[(int64_t)b * sd.S + j] : nodes[(int64_t)b * node_cap + h.fpos[b] + j];
+  const bool in = v >= 0 && (int64_t)v < N;
   int64_t o0 = 0, d = 0;
-  if (v >= 0 && (int64_t)v < N) {
+  if (in && degree) {
     o0 = off[v];
-    int64_t o1 = off[v + 1];
+    const int64_t o1 = off[v + 1];
     if (o0 < 0 || o1 < o0 || o1 > E) {
       atomicOr(err, ERR_CSR);
     } else {
       d = o1 - o0;
     }
   }
-  f_off[i] = o0;
-  f_deg[i] = d;
-  f_cnt[i] = (h.f < 0 || d <= (int64_t)h.f) ? d : (int64_t)h.f;
+  if (SEEDS && valid) {
+    sd.nodes[(int64_t)b * node_cap + j] = v;
+    if (!in) {
+      atomicOr(err, ERR_NODE_RANGE);
+    } else {
+      if (sd.loc) {
+        const int32_t sl = sd.cache_slot[v];
+        if (sl < -1) atomicOr(err, ERR_CACHE_SLOT);
+        sd.loc[(int64_t)b * node_cap + j] = sl >= 0 ? -(sl + 1) : (int32_t)DG_LOC_PENDING;
+      }
+      const unsigned long long bit = 1ull << b;
+      const unsigned long long old = atomicOr((unsigned long long *)&sd.visited[v], bit);
+      if (old & bit) atomicOr(err, ERR_DUP_NODE);
+      atomicOr((unsigned long long *)&sd.prev[v], bit);  // seeds are not new at hop 1
+      sd.plines[v >> MC_TOUCH_SHIFT] = 1;
+      if (sd.local) sd.local[(int64_t)v * h.B + b] = (int32_t)j;
+    }
+  }
+  if (!degree) return;  // whole grid
+  const int64_t cnt = (h.f < 0 || d <= (int64_t)h.f) ? d : (int64_t)h.f;
+  int64_t total;
+  const int64_t eoff = block_excl_scan<THREADS>(cnt, &total);
+  if (valid) {
+    f_off[i] = o0;
+    f_deg[i] = d;
+    f_eoff[i] = eoff;
+  }
+  if (threadIdx.x == 0) tile_sum[t] = total;
 }
 
 // Emits up to EMIT sampled edges whose neighbour IDs are already loaded: the
@@ -150,23 +185,48 @@ __device__ __forceinline__ void emit_chunk(const int32_t (&u)[EMIT], const int64
 // bound the waves per SIMD and so the loads in flight; each drawn position's rank among the f
 // positions gives its slot, so no sort is needed, and lane `sub` takes the
 // draws s with s mod LPN = sub.  Neighbour loads and membership atomics are
-// issued EMIT at a time so their latencies overlap.  estart[b] = f_eoff at
-// batch b's first frontier entry (written on the device by k_batch_bounds).  A
+// issued EMIT at a time so their latencies overlap.  A block takes F_TILE/LPN
+// consecutive entries of one tile.  The block of a batch's last tile leaves the
+// batch's edges of this hop in bounds[b].  A
 // node whose edges would pass edge_cap writes nothing; the host sees the
 // overflow in the edge counts and reports it.
 template <int LPN, int FM>
 __global__ __launch_bounds__(THREADS) void k_hop_sample(
     Hop h, const int32_t *nodes, int64_t node_cap, const int32_t *idx, const int64_t *f_off,
-    const int64_t *f_deg, const int64_t *f_eoff, const int64_t *estart, int64_t edge_cap,
-    int32_t *edge_src, int32_t *edge_dst, uint64_t *visited, int64_t N, uint32_t *err) {
-  const int64_t t = (int64_t)blockIdx.x * THREADS + threadIdx.x;
-  const int64_t i = t / LPN;
-  const int sub = (int)(t % LPN);
-  if (i >= h.ftot) return;
-  int b = find_batch_wave(h.fstart, h.B, i);
-  int64_t p = h.fpos[b] + (i - h.fstart[b]);
-  int64_t o0 = f_off[i], d = f_deg[i];
-  const int64_t first = h.ebase[b] + (f_eoff[i] - estart[b]);  // local index of the 1st edge
+    const int64_t *f_deg, const int64_t *f_eoff, const int64_t *tile_sum, int64_t *bounds,
+    int64_t edge_cap, int32_t *edge_src, int32_t *edge_dst, uint64_t *visited, int64_t N,
+    uint32_t *err) {
+  const int32_t t = (int32_t)(blockIdx.x / LPN);
+  const int part = (int)(blockIdx.x % LPN);
+  const int b = tile_batch(h, t);
+  const int32_t t0 = h.tstart[b];
+  const int64_t j =
+      (int64_t)(t - t0) * F_TILE + part * (F_TILE / LPN) + (int)threadIdx.x / LPN;
+  const int64_t i = h.fstart[b] + j;
+  const int sub = (int)threadIdx.x % LPN;
+  const bool valid = i < h.fstart[b + 1];
+  int64_t o0 = 0, d = 0, eoff = 0;
+  if (valid) {
+    o0 = f_off[i];
+    d = f_deg[i];
+    eoff = f_eoff[i];
+  }
+  int64_t before = 0;  // edges of the batch's earlier tiles
+  if (t > t0) {        // uniform
+    int64_t x = 0;
+    for (int32_t q = t0 + (int32_t)threadIdx.x; q < t; q += THREADS) x += tile_sum[q];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    __shared__ int64_t s_x[THREADS / 64];
+    if ((threadIdx.x & 63) == 0) s_x[threadIdx.x >> 6] = x;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < THREADS / 64; ++q) before += s_x[q];
+  }
+  if (threadIdx.x == 0 && part == 0 && t + 1 == h.tstart[b + 1]) bounds[b] = before + tile_sum[t];
+  if (!valid) return;
+  const int64_t p = h.fpos[b] + j;
+  const int64_t first = h.ebase[b] + before + eoff;  // local index of the 1st edge
   const int64_t cnt = (h.f < 0 || d <= (int64_t)h.f) ? d : (int64_t)h.f;
   if (first + cnt > edge_cap) return;
   int64_t base = (int64_t)b * edge_cap + first;
@@ -462,18 +522,13 @@ __global__ __launch_bounds__(RL_THREADS) void k_relabel_last(LastHop h, const in
   }
 }
 
-// Host staging block (int64 entries): edge bounds, compaction totals, error word.
-constexpr int ST_BOUNDS = 0;                              // [B+1]
+// Host staging block (int64 entries): the hop's edges per batch, compaction totals,
+// error word.
+constexpr int ST_BOUNDS = 0;                              // [B]
 constexpr int ST_TOTALS = ST_BOUNDS + DG_MAX_BATCHES + 1; // [B+4]
 constexpr int ST_ERR = ST_TOTALS + DG_MAX_BATCHES + 4;
 constexpr int ST_PTOTALS = ST_ERR + 1;                      // [B+4] packing's, fused pass
 constexpr int ST_SIZE = ST_PTOTALS + DG_MAX_BATCHES + 4;
-
-// eoff at each batch's first frontier entry (and at the end).
-__global__ void k_batch_bounds(Hop h, const int64_t *f_eoff, int64_t *out) {
-  int b = threadIdx.x;
-  if (b <= h.B) out[b] = f_eoff[h.fstart[b]];
-}
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + THREADS - 1) / THREADS); }
 
@@ -484,38 +539,46 @@ struct SampleWs {
   uint32_t *err;
   uint64_t *visited, *prev;
   uint8_t *plines;  // lines of prev that hold a bit (a byte per 8 nodes)
-  int64_t *f_off, *f_deg, *f_cnt, *f_eoff, *tiles;
+  uint8_t *touched;  // touched marks (a byte per 2^MC_TOUCH_SHIFT nodes)
+  size_t state_words;  // 8-byte words from prev to the end of touched
+  int64_t *f_off, *f_deg, *f_eoff, *tiles;
   LocalTable table;  // hash relabelling
   int32_t *local;    // direct relabelling: [N][B]
   int32_t *segbuf;   // direct relabelling: last-hop segments, [B][rl_segcap(node_cap)]
   int32_t *sparse;   // ... and their sparse indices, [B][RL_SPARSE_MAX]
-  uint8_t *touched;  // touched marks (a byte per 2^MC_TOUCH_SHIFT nodes)
   int64_t *small;    // staging for a few counts
   MaskScan ms;
 };
 
-void carve_sample(SampleWs &w, Carve &c, int64_t N, int B, int64_t node_cap, bool direct) {
+// The state that DG_SAMPLE_EXIT_CLEAR leaves clear (err, prev, plines, touched; with
+// visited in the caller's membership words) comes first, at places that depend on N
+// alone.
+void carve_sample(SampleWs &w, Carve &c, int64_t N, int B, int64_t node_cap, bool direct,
+                  int rounds) {
   int64_t fmax = (int64_t)B * node_cap;  // frontier entries never exceed the node lists
   w.err = c.take<uint32_t>(64);
   w.visited = c.take<uint64_t>((size_t)N);
+  const size_t state = c.used;
   w.prev = c.take<uint64_t>((size_t)N);
   w.plines = c.take<uint8_t>((size_t)mc_touch_bytes(N));
+  w.touched = c.take<uint8_t>((size_t)mc_touch_bytes(N));
+  w.state_words = (c.used - state) / 8;
   w.f_off = c.take<int64_t>((size_t)fmax);
   w.f_deg = c.take<int64_t>((size_t)fmax);
-  w.f_cnt = c.take<int64_t>((size_t)fmax);
-  w.f_eoff = c.take<int64_t>((size_t)fmax + 1);
-  w.tiles = c.take<int64_t>(scan_tile_count(fmax));
+  w.f_eoff = c.take<int64_t>((size_t)fmax);
+  // tiles of one batch each, none of them empty
+  const int64_t tiles = fmax / F_TILE + B;
+  w.tiles = c.take<int64_t>((size_t)(tiles < fmax ? tiles : fmax));
   w.table.bits = direct ? 0 : lt_bits_for(fmax);
   w.table.slots = direct ? nullptr : c.take<uint64_t>((size_t)1 << w.table.bits);
   w.local = direct ? c.take<int32_t>((size_t)N * (size_t)B) : nullptr;
   w.segbuf = direct ? c.take<int32_t>((size_t)B * (size_t)rl_segcap(node_cap)) : nullptr;
   w.sparse = direct ? c.take<int32_t>((size_t)B * RL_SPARSE_MAX) : nullptr;
-  w.touched = c.take<uint8_t>((size_t)mc_touch_bytes(N));
   w.small = c.take<int64_t>(ST_SIZE);
   w.ms = MaskScan{};
   w.ms.N = N;
   w.ms.B = B;
-  mask_scan_carve(w.ms, c);
+  mask_scan_carve(w.ms, c, rounds);
 }
 
 int check_err(uint32_t *err_dev, hipStream_t s) {
@@ -568,7 +631,8 @@ extern "C" size_t dg_sample_workspace_bytes(int64_t num_nodes, int32_t B, int64_
     return 0;
   Carve c(nullptr);
   SampleWs w;
-  carve_sample(w, c, num_nodes, B, node_cap, (flags & DG_SAMPLE_DIRECT) != 0);
+  carve_sample(w, c, num_nodes, B, node_cap, (flags & DG_SAMPLE_DIRECT) != 0,
+               mc_rounds(num_nodes));
   return c.used;
 }
 
@@ -604,14 +668,14 @@ struct PackInto {
   int32_t *local = nullptr;           // the direct table (DG_SAMPLE_DIRECT)
 };
 
-void carve_sample_pack(PackInto &pk, Carve &c, int64_t N, int B, int64_t node_cap) {
+void carve_sample_pack(PackInto &pk, Carve &c, int64_t N, int B, int64_t node_cap, int rounds) {
   const int64_t total = (int64_t)B * node_cap;
   pk.pinfo = c.take<uint64_t>((size_t)total);
   pk.pinfo_cap = total;
-  pk.cw_slot = c.take<int32_t>((size_t)mc_blocks(N) * MC_BLOCK_NODES);
+  pk.cw_slot = c.take<int32_t>((size_t)mc_pad_nodes(N));
   pk.lines = c.take<uint8_t>((size_t)mc_touch_bytes(N));
   pk.pw_offset = c.used;  // packing's own workspace last: the unfused path hands it on whole
-  carve_pack(pk.pw, c, N, B, total);
+  carve_pack(pk.pw, c, N, B, total, rounds);
   pk.unc_cap = (total < N ? total : N) + 1;
   pk.pair_cap = total + 1;
 }
@@ -645,16 +709,22 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
                      S, K, (long long)node_cap);
   if (node_cap > LT_MAX_VALUE)
     return set_error(DG_EINVAL, "dg_sample_group: node_cap above 2^27 - 1 is not supported");
-  const size_t need_ws = dg_sample_workspace_bytes(g->num_nodes, B, node_cap, edge_cap, flags);
+  // Short tiles need a larger count matrix: where it does not fit (or packing's
+  // workspace has longer ones), the longest.
+  SampleWs w;
+  size_t need_ws = 0;
+  for (int rounds : {pk ? pk->pw.ms.rounds : mc_rounds(g->num_nodes), MC_ROUNDS_MAX}) {
+    Carve c(ws);
+    carve_sample(w, c, g->num_nodes, B, node_cap, direct, rounds);
+    need_ws = c.used;
+    if (need_ws <= ws_bytes) break;
+  }
   if (!ws || ws_bytes < need_ws || ((uintptr_t)ws & 255))
     return set_error(DG_EWORKSPACE, "dg_sample_group: workspace needs %zu bytes, 256-aligned",
                      need_ws);
 
   const int64_t N = g->num_nodes, E = g->num_edges;
   hipStream_t s = stream;
-  SampleWs w;
-  Carve c(ws);
-  carve_sample(w, c, N, B, node_cap, direct);
   w.ms.err = w.err;
 
   memset(sizes, 0, sizeof(*sizes));
@@ -664,26 +734,20 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
   mk.start = tm.mark();
 
   int rc;
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(w.err), 32, 0, s))) return rc;
   if (membership) w.visited = membership;
-  // prev (workspace) and visited must start all-zero: cleared here unless the
-  // caller asserts that they already are (see DG_SAMPLE_ENTRY_CLEAR)
+  // The error word, visited and prev with its lines, and the touched marks must
+  // start all-zero: cleared here unless the caller asserts that they already are
+  // (see DG_SAMPLE_ENTRY_CLEAR).
   if (!entry_clear) {
-    if ((rc = fill_u64(w.visited, (size_t)N, 0, s))) return rc;
-    if ((rc = fill_u64(w.prev, (size_t)N, 0, s))) return rc;
-    if ((rc = fill_u64(reinterpret_cast<uint64_t *>(w.plines), (size_t)mc_touch_bytes(N) / 8, 0,
-                       s)))
-      return rc;
+    ZeroRanges z;
+    z.add(w.err, 32);
+    z.add(w.visited, (size_t)N);
+    z.add(w.prev, w.state_words);
+    if ((rc = zero_ranges(z, s))) return rc;
   }
   bool prev_cleared = false;  // the last hop's count pass zeroed prev
   bool lines_done = false;    // the last hop's count pass wrote member_lines
   bool rl_search = false;     // the last hop's edges are relabelled by search
-  hipLaunchKernelGGL(k_seed_init, dim3(blocks_for((int64_t)B * S)), dim3(THREADS), 0, s, seeds,
-                     B, S, N, node_cap, nodes, w.visited, w.prev, w.plines, w.local, cache_slot,
-                     loc,
-                     w.err);
-  DG_HIP(hipGetLastError());  // bad seeds are reported at the first hop's round trip
-
   int64_t n_b[DG_MAX_BATCHES], e_b[DG_MAX_BATCHES];
   for (int b = 0; b < B; ++b) {
     n_b[b] = S;
@@ -702,20 +766,40 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
     fbeg[b] = 0;
     fend[b] = S;
   }
+  // Frontier pass of the hop that h describes; the first one also enters the
+  // seeds (bad seeds are reported at the first hop's round trip).
+  auto frontier = [&](bool seeding, bool degree) {
+    const SeedInit sd{seeds, S, nodes, w.visited, w.prev, w.plines, w.local, cache_slot, loc};
+    const dim3 grid((unsigned)h.tstart[B]);
+    if (seeding)
+      hipLaunchKernelGGL(k_frontier<true>, grid, dim3(THREADS), 0, s, h, sd, degree, nodes,
+                         node_cap, g->offsets, N, E, w.f_off, w.f_deg, w.f_eoff, w.tiles, w.err);
+    else
+      hipLaunchKernelGGL(k_frontier<false>, grid, dim3(THREADS), 0, s, h, sd, degree, nodes,
+                         node_cap, g->offsets, N, E, w.f_off, w.f_deg, w.f_eoff, w.tiles, w.err);
+  };
+  // Frontier positions, and their tiles, of the next hop.
+  auto lay_out = [&] {
+    h.fstart[0] = 0;
+    h.tstart[0] = 0;
+    for (int b = 0; b < B; ++b) {
+      h.fpos[b] = fbeg[b];
+      h.fstart[b + 1] = h.fstart[b] + (fend[b] - fbeg[b]);
+      h.tstart[b + 1] = h.tstart[b] + (int32_t)((fend[b] - fbeg[b] + F_TILE - 1) / F_TILE);
+      h.ebase[b] = e_b[b];
+    }
+  };
+  lay_out();
+  bool seeded = false;
   for (int k = 1; k <= K; ++k) {
     for (int b = 0; b < B; ++b) edge_ptr[(int64_t)b * (K + 1) + (k - 1)] = e_b[b];
     const int32_t f = fanouts[k - 1];
     h.f = f;
     h.k = k;
-    h.fstart[0] = 0;
-    for (int b = 0; b < B; ++b) {
-      h.fpos[b] = fbeg[b];
-      h.fstart[b + 1] = h.fstart[b] + (fend[b] - fbeg[b]);
-      h.ebase[b] = e_b[b];
-    }
-    h.ftot = h.fstart[B];
+    lay_out();
+    const int64_t ftot = h.fstart[B];
     int64_t new_b[DG_MAX_BATCHES];
-    if (h.ftot == 0 || f == 0) {
+    if (ftot == 0 || f == 0) {
       for (int b = 0; b < B; ++b) new_b[b] = 0;
     } else {
       const int ev0 = tm.mark();
@@ -726,36 +810,29 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
       // or leave prev clear: its count pass then reads every word anyway and
       // does both on the way, where marks would need a pass over the whole mask
       // for the map and a fill of prev afterwards.
-      const int64_t ebound = f < 0 ? E : h.ftot * (int64_t)f;
+      const int64_t ebound = f < 0 ? E : ftot * (int64_t)f;
       // With a packing state (and the direct table, which gives older pairs'
       // list slots) the last hop's compaction also does packing's pass.
       const bool fuse = pk && direct && k == K;
       const bool full_last = k == K && (member_lines || exit_clear || fuse);
       h.touched = (ebound <= N / 16 && !full_last) ? w.touched : nullptr;
-      if (h.touched && (rc = fill_u64(reinterpret_cast<uint64_t *>(w.touched),
-                                      (size_t)mc_touch_bytes(N) / 8, 0, s)))
-        return rc;
-      hipLaunchKernelGGL(k_frontier_degree, dim3(blocks_for(h.ftot)), dim3(THREADS), 0, s, h,
-                         nodes, node_cap, g->offsets, N, E, w.f_off, w.f_deg, w.f_cnt, w.err);
+      frontier(!seeded, true);
+      seeded = true;
       DG_HIP(hipGetLastError());
-      if ((rc = scan_exclusive(w.f_cnt, w.f_eoff, h.ftot, w.tiles, s))) return rc;
-      // edge offsets at the batch boundaries, kept on the device
-      hipLaunchKernelGGL(k_batch_bounds, dim3(1), dim3(DG_MAX_BATCHES + 1), 0, s, h, w.f_eoff,
-                         w.small + ST_BOUNDS);
       // lanes per frontier node: up to 8 while the frontier has fewer than 2^20
       // entries (never more lanes than draws; fan-outs above FMAX keep one)
       int lpn = 1;
-      while (lpn < 8 && h.ftot * lpn < (1 << 20) && (f < 0 || (f <= FMAX && 2 * lpn <= f)))
+      while (lpn < 8 && ftot * lpn < (1 << 20) && (f < 0 || (f <= FMAX && 2 * lpn <= f)))
         lpn *= 2;
-      const dim3 hg(blocks_for(h.ftot * lpn)), hb(THREADS);
+      const dim3 hg((unsigned)(h.tstart[B] * lpn)), hb(THREADS);
       // register-path capacity: the smallest that holds f (8 when f does not
       // take the register path at all)
       const int fm = (f < 0 || f > FMAX || f <= 8) ? 8 : (f <= 16 ? 16 : 32);
       auto launch = [&](auto lpn_c, auto fm_c) {
         hipLaunchKernelGGL((k_hop_sample<decltype(lpn_c)::value, decltype(fm_c)::value>), hg, hb,
                            0, s, h, nodes, node_cap, g->indices, w.f_off, w.f_deg, w.f_eoff,
-                           w.small + ST_BOUNDS, edge_cap, edge_src, edge_dst, w.visited, N,
-                           w.err);
+                           w.tiles, w.small + ST_BOUNDS, edge_cap, edge_src, edge_dst,
+                           w.visited, N, w.err);
       };
       auto launch_fm = [&](auto lpn_c) {
         if (fm == 8) launch(lpn_c, std::integral_constant<int, 8>());
@@ -776,6 +853,7 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
       w.ms.plines = w.plines;
       w.ms.keep_prev = k < K;  // after the last hop nothing reads prev
       w.ms.touched = h.touched;
+      w.ms.touched_clear = h.touched;  // read by this hop's count pass only
       // With DG_SAMPLE_EXIT_CLEAR the last hop's count pass zeroes every prev
       // word it reads; that is all non-zero ones (prev is a subset of visited)
       // unless touched marks leave some lines unread.
@@ -800,6 +878,7 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
         F.cache_slot = cache_slot;
         F.N = N;
         F.B = B;
+        F.rounds = w.ms.rounds;
         F.nblk = w.ms.nblk;
         F.clear_prev = w.ms.clear_prev;
         F.err = w.err;
@@ -860,6 +939,7 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
         F.seg_out = nodes;
         F.loc_out = loc;
         F.local_out = w.ms.local_out;
+        F.totals_p = w.small + ST_PTOTALS;
         F.packed_ptr = pk->packed_ptr;
         F.packed_cap = pk->packed_cap < pk->pinfo_cap ? pk->packed_cap : pk->pinfo_cap;
         F.pinfo = pk->pinfo;
@@ -871,7 +951,7 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
         F.nodeoff = nullptr;  // the address tables come from pinfo
         F.pairdest = pk->pw.pairdest;
         F.pair_cap = pk->pair_cap;
-        if ((rc = fuse_scan_write(F, w.small + ST_PTOTALS, pk->packed_ptr, s))) return rc;
+        if ((rc = fuse_scan_write(F, s))) return rc;
       } else if ((rc = mask_scan_write(w.ms, s))) {
         return rc;
       }
@@ -883,10 +963,10 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
       if (st[ST_ERR])
         return set_error(DG_EINVAL, "invalid input data: %s",
                          describe_device_error((uint32_t)st[ST_ERR]));
-      const int64_t *bound = st + ST_BOUNDS;
+      const int64_t *edges = st + ST_BOUNDS;
       bool over = false, nover = false;
       for (int b = 0; b < B; ++b) {
-        const int64_t cnt = bound[b + 1] - bound[b];
+        const int64_t cnt = h.fstart[b + 1] > h.fstart[b] ? edges[b] : 0;
         new_b[b] = st[ST_TOTALS + b];
         if (e_b[b] + cnt > edge_cap) over = true;
         if (n_b[b] + new_b[b] > node_cap) nover = true;
@@ -927,6 +1007,15 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
     }
   }
   for (int b = 0; b < B; ++b) edge_ptr[(int64_t)b * (K + 1) + K] = e_b[b];
+  if (!seeded) {  // no hop sampled: the seeds alone
+    for (int b = 0; b < B; ++b) {
+      fbeg[b] = 0;
+      fend[b] = S;
+    }
+    lay_out();
+    frontier(true, false);
+    DG_HIP(hipGetLastError());
+  }
 
   // Local IDs through the (node, batch) table.
   mk.r0 = tm.mark();
@@ -1085,7 +1174,7 @@ extern "C" size_t dg_sample_pack_workspace_bytes(int64_t num_nodes, int32_t B,
     return 0;
   Carve c(nullptr);
   PackInto pk;
-  carve_sample_pack(pk, c, num_nodes, B, node_cap);
+  carve_sample_pack(pk, c, num_nodes, B, node_cap, mc_rounds(num_nodes));
   return c.used;
 }
 
@@ -1108,19 +1197,26 @@ extern "C" int dg_sample_pack_group(
   if ((pack_flags & DG_PACK_ROWS_STREAM) && timing)
     return set_error(DG_EINVAL, "dg_sample_pack_group: timing cannot be combined with "
                                 "DG_PACK_ROWS_STREAM");
-  const size_t need = dg_sample_pack_workspace_bytes(g->num_nodes, B, node_cap);
-  if (need == 0 || K < 0)
+  if (dg_sample_pack_workspace_bytes(g->num_nodes, B, node_cap) == 0 || K < 0)
     return set_error(DG_EINVAL, "dg_sample_pack_group: bad sizes (B=%d K=%d node_cap=%lld)", B,
                      K, (long long)node_cap);
+  // Both workspaces take the same tiles: short ones where they fit, else the longest.
+  PackInto pk;
+  size_t need = 0;
+  for (int rounds : {mc_rounds(g->num_nodes), MC_ROUNDS_MAX}) {
+    Carve c(pack_ws), cs(nullptr);
+    carve_sample_pack(pk, c, g->num_nodes, B, node_cap, rounds);
+    SampleWs sw;
+    carve_sample(sw, cs, g->num_nodes, B, node_cap, (flags & DG_SAMPLE_DIRECT) != 0, rounds);
+    need = c.used;
+    if (need <= pack_ws_bytes && cs.used <= ws_bytes) break;
+  }
   if (!pack_ws || pack_ws_bytes < need || ((uintptr_t)pack_ws & 255))
     return set_error(DG_EWORKSPACE,
                      "dg_sample_pack_group: packing workspace needs %zu bytes, 256-aligned",
                      need);
   const bool rows_async = (pack_flags & DG_PACK_ROWS_STREAM) && packed;
   const int64_t N = g->num_nodes;
-  PackInto pk;
-  Carve c(pack_ws);
-  carve_sample_pack(pk, c, N, B, node_cap);
   pk.packed_ptr = packed_ptr;
   pk.packed_cap = packed_cap;
   pk.group_unique = group_unique;

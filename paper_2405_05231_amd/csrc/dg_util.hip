@@ -4,6 +4,8 @@
 #include <stdarg.h>
 #include <string.h>
 
+#include <type_traits>
+
 #include "dg_passes.h"
 
 namespace dg {
@@ -88,6 +90,26 @@ __global__ void k_fill_u64(uint64_t *p, size_t n, uint64_t v) {
   for (; i < n; i += stride) p[i] = v;
 }
 
+// Several ranges zeroed by one launch.
+__global__ void k_zero_ranges(ZeroRanges z) {
+  const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const size_t stride = (size_t)gridDim.x * blockDim.x;
+#pragma unroll
+  for (int q = 0; q < ZeroRanges::MAX; ++q)
+    for (size_t i = i0; i < z.n[q]; i += stride) z.p[q][i] = 0ull;
+}
+
+int zero_ranges(const ZeroRanges &z, hipStream_t s) {
+  size_t most = 0;
+  for (size_t n : z.n) most = n > most ? n : most;
+  if (most == 0) return DG_OK;
+  size_t blocks = (most + 255) / 256;
+  if (blocks > 8192) blocks = 8192;
+  hipLaunchKernelGGL(k_zero_ranges, dim3((unsigned)blocks), dim3(256), 0, s, z);
+  DG_HIP(hipGetLastError());
+  return DG_OK;
+}
+
 int fill_u64(uint64_t *p, size_t n, uint64_t value, hipStream_t s) {
   if (n == 0) return DG_OK;
   size_t blocks = (n + 255) / 256;
@@ -97,127 +119,29 @@ int fill_u64(uint64_t *p, size_t n, uint64_t value, hipStream_t s) {
   return DG_OK;
 }
 
-// ---------------------------------------------------------------- scan
-constexpr int SC_THREADS = 256;
-constexpr int SC_ITEMS = 8;
-constexpr int SC_TILE = SC_THREADS * SC_ITEMS;
-
-size_t scan_tile_count(int64_t n) { return (size_t)((n + SC_TILE - 1) / SC_TILE) + 1; }
-
-// Block-wide exclusive scan of one value per thread; *total gets the block sum.
-template <int NT>
-__device__ __forceinline__ int64_t block_excl_scan(int64_t x, int64_t *total) {
-  __shared__ int64_t s_w[NT / 64];
-  const int lane = lane_id(), w = threadIdx.x >> 6;
-  int64_t incl = wave_incl_sum(x);
-  if (lane == 63) s_w[w] = incl;
-  __syncthreads();
-  int64_t before = 0, sum = 0;
-#pragma unroll
-  for (int i = 0; i < NT / 64; ++i) {
-    int64_t v = s_w[i];
-    if (i < w) before += v;
-    sum += v;
-  }
-  __syncthreads();
-  *total = sum;
-  return before + incl - x;
-}
-
-__global__ __launch_bounds__(SC_THREADS) void k_scan_reduce(const int64_t *in, int64_t n,
-                                                            int64_t *tile_sums) {
-  int64_t t0 = (int64_t)blockIdx.x * SC_TILE;
-  int64_t acc = 0;
-#pragma unroll
-  for (int r = 0; r < SC_ITEMS; ++r) {
-    int64_t i = t0 + r * SC_THREADS + threadIdx.x;
-    if (i < n) acc += in[i];
-  }
-  int64_t total;
-  (void)block_excl_scan<SC_THREADS>(acc, &total);
-  if (threadIdx.x == 0) tile_sums[blockIdx.x] = total;
-}
-
-// One block scans the tile sums in place (exclusive); tile_sums[ntiles] = total.
-__global__ __launch_bounds__(1024) void k_scan_tiles(int64_t *tile_sums, int64_t ntiles) {
-  int64_t carry = 0;
-  for (int64_t c0 = 0; c0 < ntiles; c0 += 1024) {
-    int64_t i = c0 + threadIdx.x;
-    int64_t v = i < ntiles ? tile_sums[i] : 0;
-    int64_t total;
-    int64_t ex = block_excl_scan<1024>(v, &total);
-    if (i < ntiles) tile_sums[i] = carry + ex;
-    carry += total;
-  }
-  if (threadIdx.x == 0) tile_sums[ntiles] = carry;
-}
-
-// Each thread owns SC_ITEMS consecutive items of the tile.
-__global__ __launch_bounds__(SC_THREADS) void k_scan_apply(const int64_t *in, int64_t *out,
-                                                           int64_t n, const int64_t *tile_sums) {
-  int64_t t0 = (int64_t)blockIdx.x * SC_TILE + (int64_t)threadIdx.x * SC_ITEMS;
-  int64_t v[SC_ITEMS];
-  int64_t acc = 0;
-#pragma unroll
-  for (int r = 0; r < SC_ITEMS; ++r) {
-    int64_t i = t0 + r;
-    v[r] = i < n ? in[i] : 0;
-    acc += v[r];
-  }
-  int64_t total;
-  int64_t run = tile_sums[blockIdx.x] + block_excl_scan<SC_THREADS>(acc, &total);
-#pragma unroll
-  for (int r = 0; r < SC_ITEMS; ++r) {
-    int64_t i = t0 + r;
-    if (i < n) out[i] = run;
-    run += v[r];
-  }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    int64_t ntiles = gridDim.x;
-    out[n] = tile_sums[ntiles];
-  }
-}
-
-int scan_exclusive(const int64_t *in, int64_t *out, int64_t n, int64_t *tile_sums,
-                   hipStream_t s) {
-  int64_t ntiles = (n + SC_TILE - 1) / SC_TILE;
-  if (ntiles == 0) {
-    DG_HIP(hipMemsetAsync(out, 0, sizeof(int64_t), s));
-    return DG_OK;
-  }
-  hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)ntiles), dim3(SC_THREADS), 0, s, in, n,
-                     tile_sums);
-  hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, s, tile_sums, ntiles);
-  hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)ntiles), dim3(SC_THREADS), 0, s, in, out, n,
-                     tile_sums);
-  DG_HIP(hipGetLastError());
-  return DG_OK;
-}
-
 // ---------------------------------------------------------------- mask compaction
-size_t mask_scan_ws_bytes(int64_t N, int B) {
-  Carve c(nullptr);
-  MaskScan m{};
-  m.N = N;
-  m.B = B;
-  mask_scan_carve(m, c);
-  return c.used;
-}
-
-void mask_scan_carve(MaskScan &m, Carve &c) {
-  m.nblk = mc_blocks(m.N);
-  size_t rows = (size_t)mc_rows(m.B);
+void mask_scan_carve(MaskScan &m, Carve &c, int rounds) {
+  m.rounds = rounds;
+  m.nblk = mc_blocks(m.N, rounds);
+  const size_t rows = (size_t)mc_rows(m.B), pad = (size_t)mc_pad_nodes(m.N);
   m.cnt = c.take<uint32_t>(rows * (size_t)m.nblk);
   m.wpre = c.take<uint32_t>(rows * (size_t)m.nblk * MC_WAVES);
   m.wcnt = c.take<uint32_t>((size_t)m.nblk * MC_WAVES);
-  m.cw_mask = c.take<uint64_t>((size_t)m.nblk * MC_BLOCK_NODES);
-  m.cw_off = c.take<uint16_t>((size_t)m.nblk * MC_BLOCK_NODES);
+  m.cw_mask = c.take<uint64_t>(pad);
+  m.cw_off = c.take<uint16_t>(pad);
   m.base = c.take<int64_t>(rows * (size_t)m.nblk);
-  m.chunk_sum = c.take<int64_t>(rows * (size_t)mc_chunks(m.nblk));
   m.totals = c.take<int64_t>(rows + 1);  // + a slot for the staged error word
 }
 
-// Count pass.  One wave per tile of MC_TILE nodes, MC_ROUNDS rounds of 64.
+// Calls f with the rounds per tile as a compile-time constant.
+template <typename F>
+static void with_rounds(int rounds, F f) {
+  if (rounds == 16) f(std::integral_constant<int, 16>());
+  else if (rounds == 4) f(std::integral_constant<int, 4>());
+  else f(std::integral_constant<int, 1>());
+}
+
+// Count pass.  One wave per tile of R rounds of 64 nodes.
 // What is the same across the wave is kept in scalar registers: the tile base,
 // the rounds that may hold a word, and for each round the lanes whose word is
 // non-empty and the lanes whose node is cached; a round without a word costs a
@@ -237,8 +161,8 @@ void mask_scan_carve(MaskScan &m, Carve &c) {
 // (with clear_prev the prev words read are zeroed instead).  Otherwise packing
 // mode (no prev; cache_slot nullable; with clear_mask each non-zero mask word
 // is zeroed once read).
-constexpr int MC_CROUNDS = 4;
-constexpr int MC_CWORDS = 64 * MC_CROUNDS + 4;  // + zero padding for the last read
+constexpr int mc_crounds(int R) { return R < 4 ? R : 4; }
+constexpr int mc_cwords(int R) { return 64 * mc_crounds(R) + 4; }  // + zero padding for the last read
 
 __device__ __forceinline__ uint32_t rank_below(uint64_t set, uint32_t base) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(set >> 32),
@@ -255,9 +179,11 @@ __device__ __forceinline__ void wait_vm_all() { __builtin_amdgcn_s_waitcnt(0x0F7
 // Eight waves per SIMD: the pass is latency-bound under load, and with the
 // prev words read in two halves it fits in 64 VGPRs (a few spill to scratch);
 // without the hint it takes 72 and runs seven.
-template <bool SAMPLE>
+template <bool SAMPLE, int R>
 __global__ __launch_bounds__(MC_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void k_mask_count(MaskScan a) {
+  constexpr int MC_ROUNDS = R, MC_TILE = 64 * R, MC_BLOCK_NODES = MC_TILE * MC_WAVES;
+  constexpr int MC_CROUNDS = mc_crounds(R), MC_CWORDS = mc_cwords(R);
   __shared__ uint32_t s_cnt[MC_WAVES][DG_MAX_BATCHES + 4];
   __shared__ __align__(16) uint32_t s_w[MC_WAVES][2][MC_CWORDS];
   const int lane = lane_id();
@@ -282,6 +208,11 @@ void k_mask_count(MaskScan a) {
     }
     live = __builtin_amdgcn_readfirstlane(l);
     lmask = lm;
+    if (a.touched_clear) {  // the marks are done with: left zero for the next hop or call
+      uint64_t *fw = reinterpret_cast<uint64_t *>(a.touched_clear + (t0 >> MC_TOUCH_SHIFT));
+      const uint64_t mine = lane < MC_ROUNDS ? f[lane] : 0ull;
+      if (mine != 0ull) fw[lane] = 0ull;
+    }
   }
 
   uint64_t m[MC_ROUNDS];
@@ -325,6 +256,12 @@ void k_mask_count(MaskScan a) {
     }
     if (lane < MC_ROUNDS)
       reinterpret_cast<uint64_t *>(a.lines_out + (t0 >> MC_TOUCH_SHIFT))[lane] = lb;
+    if (blockIdx.x == gridDim.x - 1) {  // the map's bytes past the last tile
+      const int64_t end = mc_touch_bytes(a.N);
+      for (int64_t i = (((int64_t)gridDim.x * MC_BLOCK_NODES) >> MC_TOUCH_SHIFT) + threadIdx.x;
+           i < end; i += MC_THREADS)
+        a.lines_out[i] = 0;
+    }
   }
   uint64_t any[MC_ROUNDS];  // lanes of round r with a word to list (uniform)
 #pragma unroll
@@ -355,7 +292,7 @@ void k_mask_count(MaskScan a) {
     // prev words in two halves of the rounds: half the registers (so more
     // waves per SIMD) for one more round trip
     uint64_t *pv = a.prev + t0;
-    constexpr int H = MC_ROUNDS / 2;
+    constexpr int H = MC_ROUNDS < 2 ? 1 : MC_ROUNDS / 2;
 #pragma unroll
     for (int h0 = 0; h0 < MC_ROUNDS; h0 += H) {
       uint64_t p[H];
@@ -466,72 +403,78 @@ void k_mask_count(MaskScan a) {
       pre[j * rows + i] = v;
       v += s_cnt[j][i];
     }
-    a.cnt[(size_t)blockIdx.x * rows + i] = v;
+    a.cnt[(size_t)i * a.nblk + blockIdx.x] = v;
   }
 }
 
-// Row scan, three phases over the [nblk][rows] count matrix: chunk sums,
-// scan of chunk sums down each row, then per-block bases.
-// A chunk of the count matrix (MC_CHUNK consecutive blocks, all rows) is one
-// contiguous run of memory; it is staged through LDS so the global reads and
-// writes are coalesced and only the column walks stride.
-constexpr int RS_THREADS = 256;
-constexpr int RS_MAX = MC_CHUNK * (DG_MAX_BATCHES + 4);
+// Row scan: one block per row of the count matrix (of each of up to two
+// matrices), RS_ITEMS values per thread in flight.  It replaces three launches
+// (chunk sums, their scan, bases) over a block-major matrix, whose rows had to
+// be walked with a stride: 21 us to 8 us at 32M nodes, 9 to 4 at 1M.  Also
+// stages the device error word for the caller's read-back (err_stage), after
+// every kernel of the pass so far has run.
+constexpr int RS_ITEMS = 4;
+struct RowScan {
+  const uint32_t *cnt[2];
+  int64_t *base[2];
+  int64_t *totals[2];
+  int rows;
+  int64_t nblk;
+  const uint32_t *err;
+  int64_t *err_stage;
+};
 
-__device__ __forceinline__ int stage_chunk(const MaskScan &a, uint32_t *s, int rows) {
-  const int64_t b0 = (int64_t)blockIdx.x * MC_CHUNK;
-  const int n = (int)(a.nblk - b0 < MC_CHUNK ? a.nblk - b0 : MC_CHUNK);
-  const uint32_t *src = a.cnt + (size_t)b0 * rows;
-  for (int i = threadIdx.x; i < n * rows; i += RS_THREADS) s[i] = src[i];
-  __syncthreads();
-  return n;
-}
-
-__global__ __launch_bounds__(RS_THREADS) void k_rows_chunk_sum(MaskScan a) {
-  __shared__ uint32_t s[RS_MAX];
-  const int rows = mc_rows(a.B);
-  const int n = stage_chunk(a, s, rows);
-  for (int t = threadIdx.x; t < rows; t += RS_THREADS) {
-    int64_t acc = 0;
-    for (int k = 0; k < n; ++k) acc += s[k * rows + t];
-    a.chunk_sum[(size_t)blockIdx.x * rows + t] = acc;
-  }
-}
-
-// Also stages the device error word for the caller's read-back (err_stage),
-// after every kernel of the pass so far has run.
-__global__ __launch_bounds__(1024) void k_rows_chunk_scan(MaskScan a) {
-  const int rows = mc_rows(a.B);
-  const int row = blockIdx.x;
-  const int64_t nch = mc_chunks(a.nblk);
+template <int NT>
+__global__ __launch_bounds__(NT) void k_rows_scan(RowScan a) {
+  const int view = blockIdx.x >= (unsigned)a.rows, row = (int)blockIdx.x - view * a.rows;
+  const uint32_t *in = (view ? a.cnt[1] : a.cnt[0]) + (size_t)row * a.nblk;
+  int64_t *out = (view ? a.base[1] : a.base[0]) + (size_t)row * a.nblk;
   int64_t carry = 0;
-  for (int64_t c0 = 0; c0 < nch; c0 += 1024) {
-    const int64_t i = c0 + threadIdx.x;
-    const int64_t v = i < nch ? a.chunk_sum[(size_t)i * rows + row] : 0;
-    int64_t total;
-    const int64_t ex = block_excl_scan<1024>(v, &total);
-    if (i < nch) a.chunk_sum[(size_t)i * rows + row] = carry + ex;
-    carry += total;
-  }
-  if (threadIdx.x == 0) a.totals[row] = carry;
-  if (row == 0 && threadIdx.x == 0 && a.err_stage) *a.err_stage = (int64_t)*a.err;
-}
-
-__global__ __launch_bounds__(RS_THREADS) void k_rows_apply(MaskScan a) {
-  __shared__ uint32_t s[RS_MAX];
-  __shared__ int64_t sb[RS_MAX];
-  const int rows = mc_rows(a.B);
-  const int n = stage_chunk(a, s, rows);
-  for (int t = threadIdx.x; t < rows; t += RS_THREADS) {
-    int64_t run = a.chunk_sum[(size_t)blockIdx.x * rows + t];
-    for (int k = 0; k < n; ++k) {
-      sb[k * rows + t] = run;
-      run += s[k * rows + t];
+  for (int64_t c0 = 0; c0 < a.nblk; c0 += NT * RS_ITEMS) {
+    uint32_t v[RS_ITEMS];
+#pragma unroll
+    for (int q = 0; q < RS_ITEMS; ++q) {
+      const int64_t i = c0 + q * NT + threadIdx.x;
+      v[q] = i < a.nblk ? in[i] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < RS_ITEMS; ++q) {
+      if (c0 + q * NT >= a.nblk) break;  // uniform
+      const int64_t i = c0 + q * NT + threadIdx.x;
+      int64_t total;
+      const int64_t ex = block_excl_scan<NT>((int64_t)v[q], &total);
+      if (i < a.nblk) out[i] = carry + ex;
+      carry += total;
     }
   }
-  __syncthreads();
-  int64_t *dst = a.base + (size_t)blockIdx.x * MC_CHUNK * rows;
-  for (int i = threadIdx.x; i < n * rows; i += RS_THREADS) dst[i] = sb[i];
+  if (threadIdx.x == 0) {
+    (view ? a.totals[1] : a.totals[0])[row] = carry;
+    if (blockIdx.x == 0 && a.err_stage) *a.err_stage = (int64_t)*a.err;
+  }
+}
+
+// The row scans of one count matrix, or of two of the same shape.
+static int rows_scan(const MaskScan &m, const MaskScan *m2, hipStream_t s) {
+  RowScan r{};
+  r.cnt[0] = m.cnt;
+  r.base[0] = m.base;
+  r.totals[0] = m.totals;
+  if (m2) {
+    r.cnt[1] = m2->cnt;
+    r.base[1] = m2->base;
+    r.totals[1] = m2->totals;
+  }
+  r.rows = mc_rows(m.B);
+  r.nblk = m.nblk;
+  r.err = m.err;
+  r.err_stage = m.err_stage;
+  const dim3 g((unsigned)(r.rows * (m2 ? 2 : 1)));
+  if (m.nblk <= 256 * RS_ITEMS)
+    hipLaunchKernelGGL(k_rows_scan<256>, g, dim3(256), 0, s, r);
+  else
+    hipLaunchKernelGGL(k_rows_scan<1024>, g, dim3(1024), 0, s, r);
+  DG_HIP(hipGetLastError());
+  return DG_OK;
 }
 
 // Member lines from the mask alone (for sweeps that did not read every word):
@@ -562,22 +505,17 @@ int mask_scan_count(MaskScan &m, hipStream_t s) {
   if ((m.prev && (m.cache_slot || m.clear_mask)) || (m.keep_prev && m.clear_prev) ||
       (!m.prev && (m.keep_prev || m.clear_prev || m.lines_out)) || (m.lines_out && m.touched))
     return set_error(DG_EINVAL, "internal: inconsistent count-pass mode");
-  if (m.prev)
-    hipLaunchKernelGGL(k_mask_count<true>, dim3((unsigned)m.nblk), dim3(MC_THREADS), 0, s, m);
-  else
-    hipLaunchKernelGGL(k_mask_count<false>, dim3((unsigned)m.nblk), dim3(MC_THREADS), 0, s, m);
+  with_rounds(m.rounds, [&](auto r) {
+    constexpr int R = decltype(r)::value;
+    if (m.prev)
+      hipLaunchKernelGGL((k_mask_count<true, R>), dim3((unsigned)m.nblk), dim3(MC_THREADS), 0, s,
+                         m);
+    else
+      hipLaunchKernelGGL((k_mask_count<false, R>), dim3((unsigned)m.nblk), dim3(MC_THREADS), 0, s,
+                         m);
+  });
   DG_HIP(hipGetLastError());
-  return mask_scan_rows(m, s);
-}
-
-int mask_scan_rows(MaskScan &m, hipStream_t s) {
-  if (m.nblk == 0) return fill_u64(reinterpret_cast<uint64_t *>(m.totals), mc_rows(m.B), 0, s);
-  const unsigned nch = (unsigned)mc_chunks(m.nblk);
-  hipLaunchKernelGGL(k_rows_chunk_sum, dim3(nch), dim3(RS_THREADS), 0, s, m);
-  hipLaunchKernelGGL(k_rows_chunk_scan, dim3((unsigned)mc_rows(m.B)), dim3(1024), 0, s, m);
-  hipLaunchKernelGGL(k_rows_apply, dim3(nch), dim3(RS_THREADS), 0, s, m);
-  DG_HIP(hipGetLastError());
-  return DG_OK;
+  return rows_scan(m, nullptr, s);
 }
 
 // 64 x 64 bit transpose across the wave: lane i holds row i (bit j is entry
@@ -653,8 +591,9 @@ __device__ __forceinline__ uint64_t wave_transpose64(uint64_t r) {
 // at the index of its list slot: the entry of a cached node is final, the
 // others are left DG_LOC_PENDING for packing.  Each lane loads the cache slot
 // of its own word before the pairs are emitted.
-template <bool PACK, bool LOCAL>
+template <bool PACK, bool LOCAL, int R>
 __global__ __launch_bounds__(MC_THREADS) void k_mask_write(MaskScan a) {
+  constexpr int MC_TILE = 64 * R, MC_BLOCK_NODES = MC_TILE * MC_WAVES;
   // per word of the chunk: first pair (packing, from run_p) << 10 | node
   // offset in the tile, cache slot, listed bits (packing)
   __shared__ int4 s_word[MC_WAVES][64];
@@ -668,24 +607,28 @@ __global__ __launch_bounds__(MC_THREADS) void k_mask_write(MaskScan a) {
   const size_t gwi = (size_t)blk * MC_WAVES + w;
   const uint64_t *cm = a.cw_mask + gwi * MC_TILE;
   const uint16_t *co = a.cw_off + gwi * MC_TILE;
-  const int64_t *bb = a.base + (size_t)blk * rows;
+  const int64_t *bb = a.base + blk;  // row r: bb[r * nblk]
   const uint32_t *pre = a.wpre + gwi * rows;
+  if (PACK && a.ptr_out && blk == 0 && w == 0) {
+    if (lane < B) a.ptr_out[lane] = a.seg_base[lane];
+    if (lane == 0) a.ptr_out[B] = a.ptr_end;
+  }
   // The count, the bases and the first chunk are requested together: the
   // chunk's 64 entries lie inside the wave's part of the compact list
   // whatever the count.
   const uint32_t n = a.wcnt[gwi];
   uint64_t m = cm[lane];
   uint32_t off = co[lane];
-  const int64_t run0 = lane < B ? bb[lane] + pre[lane] : 0;
+  const int64_t run0 = lane < B ? bb[lane * a.nblk] + pre[lane] : 0;
   int64_t dest_b = lane < B ? a.seg_base[lane] + run0 : 0;  // next list slot of batch b
   const int64_t end_b = (!PACK && lane < B) ? a.seg_end[lane] : 0;
   int32_t local_b = 0;                                      // its local index
   if (LOCAL) local_b = lane < B ? (int32_t)(a.local_base[lane] + run0) : 0;
   int64_t run_u = 0, run_nc = 0, run_p = 0;
   if (PACK) {
-    run_u = bb[row_all(B)] + pre[row_all(B)];
-    run_nc = bb[row_packed(B)] + pre[row_packed(B)];
-    run_p = bb[row_pairs(B)] + pre[row_pairs(B)];
+    run_u = bb[row_all(B) * a.nblk] + pre[row_all(B)];
+    run_nc = bb[row_packed(B) * a.nblk] + pre[row_packed(B)];
+    run_p = bb[row_pairs(B) * a.nblk] + pre[row_pairs(B)];
   }
   wait_vm_all();
   if (n == 0) return;  // wave-uniform
@@ -767,12 +710,15 @@ int mask_scan_write(const MaskScan &m, hipStream_t s) {
       (pack && m.loc_out) || (!m.loc_out != !m.loc_slot))
     return set_error(DG_EINVAL, "internal: inconsistent compaction outputs");
   const dim3 g((unsigned)m.nblk), bl(MC_THREADS);
-  if (pack)
-    hipLaunchKernelGGL((k_mask_write<true, false>), g, bl, 0, s, m);
-  else if (m.local_out)
-    hipLaunchKernelGGL((k_mask_write<false, true>), g, bl, 0, s, m);
-  else
-    hipLaunchKernelGGL((k_mask_write<false, false>), g, bl, 0, s, m);
+  with_rounds(m.rounds, [&](auto r) {
+    constexpr int R = decltype(r)::value;
+    if (pack)
+      hipLaunchKernelGGL((k_mask_write<true, false, R>), g, bl, 0, s, m);
+    else if (m.local_out)
+      hipLaunchKernelGGL((k_mask_write<false, true, R>), g, bl, 0, s, m);
+    else
+      hipLaunchKernelGGL((k_mask_write<false, false, R>), g, bl, 0, s, m);
+  });
   DG_HIP(hipGetLastError());
   return DG_OK;
 }
@@ -780,7 +726,7 @@ int mask_scan_write(const MaskScan &m, hipStream_t s) {
 // ---------------------------------------------------------------- fused compaction
 // Adds bit `lane & 31` of the low (lanes < 32) or high (lanes >= 32) halves of
 // the k words staged in lo/hi to `mine` (batch `lane`'s count), four words
-// per 128-bit LDS read.  The staging areas hold MC_CWORDS entries.
+// per 128-bit LDS read.  The staging areas hold mc_cwords(R) entries.
 __device__ __forceinline__ void lds_count(uint32_t k, uint32_t *lo, uint32_t *hi, int lane,
                                           uint32_t &mine) {
   if (k == 0) return;  // uniform
@@ -808,12 +754,13 @@ __device__ __forceinline__ void lds_count(uint32_t k, uint32_t *lo, uint32_t *hi
 // and cache slots, so a part costs one round trip.  Per-batch counts, a part
 // at a time: the part's words with new bits are staged in one LDS area and its
 // non-cached words in another, and lane b counts bit b of each.
-constexpr int FC_PART = MC_ROUNDS / 4;
-
 // It runs eight waves per SIMD without a hint (54 VGPRs); a hint of eight
 // waves caps its scalar registers at 80 and spills 20 of them into vector
 // lanes (about 150 more vector instructions per wave).
+template <int R>
 __global__ __launch_bounds__(MC_THREADS) void k_fuse_count(FuseScan a) {
+  constexpr int MC_ROUNDS = R, MC_TILE = 64 * R, MC_BLOCK_NODES = MC_TILE * MC_WAVES;
+  constexpr int MC_CROUNDS = mc_crounds(R), MC_CWORDS = mc_cwords(R), FC_PART = MC_CROUNDS;
   __shared__ uint32_t s_cs[MC_WAVES][DG_MAX_BATCHES + 4];
   __shared__ uint32_t s_cp[MC_WAVES][DG_MAX_BATCHES + 4];
   __shared__ __align__(16) uint32_t s_w[MC_WAVES][4][MC_CWORDS];
@@ -979,19 +926,7 @@ __global__ __launch_bounds__(MC_THREADS) void k_fuse_count(FuseScan a) {
       pre[j * rows + row] = v;
       v += sv ? s_cs[j][row] : s_cp[j][row];
     }
-    (sv ? a.cnt_s : a.cnt_p)[(size_t)blockIdx.x * rows + row] = v;
-  }
-}
-
-// packed_ptr from the p view's per-batch totals.
-__global__ void k_fuse_ptr(const int64_t *totals, int B, int64_t *packed_ptr) {
-  if (threadIdx.x == 0) {
-    int64_t run = 0;
-    packed_ptr[0] = 0;
-    for (int b = 0; b < B; ++b) {
-      run += totals[b];
-      packed_ptr[b + 1] = run;
-    }
+    (sv ? a.cnt_s : a.cnt_p)[(size_t)row * a.nblk + blockIdx.x] = v;
   }
 }
 
@@ -1007,7 +942,9 @@ __global__ void k_fuse_ptr(const int64_t *totals, int B, int64_t *packed_ptr) {
 // batch's share of the chunk, a few words where the chunk's nodes are cold,
 // instead of one step per word for every lane.  Blocks run in XCD-contiguous
 // order, as in the other write pass.
+template <int R>
 __global__ __launch_bounds__(MC_THREADS) void k_fuse_write(FuseScan a) {
+  constexpr int MC_TILE = 64 * R, MC_BLOCK_NODES = MC_TILE * MC_WAVES;
   // per word of the chunk: first pair (from run_p) << 10 | node offset in the
   // tile, cache slot, non-cached bits
   __shared__ int4 s_word[MC_WAVES][64];
@@ -1021,8 +958,7 @@ __global__ __launch_bounds__(MC_THREADS) void k_fuse_write(FuseScan a) {
   const uint64_t *cn = a.cw_new + gwi * MC_TILE;
   const uint16_t *co = a.cw_off + gwi * MC_TILE;
   const int32_t *csl = a.cw_slot + gwi * MC_TILE;
-  const int64_t *bs = a.base_s + (size_t)blk * rows;
-  const int64_t *bp = a.base_p + (size_t)blk * rows;
+  const int64_t *bs = a.base_s + blk, *bp = a.base_p + blk;  // row r: bs[r * nblk]
   const uint32_t *ps = a.wpre_s + gwi * rows;
   const uint32_t *pp = a.wpre_p + gwi * rows;
   // The count, the bases and the first chunk are requested together: the
@@ -1034,18 +970,27 @@ __global__ __launch_bounds__(MC_THREADS) void k_fuse_write(FuseScan a) {
   int32_t sl = csl[lane];  // the node's cache slot (for a cached node's new pairs)
   // batch `lane`: the next slot of its segment (dest_b; li within the batch's
   // node_cap entries) and the next row of its chunk of P
-  int64_t dest_b = 0, pd_b = 0;
+  int64_t dest_b = 0, pd_b = 0, packed_b = 0;
   int32_t li = 0;
   if (lane < B) {
-    dest_b = a.seg_base[lane] + bs[lane] + ps[lane];
+    packed_b = a.totals_p[lane];
+    dest_b = a.seg_base[lane] + bs[lane * a.nblk] + ps[lane];
     li = (int32_t)(dest_b - (int64_t)lane * a.node_cap);
-    pd_b = a.packed_ptr[lane] + bp[lane] + pp[lane];
+    pd_b = bp[lane * a.nblk] + pp[lane];
   }
-  int64_t run_u = bp[row_all(B)] + pp[row_all(B)];
-  int64_t run_nc = bp[row_packed(B)] + pp[row_packed(B)];
-  int64_t run_p = bp[row_pairs(B)] + pp[row_pairs(B)];
+  int64_t run_u = bp[row_all(B) * a.nblk] + pp[row_all(B)];
+  int64_t run_nc = bp[row_packed(B) * a.nblk] + pp[row_packed(B)];
+  int64_t run_p = bp[row_pairs(B) * a.nblk] + pp[row_pairs(B)];
   wait_vm_all();
-  if (n == 0) return;  // wave-uniform
+  if (n == 0 && (blk | (uint32_t)w) != 0) return;  // wave-uniform
+  {  // chunk b of P starts after the batches before it
+    const int64_t end = wave_incl_sum(packed_b);
+    pd_b += end - packed_b;
+    if (blk == 0 && w == 0) {  // packed_ptr
+      if (lane < B) a.packed_ptr[lane + 1] = end;
+      if (lane == 0) a.packed_ptr[0] = 0;
+    }
+  }
   const uint64_t lt = lanes_below();
   for (uint32_t c0 = 0; c0 < n; c0 += 64) {
     const uint32_t i = c0 + lane;
@@ -1133,26 +1078,27 @@ __global__ __launch_bounds__(MC_THREADS) void k_fuse_write(FuseScan a) {
 }
 
 int fuse_scan_count(const FuseScan &f, MaskScan &vs, MaskScan &vp, hipStream_t s) {
-  if (!f.mask || !f.prev || !f.cache_slot || !f.cw_slot || vs.nblk != f.nblk || vp.nblk != f.nblk ||
+  if (!f.mask || !f.prev || !f.cache_slot || !f.cw_slot || vs.nblk != f.nblk || vp.nblk != f.nblk || vs.rounds != f.rounds || vp.rounds != f.rounds ||
       vs.B != f.B || vp.B != f.B)
     return set_error(DG_EINVAL, "internal: inconsistent fused count pass");
   if (f.nblk > 0) {
-    hipLaunchKernelGGL(k_fuse_count, dim3((unsigned)f.nblk), dim3(MC_THREADS), 0, s, f);
+    with_rounds(f.rounds, [&](auto r) {
+      hipLaunchKernelGGL(k_fuse_count<decltype(r)::value>, dim3((unsigned)f.nblk),
+                         dim3(MC_THREADS), 0, s, f);
+    });
     DG_HIP(hipGetLastError());
   }
-  int rc;
-  if ((rc = mask_scan_rows(vs, s))) return rc;
-  return mask_scan_rows(vp, s);
+  return rows_scan(vs, &vp, s);
 }
 
-int fuse_scan_write(const FuseScan &f, const int64_t *totals_p, int64_t *packed_ptr,
-                    hipStream_t s) {
+int fuse_scan_write(const FuseScan &f, hipStream_t s) {
   if (!f.seg_out || !f.loc_out || !f.unc_ids || !f.unc_off || !f.pairdest || !f.cw_slot ||
-      (f.packed_cap > 0 && !f.pinfo) || f.packed_ptr != packed_ptr)
+      (f.packed_cap > 0 && !f.pinfo) || !f.packed_ptr || !f.totals_p || f.nblk < 1)
     return set_error(DG_EINVAL, "internal: inconsistent fused write pass");
-  hipLaunchKernelGGL(k_fuse_ptr, dim3(1), dim3(64), 0, s, totals_p, f.B, packed_ptr);
-  if (f.nblk > 0)
-    hipLaunchKernelGGL(k_fuse_write, dim3((unsigned)f.nblk), dim3(MC_THREADS), 0, s, f);
+  with_rounds(f.rounds, [&](auto r) {
+    hipLaunchKernelGGL(k_fuse_write<decltype(r)::value>, dim3((unsigned)f.nblk),
+                       dim3(MC_THREADS), 0, s, f);
+  });
   DG_HIP(hipGetLastError());
   return DG_OK;
 }
