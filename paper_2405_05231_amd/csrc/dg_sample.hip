@@ -395,58 +395,137 @@ __global__ __launch_bounds__(THREADS) void k_relabel_direct(Lists L, int64_t edg
 // The last hop's new nodes form one ascending segment at the end of each
 // batch's list, so a last-hop edge whose neighbour is one of them gets its
 // local index as the neighbour's rank in that segment; only edges into nodes
-// listed earlier look the direct table up.  The last hop then writes no table
-// entries at all.  Each batch's segment is copied into a padded, aligned buffer
-// together with a sparse index (every S-th element); a block stages its batch's
-// sparse index in LDS, searches it, and reads one S-element block of the
-// segment (from L2: blocks are ordered so that all blocks of a batch run on one
-// XCD).
+// listed earlier look a table up (the direct one, or the hash table, which then
+// holds the earlier nodes alone).  Each batch has a sparse index of its segment
+// (the first element of every block of S); a block of threads stages its batch's
+// index in LDS, searches it, and reads one block of the list (from L2: thread
+// blocks are ordered so that all of a batch run on one XCD).
+//
+// The segment is read where it lies, in blocks that start at multiples of S in
+// memory, so the first and the last may reach past it.  A padded copy of every
+// segment used to be made first: 55 us for 10M entries (32M nodes, 64 batches),
+// and the index alone takes 13 us; blocks at any alignment cost the search 10 to
+// 40% (two lines per block).
 constexpr int RL_THREADS = 512;
 constexpr int RL_CHUNKS = 4;          // edge chunks per block (one staging of the index)
 constexpr int RL_SPARSE_MAX = 16384;  // sparse-index entries per batch (64 KB of LDS)
 constexpr int RL_S_MAX_LOG2 = 6;      // block length S = 16, 32 or 64
 constexpr int RL_S_MIN_LOG2 = 4;
-constexpr int64_t RL_SEGMENT_MAX = (int64_t)RL_SPARSE_MAX << RL_S_MAX_LOG2;
+constexpr int64_t RL_SEGMENT_MAX =
+    (int64_t)(RL_SPARSE_MAX - 1) << RL_S_MAX_LOG2;  // one block more where it starts inside one
 
 // edges per thread for block length 2^SLOG2 (keeps the block reads within registers)
 __host__ __device__ constexpr int rl_edges(int slog2) { return slog2 <= 4 ? 4 : (slog2 == 5 ? 2 : 1); }
 
-inline int64_t rl_segcap(int64_t node_cap) {
-  return (node_cap + (1 << RL_S_MAX_LOG2) + 63) & ~(int64_t)63;
+// Sparse-index entries a batch has room for: the index lies in the frontier
+// arrays, which are free by then (8 bytes per list entry).  m nodes need at most
+// (m + 30) / 16 entries, and m <= node_cap.
+inline int rl_sparse_cap(int64_t node_cap) {
+  return (int)(2 * node_cap < RL_SPARSE_MAX ? 2 * node_cap : RL_SPARSE_MAX);
 }
 
 struct LastHop {
   int B;
   int s_log2;                           // block length S = 2^s_log2
+  int chunks;                           // edge chunks per block
   int32_t bstart[DG_MAX_BATCHES + 1];   // logical blocks before batch b
   int32_t m[DG_MAX_BATCHES];            // length of b's last-hop segment
+  int32_t a[DG_MAX_BATCHES];            // its first node's place in its block
   int32_t ecount[DG_MAX_BATCHES];       // b's last-hop edges
   int64_t seg0[DG_MAX_BATCHES];         // local index of the segment's first node
   int64_t e0[DG_MAX_BATCHES];           // index of b's first last-hop edge
-  int64_t cstart[DG_MAX_BATCHES + 1];   // prefix of the padded segment lengths
+  int32_t rstart[DG_MAX_BATCHES + 1];   // sparse-index entries before batch b
 };
 
-// Copies each batch's last-hop segment into segbuf (row b at b*segcap), padded
-// with INT32_MAX to a multiple of S, and every S-th element into sparse.
-__global__ __launch_bounds__(THREADS) void k_last_segments(LastHop h, const int32_t *nodes,
-                                                           int64_t node_cap, int32_t *segbuf,
-                                                           int64_t segcap, int32_t *sparse) {
-  const int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x;
-  if (i >= h.cstart[h.B]) return;
-  const int b = find_batch_wave(h.cstart, h.B, i);
-  const int64_t r = i - h.cstart[b];
-  const int32_t v = r < h.m[b] ? nodes[(int64_t)b * node_cap + h.seg0[b] + r] : INT32_MAX;
-  segbuf[(int64_t)b * segcap + r] = v;
-  if ((r & ((1 << h.s_log2) - 1)) == 0) sparse[(int64_t)b * RL_SPARSE_MAX + (r >> h.s_log2)] = v;
+// The first element of every block of each batch's last-hop segment.
+__global__ __launch_bounds__(THREADS) void k_last_sparse(LastHop h, const int32_t *nodes,
+                                                         int64_t node_cap, int32_t *sparse,
+                                                         int sparse_cap) {
+  const int32_t i = (int32_t)(blockIdx.x * THREADS + threadIdx.x);
+  if (i >= h.rstart[h.B]) return;
+  int b = 0, top = h.B;  // invariant rstart[b] <= i < rstart[top]
+  while (top - b > 1) {
+    const int mid = (b + top) >> 1;
+    if (h.rstart[mid] <= i) b = mid; else top = mid;
+  }
+  const int32_t r = i - h.rstart[b];
+  const int32_t at = max((r << h.s_log2) - h.a[b], 0);
+  sparse[(int64_t)b * sparse_cap + r] = nodes[(int64_t)b * node_cap + h.seg0[b] + at];
 }
 
-template <int SLOG2>
-__global__ __launch_bounds__(RL_THREADS) void k_relabel_last(LastHop h, const int32_t *segbuf,
-                                                             int64_t segcap,
+// A node listed before the last hop: its local index by the direct table or by
+// the hash table (< 0: absent).
+struct OlderNodes {
+  const int32_t *local;  // nullable: [N][B]
+  LocalTable table;
+};
+template <bool DIRECT>
+__device__ __forceinline__ int64_t older_index(const OlderNodes &o, int32_t u, int b, int B) {
+  return DIRECT ? (int64_t)o.local[(int64_t)u * B + b] : lt_find(o.table, u, b);
+}
+
+typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// v of the lane whose number differs in bit X (1, 2, 4 or 8).
+template <int X>
+__device__ __forceinline__ int xor_lane(int v) {
+  if constexpr (X == 1) return __builtin_amdgcn_update_dpp(0, v, 0xb1, 0xf, 0xf, false);
+  else if constexpr (X == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4e, 0xf, 0xf, false);
+  else return __builtin_amdgcn_ds_swizzle(v, (X << 10) | 0x1f);
+}
+
+// The elements of the S-element window seg[start..] below u, and whether it holds
+// u (bit 16), for each lane's u and start; pos = 0: the lane has no window.  What
+// bounds the search is lines per load instruction: the windows are scattered.
+// S = 16: a lane reads its own 64 bytes, and lanes without a window read nothing
+// (15M last-hop edges of 64 mini-batches at 32M nodes: 228 us, 250 when they
+// read).  Longer windows are read by S/4 lanes together, 16 bytes each, so that an
+// instruction touches 256/S of them and not 64 (S = 32, 3M edges: 153 -> 115 us;
+// at S = 16 the shuffles cost what that gains, 247 us).
+template <int S>
+__device__ __forceinline__ int window_count(const int32_t *seg, int u, int start, int pos,
+                                            int lane) {
+  if constexpr (S == 16) {
+    int t = 0;
+    if (pos > 0) {
+      const u4_any *bp = reinterpret_cast<const u4_any *>(seg + start);
+#pragma unroll
+      for (int q = 0; q < S / 4; ++q) {
+        const u4_any x = bp[q];
+        const int a0 = (int)x.x, a1 = (int)x.y, a2 = (int)x.z, a3 = (int)x.w;
+        t += (a0 < u) + (a1 < u) + (a2 < u) + (a3 < u);
+        t |= (int)((a0 == u) | (a1 == u) | (a2 == u) | (a3 == u)) << 16;
+      }
+    }
+    return t;
+  }
+  constexpr int G = S / 4, PER = 64 / G;  // lanes per window, windows per load
+  int mine = 0;
+#pragma unroll
+  for (int it = 0; it < G; ++it) {
+    const int src = it * PER + lane / G;
+    const int uu = __shfl(u, src, 64), st = __shfl(start, src, 64);
+    const u4_any x = *reinterpret_cast<const u4_any *>(seg + st + 4 * (lane % G));
+    const int a0 = (int)x.x, a1 = (int)x.y, a2 = (int)x.z, a3 = (int)x.w;
+    int t = (a0 < uu) + (a1 < uu) + (a2 < uu) + (a3 < uu) +
+            ((int)((a0 == uu) | (a1 == uu) | (a2 == uu) | (a3 == uu)) << 16);
+    t += xor_lane<1>(t);
+    t += xor_lane<2>(t);
+    if constexpr (G >= 8) t += xor_lane<4>(t);
+    if constexpr (G >= 16) t += xor_lane<8>(t);
+    const int got = __shfl(t, (lane % PER) * G, 64);
+    if (lane / PER == it) mine = got;
+  }
+  return mine;
+}
+
+template <int SLOG2, bool DIRECT>
+__global__ __launch_bounds__(RL_THREADS) void k_relabel_last(LastHop h, const int32_t *nodes,
+                                                             int64_t node_cap,
                                                              const int32_t *sparse,
-                                                             int64_t edge_cap, int32_t *edge_dst,
-                                                             const int32_t *local, int64_t N,
-                                                             uint32_t *err) {
+                                                             int sparse_cap, int64_t edge_cap,
+                                                             int32_t *edge_dst, OlderNodes older,
+                                                             int64_t N, uint32_t *err) {
   constexpr int S = 1 << SLOG2;
   constexpr int EPT = rl_edges(SLOG2);
   constexpr int PER_CHUNK = RL_THREADS * EPT;
@@ -457,20 +536,20 @@ __global__ __launch_bounds__(RL_THREADS) void k_relabel_last(LastHop h, const in
   if (lb >= h.bstart[h.B]) return;  // whole block
   int b = 0;
   while (b + 1 < h.B && h.bstart[b + 1] <= lb) ++b;
-  const int R = (h.m[b] + S - 1) >> SLOG2;
-  const int32_t *sp = sparse + (int64_t)b * RL_SPARSE_MAX;
+  const int m = h.m[b], a = h.a[b];
+  const int R = h.rstart[b + 1] - h.rstart[b];
+  const int32_t *sp = sparse + (int64_t)b * sparse_cap;
   for (int i = threadIdx.x; i < R; i += RL_THREADS) s_sp[i] = sp[i];
   __syncthreads();
   int top = 1;  // highest power of two <= R (uniform)
   while (top * 2 <= R) top *= 2;
   const int64_t eend = h.e0[b] + h.ecount[b];
   int32_t *ed = edge_dst + (int64_t)b * edge_cap;
-  const int32_t *seg = segbuf + (int64_t)b * segcap;
-  const int B = h.B;
   const int64_t seg0 = h.seg0[b];
-  for (int ch = 0; ch < RL_CHUNKS; ++ch) {
-    const int64_t ebase = h.e0[b] + ((int64_t)(lb - h.bstart[b]) * RL_CHUNKS + ch) * PER_CHUNK +
-                          threadIdx.x;
+  const int32_t *seg = nodes + (int64_t)b * node_cap + seg0;
+  for (int ch = 0; ch < h.chunks; ++ch) {
+    const int64_t ebase = h.e0[b] +
+                          ((int64_t)(lb - h.bstart[b]) * h.chunks + ch) * PER_CHUNK + threadIdx.x;
     if (ebase - threadIdx.x >= eend) break;  // uniform
     int32_t u[EPT];
 #pragma unroll
@@ -478,46 +557,63 @@ __global__ __launch_bounds__(RL_THREADS) void k_relabel_last(LastHop h, const in
       const int64_t e = ebase + (int64_t)k * RL_THREADS;
       u[k] = e < eend ? ed[e] : -1;
     }
-    // pos = number of sparse entries <= u: the block that may hold u is pos - 1
+    // pos = number of sparse entries <= u: the block that may hold u is pos - 1.
+    // No branch between the reads of a step, so that they are in flight together.
     int pos[EPT];
 #pragma unroll
     for (int k = 0; k < EPT; ++k) pos[k] = 0;
-    if (R > 0) {
+    if (R > 0) {  // uniform
       for (int step = top; step > 0; step >>= 1) {
+        int32_t x[EPT];
+#pragma unroll
+        for (int k = 0; k < EPT; ++k) x[k] = s_sp[min(pos[k] + step, R) - 1];
 #pragma unroll
         for (int k = 0; k < EPT; ++k)
-          if (pos[k] + step <= R && s_sp[pos[k] + step - 1] <= u[k]) pos[k] += step;
+          pos[k] += pos[k] + step <= R && x[k] <= u[k] ? step : 0;
       }
+    }
+    // The block's elements below u and whether it holds u.  A window that would
+    // reach past the segment is moved inside it: what it gains lies below u (on
+    // the left) or above (on the right).
+    int below[EPT];
+    bool found[EPT];
+    if (m >= S) {  // uniform
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) {
+        const int start = min(max(((pos[k] - 1) << SLOG2) - a, 0), m - S);
+        const int t = window_count<S>(seg, u[k], start, pos[k], (int)threadIdx.x & 63);
+        below[k] = start + (t & 0xffff);
+        found[k] = t >> 16;
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) {
+        below[k] = 0;
+        found[k] = false;
+        for (int q = 0; q < m; ++q) {
+          below[k] += seg[q] < u[k];
+          found[k] |= seg[q] == u[k];
+        }
+      }
+    }
+    // The lookups of the nodes listed before the hop, all before any is used.
+    int64_t j[EPT];
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      const bool ok = u[k] >= 0 && (int64_t)u[k] < N;  // bad IDs already reported
+      j[k] = seg0 + below[k];
+      if (!ok) j[k] = -2;
+      else if (!found[k]) j[k] = older_index<DIRECT>(older, u[k], b, h.B);
     }
 #pragma unroll
     for (int k = 0; k < EPT; ++k) {
       const int64_t e = ebase + (int64_t)k * RL_THREADS;
-      if (e >= eend || u[k] < 0 || (int64_t)u[k] >= N) continue;  // bad IDs already reported
-      int c = 0;
-      bool found = false;
-      const int blk = pos[k] - 1;
-      if (blk >= 0) {
-        const uint4 *bp = reinterpret_cast<const uint4 *>(seg + ((int64_t)blk << SLOG2));
-#pragma unroll
-        for (int q = 0; q < S / 4; ++q) {
-          const uint4 x = bp[q];
-          const int32_t a0 = (int32_t)x.x, a1 = (int32_t)x.y;
-          const int32_t a2 = (int32_t)x.z, a3 = (int32_t)x.w;
-          c += (a0 < u[k]) + (a1 < u[k]) + (a2 < u[k]) + (a3 < u[k]);
-          found |= (a0 == u[k]) | (a1 == u[k]) | (a2 == u[k]) | (a3 == u[k]);
-        }
+      if (j[k] == -2 || e >= eend) continue;
+      if (!found[k] && (j[k] < 0 || j[k] >= seg0)) {
+        atomicOr(err, ERR_INTERNAL);
+        continue;
       }
-      int64_t j;
-      if (found) {
-        j = seg0 + ((int64_t)blk << SLOG2) + c;
-      } else {  // a node listed before the last hop
-        j = local[(int64_t)u[k] * B + b];
-        if (j < 0 || j >= seg0) {
-          atomicOr(err, ERR_INTERNAL);
-          continue;
-        }
-      }
-      ed[e] = (int32_t)j;
+      ed[e] = (int32_t)j[k];
     }
   }
 }
@@ -544,8 +640,6 @@ struct SampleWs {
   int64_t *f_off, *f_deg, *f_eoff, *tiles;
   LocalTable table;  // hash relabelling
   int32_t *local;    // direct relabelling: [N][B]
-  int32_t *segbuf;   // direct relabelling: last-hop segments, [B][rl_segcap(node_cap)]
-  int32_t *sparse;   // ... and their sparse indices, [B][RL_SPARSE_MAX]
   int64_t *small;    // staging for a few counts
   MaskScan ms;
 };
@@ -572,8 +666,6 @@ void carve_sample(SampleWs &w, Carve &c, int64_t N, int B, int64_t node_cap, boo
   w.table.bits = direct ? 0 : lt_bits_for(fmax);
   w.table.slots = direct ? nullptr : c.take<uint64_t>((size_t)1 << w.table.bits);
   w.local = direct ? c.take<int32_t>((size_t)N * (size_t)B) : nullptr;
-  w.segbuf = direct ? c.take<int32_t>((size_t)B * (size_t)rl_segcap(node_cap)) : nullptr;
-  w.sparse = direct ? c.take<int32_t>((size_t)B * RL_SPARSE_MAX) : nullptr;
   w.small = c.take<int64_t>(ST_SIZE);
   w.ms = MaskScan{};
   w.ms.N = N;
@@ -904,11 +996,11 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
         w.ms.seg_end[b] = (int64_t)(b + 1) * node_cap;
         w.ms.local_base[b] = n_b[b];
       }
-      // Direct relabelling: the last hop's edges find their new neighbours by
-      // search in the hop's segment, so that hop writes no table entries,
-      // unless a segment could outgrow the sparse index (an upper bound is all
-      // that is known before the hop's counts come back).
-      if (direct && k == K) {
+      // The last hop's edges find their new neighbours by search in the hop's
+      // segment, so that hop enters no table, unless a segment could outgrow the
+      // sparse index (an upper bound is all that is known before the hop's counts
+      // come back).
+      if (k == K) {
         int64_t mbound = 0, ebound = 0;
         for (int b = 0; b < B; ++b) {
           const int64_t front = h.fstart[b + 1] - h.fstart[b];
@@ -1026,13 +1118,38 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
     LE.start[b + 1] = LE.start[b] + e_b[b];
     LE.n[b] = n_b[b];
   }
-  if (LE.start[B] > 0 && direct && rl_search) {
+  // The hash table of the nodes listed before hop `hops` (at load <= 1/2).
+  LocalTable table = w.table;
+  auto hash_lists = [&](int hops) -> int {
+    Segs LS;
+    LS.B = B;
+    LS.start[0] = 0;
+    for (int b = 0; b < B; ++b) {
+      LS.start[b + 1] = LS.start[b] + hop_ptr[(int64_t)b * (K + 2) + hops];
+      LS.seg0[b] = 0;
+    }
+    table.bits = lt_bits_for(LS.start[B]);
+    DG_TRY(fill_u64(table.slots, (size_t)1 << table.bits, 0, s));
+    hipLaunchKernelGGL(k_table_insert, dim3(blocks_for(LS.start[B])), dim3(THREADS), 0, s, LS,
+                       nodes, node_cap, table, w.err);
+    DG_HIP(hipGetLastError());
+    return DG_OK;
+  };
+  auto relabel = [&] {  // the edges that LE describes, through the table in use
+    if (direct)
+      hipLaunchKernelGGL(k_relabel_direct, dim3(blocks_for(LE.start[B])), dim3(THREADS), 0, s,
+                         LE, edge_cap, edge_dst, w.local, N, w.err);
+    else
+      hipLaunchKernelGGL(k_relabel, dim3(blocks_for(LE.start[B])), dim3(THREADS), 0, s, LE,
+                         edge_cap, edge_dst, table, N, w.err);
+  };
+  if (LE.start[B] > 0 && rl_search) {
     // edges of the hops before the last through the table, the last hop's by
-    // search in its segment
+    // search in its segment (and the table for nodes listed before the hop)
     LastHop lh;
     memset(&lh, 0, sizeof(lh));
     lh.B = B;
-    int64_t m_max = 0;
+    int64_t m_max = 0, last_edges = 0;
     for (int b = 0; b < B; ++b) {
       const int64_t before = edge_ptr[(int64_t)b * (K + 1) + (K - 1)];
       LE.start[b + 1] = LE.start[b] + before;
@@ -1040,64 +1157,69 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
       lh.m[b] = (int32_t)(n_b[b] - lh.seg0[b]);
       lh.e0[b] = before;
       lh.ecount[b] = (int32_t)(e_b[b] - before);
+      last_edges += lh.ecount[b];
       if (lh.m[b] > m_max) m_max = lh.m[b];
     }
+    const int sparse_cap = rl_sparse_cap(node_cap);
+    int32_t *sparse = reinterpret_cast<int32_t *>(w.f_off);
     lh.s_log2 = RL_S_MIN_LOG2;
-    while (lh.s_log2 < RL_S_MAX_LOG2 && (m_max + (1 << lh.s_log2) - 1) >> lh.s_log2 > RL_SPARSE_MAX)
+    while (lh.s_log2 < RL_S_MAX_LOG2 &&
+           (m_max >> lh.s_log2) + 2 > sparse_cap)  // blocks a segment of m_max can touch
       ++lh.s_log2;
     const int S = 1 << lh.s_log2;
-    const int per_block = RL_THREADS * rl_edges(lh.s_log2) * RL_CHUNKS;
-    lh.cstart[0] = 0;
+    const int per_chunk = RL_THREADS * rl_edges(lh.s_log2);
+    lh.rstart[0] = 0;
     lh.bstart[0] = 0;
-    int64_t r_max = 0;
+    int r_max = 0;
     for (int b = 0; b < B; ++b) {
-      const int64_t r = (lh.m[b] + S - 1) / S;
+      lh.a[b] = (int32_t)(((uintptr_t)nodes / 4 + (uintptr_t)b * (uintptr_t)node_cap +
+                           (uintptr_t)lh.seg0[b]) & (uintptr_t)(S - 1));
+      const int r = lh.m[b] == 0 ? 0 : (int)(((int64_t)lh.m[b] + lh.a[b] + S - 1) / S);
       if (r > r_max) r_max = r;
-      lh.cstart[b + 1] = lh.cstart[b] + r * S;
-      lh.bstart[b + 1] = lh.bstart[b] + (int32_t)((lh.ecount[b] + per_block - 1) / per_block);
+      lh.rstart[b + 1] = lh.rstart[b] + r;
     }
-    if (r_max > RL_SPARSE_MAX)
+    // Several chunks per block share one staging of the index where that is longer
+    // than half a chunk, as long as every CU gets two blocks (one mini-batch of
+    // 130k edges: 44 us with four chunks, i.e. 16 blocks, 16 us with one; 3M edges
+    // of 8 mini-batches, index of 9600 entries: 152 us with two, 129 with four).
+    lh.chunks = 1;
+    while (lh.chunks < RL_CHUNKS && per_chunk * lh.chunks < 2 * r_max &&
+           last_edges >= (int64_t)512 * per_chunk * 2 * lh.chunks)
+      lh.chunks *= 2;
+    const int per_block = per_chunk * lh.chunks;
+    for (int b = 0; b < B; ++b) {
+      lh.bstart[b + 1] = lh.bstart[b] + (int32_t)((lh.ecount[b] + (int64_t)per_block - 1) / per_block);
+    }
+    if (r_max > sparse_cap)
       return set_error(DG_EINVAL, "internal: last-hop segment of %lld nodes", (long long)m_max);
-    if (LE.start[B] > 0) {
-      hipLaunchKernelGGL(k_relabel_direct, dim3(blocks_for(LE.start[B])), dim3(THREADS), 0, s,
-                         LE, edge_cap, edge_dst, w.local, N, w.err);
-    }
-    if (lh.cstart[B] > 0)
-      hipLaunchKernelGGL(k_last_segments, dim3(blocks_for(lh.cstart[B])), dim3(THREADS), 0, s,
-                         lh, nodes, node_cap, w.segbuf, rl_segcap(node_cap), w.sparse);
+    if (!direct && (rc = hash_lists(K))) return rc;
+    if (LE.start[B] > 0) relabel();
+    if (lh.rstart[B] > 0)
+      hipLaunchKernelGGL(k_last_sparse, dim3(blocks_for(lh.rstart[B])), dim3(THREADS), 0, s, lh,
+                         nodes, node_cap, sparse, sparse_cap);
     if (lh.bstart[B] > 0) {
       const unsigned grid = (unsigned)((lh.bstart[B] + 7) & ~7);
       const size_t lds = (size_t)(r_max > 0 ? r_max : 1) * sizeof(int32_t);
+      const OlderNodes older{w.local, table};
       auto go = [&](auto slog2) {
-        hipLaunchKernelGGL((k_relabel_last<decltype(slog2)::value>), dim3(grid),
-                           dim3(RL_THREADS), lds, s, lh, w.segbuf, rl_segcap(node_cap),
-                           w.sparse, edge_cap, edge_dst, w.local, N, w.err);
+        constexpr int SL = decltype(slog2)::value;
+        if (direct)
+          hipLaunchKernelGGL((k_relabel_last<SL, true>), dim3(grid), dim3(RL_THREADS), lds, s, lh,
+                             nodes, node_cap, sparse, sparse_cap, edge_cap, edge_dst, older, N,
+                             w.err);
+        else
+          hipLaunchKernelGGL((k_relabel_last<SL, false>), dim3(grid), dim3(RL_THREADS), lds, s,
+                             lh, nodes, node_cap, sparse, sparse_cap, edge_cap, edge_dst, older,
+                             N, w.err);
       };
       if (lh.s_log2 == 4) go(std::integral_constant<int, 4>());
       else if (lh.s_log2 == 5) go(std::integral_constant<int, 5>());
       else go(std::integral_constant<int, 6>());
     }
     DG_HIP(hipGetLastError());
-  } else if (LE.start[B] > 0 && direct) {
-    hipLaunchKernelGGL(k_relabel_direct, dim3(blocks_for(LE.start[B])), dim3(THREADS), 0, s, LE,
-                       edge_cap, edge_dst, w.local, N, w.err);
-    DG_HIP(hipGetLastError());
   } else if (LE.start[B] > 0) {
-    // the table holds every (node, batch) pair of the group, at load <= 1/2
-    Segs LS;
-    LS.B = B;
-    LS.start[0] = 0;
-    for (int b = 0; b < B; ++b) {
-      LS.start[b + 1] = LS.start[b] + n_b[b];
-      LS.seg0[b] = 0;
-    }
-    LocalTable table = w.table;
-    table.bits = lt_bits_for(LS.start[B]);
-    if ((rc = fill_u64(table.slots, (size_t)1 << table.bits, 0, s))) return rc;
-    hipLaunchKernelGGL(k_table_insert, dim3(blocks_for(LS.start[B])), dim3(THREADS), 0, s, LS,
-                       nodes, node_cap, table, w.err);
-    hipLaunchKernelGGL(k_relabel, dim3(blocks_for(LE.start[B])), dim3(THREADS), 0, s, LE,
-                       edge_cap, edge_dst, table, N, w.err);
+    if (!direct && (rc = hash_lists(K + 1))) return rc;
+    relabel();
     DG_HIP(hipGetLastError());
   }
   mk.r1 = tm.mark();
