@@ -31,16 +31,24 @@ def version() -> str:
 
 
 def _ptr(t: torch.Tensor | None):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _host(a: np.ndarray):
+    """Address of a host array's data."""
+    return a.ctypes.data
 
 
 def _stream(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _need(t: torch.Tensor, name: str, dtype=None, device=None):
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()
+            and (dtype is None or t.dtype is dtype) and (device is None or t.device == device)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name}: expected a torch tensor")
     if dtype is not None and t.dtype != dtype:
@@ -174,8 +182,8 @@ def sample_group(offsets: torch.Tensor, indices: torch.Tensor, seeds: torch.Tens
     sz, tm = Sizes(), Timing()
     st = _L.dg_sample_group(
         ctypes.byref(g), _ptr(seeds), B, S, batch_base, fo, K, rng_seed & (2**64 - 1),
-        flags, node_cap, _ptr(out.nodes), out.hop_ptr.ctypes.data_as(_lib.I64P), edge_cap,
-        _ptr(out.edge_src), _ptr(out.edge_dst), out.edge_ptr.ctypes.data_as(_lib.I64P),
+        flags, node_cap, _ptr(out.nodes), _host(out.hop_ptr), edge_cap,
+        _ptr(out.edge_src), _ptr(out.edge_dst), _host(out.edge_ptr),
         _ptr(membership), _ptr(member_lines), _ptr(cache_slot), _ptr(loc), _ptr(ws),
         ws.numel(), _stream(stream),
         ctypes.byref(sz),
@@ -204,7 +212,8 @@ class PackResult:
 
 
 def _row_bytes(feats: torch.Tensor) -> int:
-    return feats[0].numel() * feats.element_size() if feats.shape[0] else 0
+    n = feats.shape[0]
+    return feats.numel() // n * feats.element_size() if n else 0
 
 
 def pack_group(feats: torch.Tensor, cache_slot: torch.Tensor, nodes: torch.Tensor, node_count,
@@ -273,8 +282,8 @@ def pack_group(feats: torch.Tensor, cache_slot: torch.Tensor, nodes: torch.Tenso
              fill_cache=True):
         fill = fill_cache and cache_nodes is not None
         head = (_ptr(feats), N, R, _ptr(cache_slot), B, _ptr(nodes), stride,
-                counts.ctypes.data_as(_lib.I64P), cap, packed, packed_ids, ptr,
-                ptr_host.ctypes.data_as(_lib.I64P), loc, unique, unique_cap,
+                _host(counts), cap, packed, packed_ids, ptr,
+                _host(ptr_host), loc, unique, unique_cap,
                 _ptr(membership), _ptr(member_lines), _ptr(cache_nodes) if fill else None,
                 n_cache if fill else 0, _ptr(cache_table) if fill else None, flags)
         if no_alloc:
@@ -387,11 +396,11 @@ def sample_pack_group(offsets: torch.Tensor, indices: torch.Tensor, seeds: torch
     def call(po, cap, flags_, sz, tm):
         return _L.dg_sample_pack_group(
             ctypes.byref(g), _ptr(seeds), B, S, batch_base, fo, K, rng_seed & (2**64 - 1),
-            flags_, node_cap, _ptr(out.nodes), out.hop_ptr.ctypes.data_as(_lib.I64P), edge_cap,
-            _ptr(out.edge_src), _ptr(out.edge_dst), out.edge_ptr.ctypes.data_as(_lib.I64P),
+            flags_, node_cap, _ptr(out.nodes), _host(out.hop_ptr), edge_cap,
+            _ptr(out.edge_src), _ptr(out.edge_dst), _host(out.edge_ptr),
             _ptr(membership), _ptr(cache_slot), _ptr(po.loc), _ptr(feats), R, cap,
             _ptr(po.packed) if cap > 0 else None, _ptr(po.packed_ids) if cap > 0 else None,
-            _ptr(po.packed_ptr), po.packed_ptr_host.ctypes.data_as(_lib.I64P),
+            _ptr(po.packed_ptr), _host(po.packed_ptr_host),
             _ptr(po.unique), po.unique.numel() if po.unique is not None else 0,
             _lib.DG_PACK_ROWS_STREAM if (rows_stream is not None and cap > 0) else 0,
             _ptr(ws), ws.numel(), _ptr(pws), pws.numel(), _stream(stream),
@@ -493,8 +502,8 @@ def assemble_batches(cache: torch.Tensor | None, pr: PackResult, node_count, out
     ptr = np.ascontiguousarray(pr.packed_ptr_host, dtype=np.int64)
     optr = (ctypes.c_void_p * len(outs))(*[o.data_ptr() for o in outs])
     check(_L.dg_assemble_batches(_ptr(cache) if cache_rows else None, cache_rows, _ptr(packed),
-                                 ptr.ctypes.data_as(_lib.I64P), _ptr(pr.loc), pr.loc.shape[1],
-                                 counts.ctypes.data_as(_lib.I64P), B, R, optr, len(outs),
+                                 _host(ptr), _ptr(pr.loc), pr.loc.shape[1],
+                                 _host(counts), B, R, optr, len(outs),
                                  _ptr(status), _stream(stream)))
 
 

@@ -43,7 +43,10 @@ class Sizes(ctypes.Structure):
                 ("unique_packed", I64), ("exact", I32)]
 
     def as_dict(self):
-        return {k: getattr(self, k) for k, _ in self._fields_}
+        return {"max_batch_nodes": self.max_batch_nodes, "max_batch_edges": self.max_batch_edges,
+                "total_nodes": self.total_nodes, "total_edges": self.total_edges,
+                "packed_rows": self.packed_rows, "unique_nodes": self.unique_nodes,
+                "unique_packed": self.unique_packed, "exact": self.exact}
 
 
 class Timing(ctypes.Structure):
@@ -64,28 +67,28 @@ SIGNATURES = {
     "dg_sample_workspace_bytes": (SZ, [I64, I32, I64, I64, U32]),
     "dg_member_lines_bytes": (SZ, [I64]),
     "dg_sample_group": (ctypes.c_int, [ctypes.POINTER(Csr), VP, I32, I32, I64, I32P, I32, U64,
-                                       ctypes.c_uint32, I64, VP, I64P, I64, VP, VP, I64P, VP,
+                                       ctypes.c_uint32, I64, VP, VP, I64, VP, VP, VP, VP,
                                        VP, VP, VP, VP, SZ, VP,
                                        ctypes.POINTER(Sizes), ctypes.POINTER(Timing)]),
     "dg_pack_workspace_bytes": (SZ, [I64, I32, I64]),
-    "dg_pack_group": (ctypes.c_int, [VP, I64, I64, VP, I32, VP, I64, I64P, I64, VP, VP, VP, I64P,
+    "dg_pack_group": (ctypes.c_int, [VP, I64, I64, VP, I32, VP, I64, VP, I64, VP, VP, VP, VP,
                                      VP, VP, I64, VP, VP, VP, I64, VP, U32, VP, SZ, VP, VP,
                                      ctypes.POINTER(Sizes), ctypes.POINTER(Timing)]),
     "dg_sample_pack_workspace_bytes": (SZ, [I64, I32, I64]),
     "dg_sample_pack_group": (ctypes.c_int, [ctypes.POINTER(Csr), VP, I32, I32, I64, I32P, I32,
-                                            U64, ctypes.c_uint32, I64, VP, I64P, I64, VP, VP,
-                                            I64P, VP, VP, VP, VP, I64, I64, VP, VP, VP, I64P,
+                                            U64, ctypes.c_uint32, I64, VP, VP, I64, VP, VP,
+                                            VP, VP, VP, VP, VP, I64, I64, VP, VP, VP, VP,
                                             VP, I64, U32, VP, SZ, VP, SZ, VP, VP,
                                             ctypes.POINTER(Sizes), ctypes.POINTER(Timing)]),
     "dg_pack_noalloc_scratch_bytes": (SZ, []),
-    "dg_pack_group_noalloc": (ctypes.c_int, [VP, I64, I64, VP, I32, VP, I64, I64P, I64, VP, VP,
-                                             VP, I64P, VP, VP, I64, VP, VP, VP, I64, VP, U32,
+    "dg_pack_group_noalloc": (ctypes.c_int, [VP, I64, I64, VP, I32, VP, I64, VP, I64, VP, VP,
+                                             VP, VP, VP, VP, I64, VP, VP, VP, I64, VP, U32,
                                              VP, ctypes.POINTER(Sizes)]),
     "dg_assemble_batch": (ctypes.c_int, [VP, I64, VP, I64, VP, I64, I64, VP, VP, VP]),
-    "dg_assemble_batches": (ctypes.c_int, [VP, I64, VP, I64P, VP, I64, I64P, I32, I64,
+    "dg_assemble_batches": (ctypes.c_int, [VP, I64, VP, VP, VP, I64, VP, I32, I64,
                                            ctypes.POINTER(VP), I32, VP, VP]),
     "dg_cache_workspace_bytes": (SZ, [I64]),
-    "dg_cache_by_frequency": (ctypes.c_int, [VP, I64, I32, I64, VP, VP, I64P, VP, SZ, VP]),
+    "dg_cache_by_frequency": (ctypes.c_int, [VP, I64, I32, I64, VP, VP, VP, VP, SZ, VP]),
     "dg_gather_rows": (ctypes.c_int, [VP, I64, I64, VP, I64, VP, VP, VP]),
     "dg_minhash_workspace_bytes": (SZ, [I64]),
     "dg_minhash_order": (ctypes.c_int, [VP, I64, I32, VP, I64, VP, I32, VP, VP, VP, SZ, VP]),
