@@ -357,72 +357,17 @@ int pack_impl(const void *feats, int64_t N, int64_t row_bytes, const int32_t *ca
   return DG_OK;
 }
 
-namespace {
-
-struct LocFill {
-  int B;
-  int64_t node_cap;
-  int64_t start[DG_MAX_BATCHES + 1];  // packed_ptr
-  int64_t n[DG_MAX_BATCHES];          // list lengths
-};
-
-// P_b and the address-table entries of the packed pairs after a fused
-// compaction: packed row i of chunk b holds node u (low half of pinfo[i]),
-// which is entry j of nodes_b, with j the list slot in the high half for a
-// pair new at the last hop, else u's local index in the direct table;
-// packed_ids[i] = u and loc_b[j] = i - packed_ptr[b], u's rank in P_b.  Every
-// non-cached list entry is reached once this way (its pair is in P_b).
-__global__ __launch_bounds__(THREADS) void k_loc_packed(LocFill F, const uint64_t *pinfo,
-                                                        const int32_t *local,
-                                                        int32_t *packed_ids, int32_t *loc,
-                                                        uint32_t *err) {
-  const int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x;
-  if (i >= F.start[F.B]) return;
-  const int b = find_batch_wave(F.start, F.B, i);
-  const uint64_t e = pinfo[i];
-  const int32_t u = (int32_t)(uint32_t)e;
-  int32_t j = (int32_t)(e >> 32);
-  packed_ids[i] = u;
-  if (j < 0) j = local[(int64_t)u * F.B + b];
-  if (j < 0 || (int64_t)j >= F.n[b]) {
-    atomicOr(err, ERR_INTERNAL);
-    return;
-  }
-  loc[(int64_t)b * F.node_cap + j] = (int32_t)(i - F.start[b]);
-}
-
-}  // namespace
-
-int pack_fused_tail(const FusedTail &t, bool rows_async, hipStream_t s, hipStream_t rows_stream,
-                    PhaseTimer *tm, int *ev_loc, int *ev_gather) {
-  // The row copy depends only on the write pass's U_nc lists: on a second
-  // stream it starts at once, beside the address tables.
+int pack_fused_rows(const FusedRows &t, bool rows_async, hipStream_t s, hipStream_t rows_stream) {
+  if (!t.packed || t.n_unc == 0) return DG_OK;
   const RowCopy rc_rows{t.feats,   t.N,       t.row_bytes, t.unc_ids, t.unc_off,
                         t.n_unc,   t.rows,    t.pairdest,  t.packed,  nullptr,
                         0,         nullptr,   t.err};
-  const bool copy = t.packed && t.n_unc > 0;
-  int rc;
-  if (copy && rows_async) {
-    SideStream *ss = nullptr;
-    DG_TRY(side_stream(&ss));
-    DG_HIP(hipEventRecord(ss->handoff, s));
-    DG_HIP(hipStreamWaitEvent(rows_stream, ss->handoff, 0));
-    if ((rc = launch_fanout(rc_rows, rows_stream))) return rc;
-  }
-  if (t.rows > 0) {
-    LocFill F;
-    F.B = t.B;
-    F.node_cap = t.node_cap;
-    for (int b = 0; b <= t.B; ++b) F.start[b] = t.packed_ptr_host[b];
-    for (int b = 0; b < t.B; ++b) F.n[b] = t.n_b[b];
-    hipLaunchKernelGGL(k_loc_packed, dim3(blocks_for(t.rows)), dim3(THREADS), 0, s, F,
-                       t.pinfo, t.local, t.packed_ids, t.loc, t.err);
-    DG_HIP(hipGetLastError());
-  }
-  *ev_loc = tm ? tm->mark() : -1;
-  if (copy && !rows_async && (rc = launch_fanout(rc_rows, s))) return rc;
-  *ev_gather = tm ? tm->mark() : -1;
-  return DG_OK;
+  if (!rows_async) return launch_fanout(rc_rows, s);
+  SideStream *ss = nullptr;
+  DG_TRY(side_stream(&ss));
+  DG_HIP(hipEventRecord(ss->handoff, s));
+  DG_HIP(hipStreamWaitEvent(rows_stream, ss->handoff, 0));
+  return launch_fanout(rc_rows, rows_stream);
 }
 
 }  // namespace dg

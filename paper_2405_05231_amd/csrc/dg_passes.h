@@ -195,29 +195,17 @@ int pack_impl(const void *feats, int64_t N, int64_t row_bytes, const int32_t *ca
               int64_t cache_rows, void *cache_table, uint32_t flags, void *ws,
               size_t ws_bytes, hipStream_t stream, hipStream_t rows_stream, dg_sizes *sizes,
               dg_timing *timing, bool no_alloc);
-// What follows a fused compaction: P_b (packed_ids) and the address-table
-// entries of the packed pairs, loc[b*node_cap + j] = r for packed row
-// packed_ptr[b] + r, with j the list slot in the row's pinfo for a pair new at
-// the last hop, else local[u*B + b]; then the row copy (on rows_stream, not
-// waited for, when rows_async).
-struct FusedTail {
+// The row copy after a fused compaction (on rows_stream, not waited for, when
+// rows_async): it depends on the write pass's U_nc lists alone.
+struct FusedRows {
   const void *feats;
   int64_t N, row_bytes;
-  int B;
-  int64_t node_cap;
-  const int64_t *n_b;              // [host] list lengths
-  const int64_t *packed_ptr_host;  // [host] B+1
-  const uint64_t *pinfo;
-  const int32_t *local;
-  int32_t *packed_ids;
-  int32_t *loc;
   void *packed;  // nullable: no row copy
   const int32_t *unc_ids;
   const int64_t *unc_off, *pairdest;
   int64_t n_unc, rows;
   uint32_t *err;
 };
-int pack_fused_tail(const FusedTail &t, bool rows_async, hipStream_t s, hipStream_t rows_stream,
-                    PhaseTimer *tm, int *ev_loc, int *ev_gather);
+int pack_fused_rows(const FusedRows &t, bool rows_async, hipStream_t s, hipStream_t rows_stream);
 
 }  // namespace dg

@@ -63,14 +63,6 @@ __device__ __forceinline__ int tile_batch(const Hop &h, int32_t t) {
   return lo;
 }
 
-// Flattened (batch, position) ranges, for passes over all edge lists, with
-// each batch's node count.
-struct Lists {
-  int B;
-  int64_t start[DG_MAX_BATCHES + 1];
-  int64_t n[DG_MAX_BATCHES];
-};
-
 // What the seeds need before the first hop.
 struct SeedInit {
   const int32_t *seeds;
@@ -378,44 +370,6 @@ __global__ __launch_bounds__(THREADS) void k_table_insert(Segs L, const int32_t 
   if (!lt_insert(table, nodes[(int64_t)b * node_cap + j], b, j)) atomicOr(err, ERR_INTERNAL);
 }
 
-// Sampled neighbours' global IDs -> local indices through the group's
-// (node, batch) hash table.
-__global__ __launch_bounds__(THREADS) void k_relabel(Lists L, int64_t edge_cap, int32_t *edge_dst,
-                                                     LocalTable table, int64_t N, uint32_t *err) {
-  int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x;
-  if (i >= L.start[L.B]) return;
-  int b = find_batch_wave(L.start, L.B, i);
-  int64_t e = (int64_t)b * edge_cap + (i - L.start[b]);
-  int32_t u = edge_dst[e];
-  if (u < 0 || (int64_t)u >= N) return;  // already reported
-  int64_t j = lt_find(table, u, b);
-  if (j < 0) {
-    atomicOr(err, ERR_INTERNAL);
-    return;
-  }
-  edge_dst[e] = (int32_t)j;
-}
-
-// The same through the direct [N][B] table.  Every looked-up pair was written
-// when its node entered the batch; the range check guards that invariant.
-__global__ __launch_bounds__(THREADS) void k_relabel_direct(Lists L, int64_t edge_cap,
-                                                            int32_t *edge_dst,
-                                                            const int32_t *local, int64_t N,
-                                                            uint32_t *err) {
-  int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x;
-  if (i >= L.start[L.B]) return;
-  int b = find_batch_wave(L.start, L.B, i);
-  int64_t e = (int64_t)b * edge_cap + (i - L.start[b]);
-  int32_t u = edge_dst[e];
-  if (u < 0 || (int64_t)u >= N) return;  // already reported
-  int32_t j = local[(int64_t)u * L.B + b];
-  if (j < 0 || (int64_t)j >= L.n[b]) {
-    atomicOr(err, ERR_INTERNAL);
-    return;
-  }
-  edge_dst[e] = j;
-}
-
 // ---------------------------------------------------------------- last-hop relabelling by search
 // The last hop's new nodes form one ascending segment at the end of each
 // batch's list, so a last-hop edge whose neighbour is one of them gets its
@@ -462,22 +416,6 @@ struct LastHop {
   int32_t rstart[DG_MAX_BATCHES + 1];   // sparse-index entries before batch b
 };
 
-// The first element of every block of each batch's last-hop segment.
-__global__ __launch_bounds__(THREADS) void k_last_sparse(LastHop h, const int32_t *nodes,
-                                                         int64_t node_cap, int32_t *sparse,
-                                                         int sparse_cap) {
-  const int32_t i = (int32_t)(blockIdx.x * THREADS + threadIdx.x);
-  if (i >= h.rstart[h.B]) return;
-  int b = 0, top = h.B;  // invariant rstart[b] <= i < rstart[top]
-  while (top - b > 1) {
-    const int mid = (b + top) >> 1;
-    if (h.rstart[mid] <= i) b = mid; else top = mid;
-  }
-  const int32_t r = i - h.rstart[b];
-  const int32_t at = max((r << h.s_log2) - h.a[b], 0);
-  sparse[(int64_t)b * sparse_cap + r] = nodes[(int64_t)b * node_cap + h.seg0[b] + at];
-}
-
 // A node listed before the last hop: its local index by the direct table or by
 // the hash table (< 0: absent).
 struct OlderNodes {
@@ -487,6 +425,92 @@ struct OlderNodes {
 template <bool DIRECT>
 __device__ __forceinline__ int64_t older_index(const OlderNodes &o, int32_t u, int b, int B) {
   return DIRECT ? (int64_t)o.local[(int64_t)u * B + b] : lt_find(o.table, u, b);
+}
+
+// What the relabelling does beside the last hop's search: three independent
+// parts of one launch, each a run of its blocks.  As three launches the whole step
+// took 135.5 us against 131 (10,000 nodes), 213 against 208 (one mini-batch at 1M
+// nodes) and 1092 against 1084 (32 of them).
+struct TailEdges {  // edges whose neighbours the table knows: of b, the first n[b]
+  int B;
+  unsigned blocks;
+  int64_t start[DG_MAX_BATCHES + 1];  // prefix of the edges
+  int64_t limit[DG_MAX_BATCHES];      // local indices lie below (0: not checked)
+};
+struct TailSparse {  // the index of the last-hop segments
+  unsigned blocks;
+  int s_log2, cap;
+  int32_t rstart[DG_MAX_BATCHES + 1];
+  int32_t a[DG_MAX_BATCHES];
+  int64_t seg0[DG_MAX_BATCHES];
+  int32_t *sparse;
+};
+struct TailLoc {  // P_b and the address tables of the packed pairs
+  unsigned blocks;
+  int64_t start[DG_MAX_BATCHES + 1];  // packed_ptr
+  const uint64_t *pinfo;
+  int32_t *packed_ids, *loc;
+};
+
+// Edges: sampled neighbours' global IDs -> local indices through the direct [N][B]
+// table or the group's (node, batch) hash table.  Every looked-up pair was
+// entered when its node entered the batch; the range check guards that.
+// Sparse index: the first element of every block of each batch's last-hop segment.
+// Packed pairs, after a fused compaction: packed row i of chunk b holds node u (low
+// half of pinfo[i]), which is entry j of nodes_b, with j the list slot in the high
+// half for a pair new at the last hop, else u's local index in the direct table;
+// packed_ids[i] = u and loc_b[j] = i - packed_ptr[b], u's rank in P_b.  Every
+// non-cached list entry is reached once this way (its pair is in P_b).
+template <bool DIRECT>
+__global__ __launch_bounds__(THREADS) void k_relabel_tail(TailEdges te, TailSparse ts, TailLoc tl,
+                                                          const int32_t *nodes, int64_t node_cap,
+                                                          int64_t edge_cap, int32_t *edge_dst,
+                                                          OlderNodes older, int64_t N,
+                                                          uint32_t *err) {
+  unsigned blk = blockIdx.x;
+  if (blk < te.blocks) {
+    const int64_t i = (int64_t)blk * THREADS + threadIdx.x;
+    if (i >= te.start[te.B]) return;
+    const int b = find_batch_wave(te.start, te.B, i);
+    const int64_t e = (int64_t)b * edge_cap + (i - te.start[b]);
+    const int32_t u = edge_dst[e];
+    if (u < 0 || (int64_t)u >= N) return;  // already reported
+    const int64_t j = older_index<DIRECT>(older, u, b, te.B);
+    if (j < 0 || j >= te.limit[b]) {
+      atomicOr(err, ERR_INTERNAL);
+      return;
+    }
+    edge_dst[e] = (int32_t)j;
+    return;
+  }
+  blk -= te.blocks;
+  if (blk < ts.blocks) {
+    const int32_t i = (int32_t)(blk * THREADS + threadIdx.x);
+    if (i >= ts.rstart[te.B]) return;
+    int b = 0, top = te.B;  // invariant rstart[b] <= i < rstart[top]
+    while (top - b > 1) {
+      const int mid = (b + top) >> 1;
+      if (ts.rstart[mid] <= i) b = mid; else top = mid;
+    }
+    const int32_t r = i - ts.rstart[b];
+    const int32_t at = max((r << ts.s_log2) - ts.a[b], 0);
+    ts.sparse[(int64_t)b * ts.cap + r] = nodes[(int64_t)b * node_cap + ts.seg0[b] + at];
+    return;
+  }
+  blk -= ts.blocks;
+  const int64_t i = (int64_t)blk * THREADS + threadIdx.x;
+  if (i >= tl.start[te.B]) return;
+  const int b = find_batch_wave(tl.start, te.B, i);
+  const uint64_t x = tl.pinfo[i];
+  const int32_t u = (int32_t)(uint32_t)x;
+  int64_t j = (int32_t)(x >> 32);
+  tl.packed_ids[i] = u;
+  if (j < 0) j = older_index<DIRECT>(older, u, b, te.B);
+  if (j < 0 || j >= te.limit[b]) {
+    atomicOr(err, ERR_INTERNAL);
+    return;
+  }
+  tl.loc[(int64_t)b * node_cap + j] = (int32_t)(i - tl.start[b]);
 }
 
 typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -775,9 +799,12 @@ struct PackInto {
   int64_t unc_cap, pair_cap;
   int64_t *packed_ptr;
   int64_t packed_cap;
+  int32_t *packed_ids;
   int32_t *group_unique;
   int64_t unique_cap;
   // set by sample_impl
+  bool fits = false;                  // the totals match and fit the outputs
+  bool loc_done = false;              // P_b and the address tables are queued
   bool fused = false;                 // the last hop's compaction did packing's pass
   int64_t ptot[DG_MAX_BATCHES + 4];  // packing's row totals (fused)
   uint32_t *err = nullptr;            // sampling's device error word, not yet checked
@@ -1108,6 +1135,12 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
       if (fuse) {
         pk->fused = true;
         for (int r = 0; r < mc_rows(B); ++r) pk->ptot[r] = st[ST_PTOTALS + r];
+        // the caller reports what does not fit or match
+        pk->fits = pk->ptot[row_pairs(B)] <= pk->packed_cap &&
+                   (!pk->group_unique || pk->ptot[row_all(B)] <= pk->unique_cap);
+        int64_t rows = 0;
+        for (int b = 0; b < B; ++b) rows += pk->ptot[b];
+        pk->fits = pk->fits && rows == pk->ptot[row_pairs(B)];
       }
       if (mk.nhop < 8) {
         mk.hop[mk.nhop][0] = ev0;
@@ -1137,13 +1170,18 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
 
   // Local IDs through the (node, batch) table.
   mk.r0 = tm.mark();
-  Lists LE;
-  LE.B = B;
-  LE.start[0] = 0;
+  TailEdges te;
+  TailSparse ts;
+  TailLoc tl;
+  memset(&te, 0, sizeof(te));
+  memset(&ts, 0, sizeof(ts));
+  memset(&tl, 0, sizeof(tl));
+  te.B = B;
   for (int b = 0; b < B; ++b) {
-    LE.start[b + 1] = LE.start[b] + e_b[b];
-    LE.n[b] = n_b[b];
+    te.start[b + 1] = te.start[b] + e_b[b];
+    te.limit[b] = n_b[b];
   }
+  const bool any_edges = te.start[B] > 0;
   // The hash table of the nodes listed before hop `hops` (at load <= 1/2).
   LocalTable table = w.table;
   auto hash_lists = [&](int hops) -> int {
@@ -1161,15 +1199,27 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
     DG_HIP(hipGetLastError());
     return DG_OK;
   };
-  auto relabel = [&] {  // the edges that LE describes, through the table in use
+  // The fused pass's packed pairs go with the relabelling, unless phases are timed.
+  if (pk && pk->fused && pk->fits && !tm.on) {
+    for (int b = 0; b < B; ++b) tl.start[b + 1] = tl.start[b] + pk->ptot[b];
+    tl.blocks = blocks_for(tl.start[B]);
+    tl.pinfo = pk->pinfo;
+    tl.packed_ids = pk->packed_ids;
+    tl.loc = loc;
+    pk->loc_done = true;
+  }
+  auto launch_tail = [&] {
+    const OlderNodes older{w.local, table};
+    const unsigned grid = te.blocks + ts.blocks + tl.blocks;
+    if (grid == 0) return;
     if (direct)
-      hipLaunchKernelGGL(k_relabel_direct, dim3(blocks_for(LE.start[B])), dim3(THREADS), 0, s,
-                         LE, edge_cap, edge_dst, w.local, N, w.err);
+      hipLaunchKernelGGL(k_relabel_tail<true>, dim3(grid), dim3(THREADS), 0, s, te, ts, tl, nodes,
+                         node_cap, edge_cap, edge_dst, older, N, w.err);
     else
-      hipLaunchKernelGGL(k_relabel, dim3(blocks_for(LE.start[B])), dim3(THREADS), 0, s, LE,
-                         edge_cap, edge_dst, table, N, w.err);
+      hipLaunchKernelGGL(k_relabel_tail<false>, dim3(grid), dim3(THREADS), 0, s, te, ts, tl, nodes,
+                         node_cap, edge_cap, edge_dst, older, N, w.err);
   };
-  if (LE.start[B] > 0 && rl_search) {
+  if (any_edges && rl_search) {
     // edges of the hops before the last through the table, the last hop's by
     // search in its segment (and the table for nodes listed before the hop)
     LastHop lh;
@@ -1178,7 +1228,7 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
     int64_t m_max = 0, last_edges = 0;
     for (int b = 0; b < B; ++b) {
       const int64_t before = edge_ptr[(int64_t)b * (K + 1) + (K - 1)];
-      LE.start[b + 1] = LE.start[b] + before;
+      te.start[b + 1] = te.start[b] + before;
       lh.seg0[b] = hop_ptr[(int64_t)b * (K + 2) + K];
       lh.m[b] = (int32_t)(n_b[b] - lh.seg0[b]);
       lh.e0[b] = before;
@@ -1219,10 +1269,15 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
     if (r_max > sparse_cap)
       return set_error(DG_EINVAL, "internal: last-hop segment of %lld nodes", (long long)m_max);
     if (!direct && (rc = hash_lists(K))) return rc;
-    if (LE.start[B] > 0) relabel();
-    if (lh.rstart[B] > 0)
-      hipLaunchKernelGGL(k_last_sparse, dim3(blocks_for(lh.rstart[B])), dim3(THREADS), 0, s, lh,
-                         nodes, node_cap, sparse, sparse_cap);
+    te.blocks = blocks_for(te.start[B]);
+    ts.blocks = blocks_for(lh.rstart[B]);
+    ts.s_log2 = lh.s_log2;
+    ts.cap = sparse_cap;
+    ts.sparse = sparse;
+    memcpy(ts.rstart, lh.rstart, sizeof(ts.rstart));
+    memcpy(ts.a, lh.a, sizeof(ts.a));
+    memcpy(ts.seg0, lh.seg0, sizeof(ts.seg0));
+    launch_tail();
     if (lh.bstart[B] > 0) {
       const unsigned grid = (unsigned)((lh.bstart[B] + 7) & ~7);
       const size_t lds = (size_t)(r_max > 0 ? r_max : 1) * sizeof(int32_t);
@@ -1243,9 +1298,13 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
       else go(std::integral_constant<int, 6>());
     }
     DG_HIP(hipGetLastError());
-  } else if (LE.start[B] > 0) {
+  } else if (any_edges) {
     if (!direct && (rc = hash_lists(K + 1))) return rc;
-    relabel();
+    te.blocks = blocks_for(te.start[B]);
+    launch_tail();
+    DG_HIP(hipGetLastError());
+  } else if (tl.blocks > 0) {
+    launch_tail();
     DG_HIP(hipGetLastError());
   }
   mk.r1 = tm.mark();
@@ -1265,17 +1324,17 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
     return rc;
   }
 
-  int64_t tn = 0, te = 0, mn = 0, me = 0;
+  int64_t sum_n = 0, sum_e = 0, mn = 0, me = 0;
   for (int b = 0; b < B; ++b) {
-    tn += n_b[b];
-    te += e_b[b];
+    sum_n += n_b[b];
+    sum_e += e_b[b];
     if (n_b[b] > mn) mn = n_b[b];
     if (e_b[b] > me) me = e_b[b];
   }
   sizes->max_batch_nodes = mn;
   sizes->max_batch_edges = me;
-  sizes->total_nodes = tn;
-  sizes->total_edges = te;
+  sizes->total_nodes = sum_n;
+  sizes->total_edges = sum_e;
   return DG_OK;
 }
 
@@ -1367,6 +1426,7 @@ extern "C" int dg_sample_pack_group(
   const int64_t N = g->num_nodes;
   pk.packed_ptr = packed_ptr;
   pk.packed_cap = packed_cap;
+  pk.packed_ids = packed_ids;
   pk.group_unique = group_unique;
   pk.unique_cap = group_unique ? unique_cap : 0;
   if (timing) memset(timing, 0, sizeof(*timing));
@@ -1423,28 +1483,31 @@ extern "C" int dg_sample_pack_group(
     return set_error(DG_ECAPACITY,
                      "dg_sample_pack_group: need packed_cap >= %lld and unique_cap >= %lld",
                      (long long)rows, (long long)sizes->unique_nodes);
-  FusedTail t;
-  t.feats = feats;
-  t.N = N;
-  t.row_bytes = row_bytes;
-  t.B = B;
-  t.node_cap = node_cap;
-  t.n_b = n_b;
-  t.packed_ptr_host = packed_ptr_host;
-  t.packed_ids = packed_ids;
-  t.pinfo = pk.pinfo;
-  t.local = pk.local;
-  t.loc = loc;
-  t.packed = packed;
-  t.unc_ids = pk.pw.unc_ids;
-  t.unc_off = pk.pw.unc_off;
-  t.pairdest = pk.pw.pairdest;
-  t.n_unc = sizes->unique_packed;
-  t.rows = rows;
-  t.err = pk.err;
-  int ev_loc = -1, ev_gather = -1;
-  if ((rc = pack_fused_tail(t, rows_async, stream, rows_stream, &tm, &ev_loc, &ev_gather)))
-    return rc;
+  const FusedRows t{feats,  N,      row_bytes,       packed, pk.pw.unc_ids, pk.pw.unc_off,
+                    pk.pw.pairdest, sizes->unique_packed, rows,   pk.err};
+  // On a second stream the row copy starts at once, beside what is left here.
+  if (rows_async && (rc = pack_fused_rows(t, true, stream, rows_stream))) return rc;
+  if (!pk.loc_done && rows > 0) {  // phases are timed: the address tables by themselves
+    TailEdges te;
+    TailSparse ts;
+    TailLoc tl;
+    memset(&te, 0, sizeof(te));
+    memset(&ts, 0, sizeof(ts));
+    te.B = B;
+    for (int b = 0; b < B; ++b) te.limit[b] = n_b[b];
+    for (int b = 0; b <= B; ++b) tl.start[b] = packed_ptr_host[b];
+    tl.blocks = blocks_for(rows);
+    tl.pinfo = pk.pinfo;
+    tl.packed_ids = packed_ids;
+    tl.loc = loc;
+    hipLaunchKernelGGL(k_relabel_tail<true>, dim3(tl.blocks), dim3(THREADS), 0, stream, te, ts, tl,
+                       nodes, node_cap, edge_cap, edge_dst, OlderNodes{pk.local, LocalTable{}}, N,
+                       pk.err);
+    DG_HIP(hipGetLastError());
+  }
+  const int ev_loc = tm.mark();
+  if (!rows_async && (rc = pack_fused_rows(t, false, stream, nullptr))) return rc;
+  const int ev_gather = tm.mark();
   if ((rc = check_err(pk.err, stream))) return rc;
   if (timing) {
     sample_times(tm, mk, timing);
