@@ -4,7 +4,8 @@
 // Device state: a node-major membership mask visited[u] (bit b = u is in
 // mini-batch b) and its copy prev[u] as of the start of the current hop.  A
 // hop is:
-//   degree pass over the frontier -> exclusive scan (edge slots) ->
+//   frontier pass (the seeds enter with the first one): degrees, and edge slots
+//     by an exclusive scan within tiles of one batch ->
 //   draw + mark: 1-8 lanes per frontier node, a fire-and-forget atomicOr on
 //     visited per sampled edge; a hop that can reach only a small share of the
 //     nodes also marks the 8-node lines of the mask it touches ->
@@ -16,7 +17,8 @@
 // Sampled neighbours are relabelled from global to local IDs at the end,
 // through one of two tables: a direct [N][B] array of local indices that the
 // compaction fills as it assigns them (DG_SAMPLE_DIRECT), or a (node, batch)
-// hash table sized for the group and filled after the last hop.
+// hash table sized for the group and filled after the last hop.  The last
+// hop's own new nodes are found by search in their ascending segment instead.
 #include <string.h>
 
 #include <type_traits>
