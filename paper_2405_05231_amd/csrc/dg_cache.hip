@@ -52,8 +52,10 @@ struct KeySort {
   int64_t N;          // nodes
   int64_t n;          // list length
   int64_t ncol;       // waves
-  uint32_t *cnt;      // [KEYS + 1][ncol] counts, then exclusive scans along each key's
-                      // row; the last row holds each wave's error bits (MINHASH)
+  bool wide;          // ranks of more than 31 bits
+  void *cnt;          // [KEYS + 1][ncol] counts, then exclusive scans along each key's
+                      // row, 4 bytes each, or 8 if wide; the last row holds each
+                      // wave's error bits (MINHASH)
   int64_t *totals;    // [KEYS + 1]: per key; the error bits
   uint8_t *keys;      // [n] each element's key; NULL: the place pass finds it again
   // FREQ outputs
@@ -162,7 +164,8 @@ __device__ __forceinline__ uint64_t same_key(int key, uint64_t act) {
   return m;
 }
 
-template <int MODE, int R>
+// P: unsigned integer that holds a rank (uint64_t if wide).
+template <int MODE, int R, typename P>
 __global__ __launch_bounds__(CF_THREADS) void k_key_count(KeySort a) {
   constexpr int U = R < CF_FLIGHT ? R : CF_FLIGHT;
   __shared__ uint32_t s_cnt[CF_WAVES][KEYS + 3];
@@ -196,12 +199,13 @@ __global__ __launch_bounds__(CF_THREADS) void k_key_count(KeySort a) {
   }
   __builtin_amdgcn_wave_barrier();
   if (col < a.ncol) {
-    a.cnt[(int64_t)lane * a.ncol + col] = cnt[lane];
-    if (lane == 0) a.cnt[64 * a.ncol + col] = cnt[64];
+    P *out = static_cast<P *>(a.cnt);
+    out[(int64_t)lane * a.ncol + col] = cnt[lane];
+    if (lane == 0) out[64 * a.ncol + col] = cnt[64];
     if (MODE == MINHASH) {
       const uint32_t node = __ballot((bad & ERR_NODE_RANGE) != 0) ? (uint32_t)ERR_NODE_RANGE : 0u;
       const uint32_t row = __ballot((bad & ERR_ROW_RANGE) != 0) ? (uint32_t)ERR_ROW_RANGE : 0u;
-      if (lane == 0) a.cnt[65 * a.ncol + col] = node | row;
+      if (lane == 0) out[65 * a.ncol + col] = node | row;
     }
   }
 }
@@ -209,17 +213,18 @@ __global__ __launch_bounds__(CF_THREADS) void k_key_count(KeySort a) {
 // One block per row: exclusive scan in place of a key's counts, or (row KEYS) the
 // OR of the error bits.
 constexpr int KS_ITEMS = 8;
+template <typename P>
 __global__ __launch_bounds__(1024) void k_key_scan(KeySort a) {
   __shared__ uint32_t s_w[KS_ITEMS][16];
   const int row = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t *p = a.cnt + (int64_t)row * a.ncol;
-  uint32_t carry = 0;
+  P *p = static_cast<P *>(a.cnt) + (int64_t)row * a.ncol;
+  P carry = 0;
   for (int64_t c0 = 0; c0 < a.ncol; c0 += 1024 * KS_ITEMS) {
-    uint32_t v[KS_ITEMS], incl[KS_ITEMS];
+    uint32_t v[KS_ITEMS], incl[KS_ITEMS];  // a chunk's sum fits 32 bits
 #pragma unroll
     for (int q = 0; q < KS_ITEMS; ++q) {
       const int64_t i = c0 + q * 1024 + threadIdx.x;
-      v[q] = i < a.ncol ? p[i] : 0u;
+      v[q] = i < a.ncol ? (uint32_t)p[i] : 0u;
     }
     if (row == KEYS) {
 #pragma unroll
@@ -255,10 +260,10 @@ __global__ __launch_bounds__(1024) void k_key_scan(KeySort a) {
   if (threadIdx.x == 0) a.totals[row] = (int64_t)carry;
 }
 
-template <int MODE, int R>
+template <int MODE, int R, typename P>
 __global__ __launch_bounds__(CF_THREADS) void k_key_place(KeySort a) {
   constexpr int U = R < CF_FLIGHT ? R : CF_FLIGHT;
-  __shared__ uint32_t s_run[CF_WAVES][KEYS + 3];  // next rank of each key
+  __shared__ P s_run[CF_WAVES][KEYS + 3];  // next rank of each key
   __shared__ LowTable s_low[1];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t bad = 0;
@@ -266,14 +271,16 @@ __global__ __launch_bounds__(CF_THREADS) void k_key_place(KeySort a) {
   const int64_t col = (int64_t)blockIdx.x * CF_WAVES + w;
   const int64_t at = col < a.ncol ? col : a.ncol - 1;
   // rank of the first element of each key (lane k: key k), and key 64's
-  const int32_t tot = (int32_t)a.totals[lane], tot64 = (int32_t)a.totals[64];
-  const int32_t incl = wave_incl_sum_i32(tot);
-  const int32_t all = __builtin_amdgcn_readlane(incl, 63);  // keys 0..63 (FREQ: 1..63)
-  const int32_t first = MODE == FREQ ? tot64 + all - incl : incl - tot;
-  const int32_t first64 = MODE == FREQ ? 0 : all;
-  uint32_t *run = s_run[w];  // this wave's own
-  run[lane] = (uint32_t)first + a.cnt[(int64_t)lane * a.ncol + at];
-  if (lane == 0) run[64] = (uint32_t)first64 + a.cnt[64 * a.ncol + at];
+  const P tot = (P)a.totals[lane], tot64 = (P)a.totals[64];
+  const P incl = sizeof(P) == 8 ? (P)wave_incl_sum((int64_t)tot)
+                                : (P)(uint32_t)wave_incl_sum_i32((int32_t)tot);
+  const P all = (P)read_lane((int64_t)incl, 63);  // keys 0..63 (FREQ: 1..63)
+  const P first = MODE == FREQ ? tot64 + all - incl : incl - tot;
+  const P first64 = MODE == FREQ ? 0 : all;
+  P *run = s_run[w];  // this wave's own
+  const P *base = static_cast<const P *>(a.cnt);
+  run[lane] = first + base[(int64_t)lane * a.ncol + at];
+  if (lane == 0) run[64] = first64 + base[64 * a.ncol + at];
   // FREQ: keys from `cut` on have a rank below cap (first is non-increasing in
   // the key); cut = 65: none has
   int cut = 0;
@@ -281,7 +288,7 @@ __global__ __launch_bounds__(CF_THREADS) void k_key_place(KeySort a) {
     const uint64_t in = __ballot(lane > 0 && (int64_t)first < a.cap);
     cut = in ? __builtin_ctzll(in) : ((int64_t)first64 < a.cap ? 64 : 65);
     // slots no node takes
-    const int64_t used = (int64_t)tot64 + all;
+    const int64_t used = (int64_t)(tot64 + all);
     for (int64_t r = used + (int64_t)blockIdx.x * CF_THREADS + threadIdx.x; r < a.cap;
          r += (int64_t)gridDim.x * CF_THREADS)
       a.cache_nodes[r] = -1;
@@ -323,18 +330,18 @@ __global__ __launch_bounds__(CF_THREADS) void k_key_place(KeySort a) {
             const int kk = __builtin_amdgcn_readlane(k[r], src);
             const uint64_t same = __ballot(k[r] == kk);
             todo &= ~same;
-            const uint32_t at0 = run[kk];
+            const P at0 = run[kk];
             if (k[r] == kk) rank = (int64_t)at0 + __popcll(same & lt);
-            if (lane == src) run[kk] = at0 + (uint32_t)__popcll(same);
+            if (lane == src) run[kk] = at0 + (P)__popcll(same);
             __builtin_amdgcn_wave_barrier();
           }
         } else {
           const uint64_t same = same_key(k[r], act);
           if (cand) {
-            const uint32_t at0 = run[k[r]];
+            const P at0 = run[k[r]];
             rank = (int64_t)at0 + __popcll(same & lt);
             __builtin_amdgcn_wave_barrier();
-            if (__builtin_ctzll(same) == lane) run[k[r]] = at0 + (uint32_t)__popcll(same);
+            if (__builtin_ctzll(same) == lane) run[k[r]] = at0 + (P)__popcll(same);
           }
           __builtin_amdgcn_wave_barrier();
         }
@@ -370,7 +377,9 @@ int64_t key_cols(int64_t n, int rounds) {
 int carve_keysort(KeySort &a, Carve &c, bool with_keys) {
   const int rounds = with_keys ? key_rounds(a.n) : 64;
   a.ncol = key_cols(a.n, rounds);
-  a.cnt = c.take<uint32_t>((size_t)(KEYS + 1) * (size_t)a.ncol);
+  a.wide = a.n > 0x7fffffffll;
+  a.cnt = c.take<char>((size_t)(KEYS + 1) * (size_t)a.ncol *
+                       (a.wide ? sizeof(uint64_t) : sizeof(uint32_t)));
   a.totals = c.take<int64_t>(KEYS + 1);
   a.keys = with_keys ? c.take<uint8_t>((size_t)a.n) : nullptr;
   return rounds;
@@ -401,15 +410,18 @@ size_t keysort_bytes(int64_t n) {
 template <int MODE>
 int keysort_run(KeySort &a, int rounds, int64_t *totals, hipStream_t s) {
   const dim3 g((unsigned)((a.ncol + CF_WAVES - 1) / CF_WAVES)), b(CF_THREADS);
-  auto go = [&](auto r) {
+  auto go = [&](auto r, auto p) {
     constexpr int R = decltype(r)::value;
-    hipLaunchKernelGGL((k_key_count<MODE, R>), g, b, 0, s, a);
-    hipLaunchKernelGGL(k_key_scan, dim3(MODE == MINHASH ? KEYS + 1 : KEYS), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL((k_key_place<MODE, R>), g, b, 0, s, a);
+    using P = decltype(p);
+    hipLaunchKernelGGL((k_key_count<MODE, R, P>), g, b, 0, s, a);
+    hipLaunchKernelGGL(k_key_scan<P>, dim3(MODE == MINHASH ? KEYS + 1 : KEYS), dim3(1024), 0, s,
+                       a);
+    hipLaunchKernelGGL((k_key_place<MODE, R, P>), g, b, 0, s, a);
   };
-  if (rounds == 64) go(std::integral_constant<int, 64>());
-  else if (rounds == 16) go(std::integral_constant<int, 16>());
-  else go(std::integral_constant<int, 4>());
+  if (MODE == MINHASH && a.wide) go(std::integral_constant<int, 64>(), uint64_t());  // n > 2^31
+  else if (rounds == 64) go(std::integral_constant<int, 64>(), uint32_t());
+  else if (rounds == 16) go(std::integral_constant<int, 16>(), uint32_t());
+  else go(std::integral_constant<int, 4>(), uint32_t());
   DG_HIP(hipGetLastError());
   DG_TRY(read_to_host(totals, a.totals, sizeof(int64_t) * (KEYS + 1), s));
   return DG_OK;

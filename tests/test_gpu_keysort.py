@@ -111,3 +111,40 @@ def test_minhash_every_tile(dg, m, kind):
             wrong[m // 2] = N
             with pytest.raises(dg.DGError, match="node ID"):
                 dg.minhash_order(mask, B, wrong, perms)
+
+
+@pytest.mark.big
+@pytest.mark.parametrize("m", [2**31 + 4096 * 300 + 70, 2**32 + 4096 * 300 + 70])
+def test_minhash_ranks_above_32_bits(dg, m):
+    """Lists (with repeats) whose ranks need 32 and 33 bits: entry i is node i mod 300, in a
+    workspace with the keys and in one without."""
+    N, B = 300, 64
+    print(f"[minhash m={m}]", flush=True)
+    mask = torch.zeros(N, dtype=torch.int64, device=DEV)
+    mask[0::3] = 1 << 7  # every third node in sample 7, the next in samples 5 and 9, the last in none
+    mask[1::3] = (1 << 5) | (1 << 9)
+    perms = torch.arange(B, dtype=torch.int32, device=DEV).flip(0).reshape(1, B).contiguous()
+    # samples 7 and {5, 9} have minima 56 and 54: the second class comes first
+    period = torch.arange(N, dtype=torch.int32, device=DEV)
+    entries = period.repeat(m // N + 1)[:m].contiguous()
+    order = torch.empty(m, dtype=torch.int32, device=DEV)
+    tail = m % N
+    for ws_bytes in (dg._L.dg_minhash_workspace_bytes(m), old_bytes(m, 512)):
+        order.fill_(-7)
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device=DEV)
+        dg.check(dg._L.dg_minhash_order(
+            mask.data_ptr(), N, B, entries.data_ptr(), m, perms.data_ptr(), 1, order.data_ptr(),
+            None, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream))
+        at = 0
+        for c in (1, 0, 2):
+            ids = period[c::3]
+            n = (m // N) * ids.numel() + int((ids < tail).sum())
+            got = order[at:at + n]
+            whole = n // ids.numel() * ids.numel()
+            for lo in range(0, whole, ids.numel() << 20):
+                part = got[lo:min(whole, lo + (ids.numel() << 20))].view(-1, ids.numel())
+                assert bool((part == ids).all()), (ws_bytes, c, lo)
+            assert torch.equal(got[whole:], ids[:n - whole])
+            at += n
+        assert at == m
+        del ws
