@@ -66,9 +66,38 @@ struct KeySort {
   const int32_t *ids;    // V_d
   const int32_t *perms;  // [k][B]
   int32_t k, B;
+  int8_t *minv;          // [64] behind totals: minima over many hash functions
+  bool min_done;         // minv holds them
   int32_t *order;        // V_r
   int32_t *signature;    // S(v) per entry (-1: in no sample)
 };
+
+// M(i) = min over the k hash functions of H_j(i) for i < B, or -1 if one of the values
+// is outside [0, B).  Every block of the count pass (and of the place pass without
+// keys) takes the minima for its table itself; above K_ITSELF functions that chain of k
+// loads per block costs more than this launch, which does it once (blocks themselves
+// against this launch, whole call: 30M entries 728 / 725 us at 17 functions, 820 / 725
+// at 64, 2018 / 736 at 512; 1000 entries 37.6 / 38.7, 43.1 / 38.6 and 91 / 41).
+constexpr int K_ITSELF = 16;
+constexpr int MV_PARTS = 16;
+__global__ __launch_bounds__(64 * MV_PARTS) void k_minhash_min(KeySort a) {
+  __shared__ int32_t s_m[MV_PARTS][64];
+  const int i = threadIdx.x & 63, part = threadIdx.x >> 6;
+  int32_t m = 64;
+  if (i < a.B) {
+    for (int j = part; j < a.k; j += MV_PARTS) {
+      const int32_t h = a.perms[(int64_t)j * a.B + i];
+      m = min(m, h < a.B ? h : -1);
+    }
+  }
+  s_m[part][i] = m;
+  __syncthreads();
+  if (part == 0) {
+#pragma unroll
+    for (int q = 1; q < MV_PARTS; ++q) m = min(m, s_m[q][i]);
+    a.minv[i] = (int8_t)max(m, -1);
+  }
+}
 
 // MINHASH: the smallest value of each set of samples is found a byte of the
 // membership word at a time: s_low[q][x] = min over the bits of x of the
@@ -86,9 +115,10 @@ __device__ __forceinline__ uint32_t stage_low(const KeySort &a, LowTable *t) {
     if (threadIdx.x < 64) {
       const int i = threadIdx.x;
       int m = 64;
+      const int funcs = a.min_done ? 1 : a.k;
       if (i < a.B)
-        for (int j = 0; j < a.k; ++j) {
-          const int32_t h = a.perms[(int64_t)j * a.B + i];
+        for (int j = 0; j < funcs; ++j) {
+          const int32_t h = a.min_done ? (int32_t)a.minv[i] : a.perms[(int64_t)j * a.B + i];
           if (h < 0 || h >= a.B) bad = ERR_ROW_RANGE;
           else m = min(m, (int)h);
         }
@@ -380,7 +410,8 @@ int carve_keysort(KeySort &a, Carve &c, bool with_keys) {
   a.wide = a.n > 0x7fffffffll;
   a.cnt = c.take<char>((size_t)(KEYS + 1) * (size_t)a.ncol *
                        (a.wide ? sizeof(uint64_t) : sizeof(uint32_t)));
-  a.totals = c.take<int64_t>(KEYS + 1);
+  a.totals = c.take<int64_t>(KEYS + 1 + 64 / sizeof(int64_t));
+  a.minv = a.totals ? reinterpret_cast<int8_t *>(a.totals + KEYS + 1) : nullptr;
   a.keys = with_keys ? c.take<uint8_t>((size_t)a.n) : nullptr;
   return rounds;
 }
@@ -410,6 +441,10 @@ size_t keysort_bytes(int64_t n) {
 template <int MODE>
 int keysort_run(KeySort &a, int rounds, int64_t *totals, hipStream_t s) {
   const dim3 g((unsigned)((a.ncol + CF_WAVES - 1) / CF_WAVES)), b(CF_THREADS);
+  if (MODE == MINHASH && a.k > K_ITSELF) {
+    hipLaunchKernelGGL(k_minhash_min, dim3(1), dim3(64 * MV_PARTS), 0, s, a);
+    a.min_done = true;
+  }
   auto go = [&](auto r, auto p) {
     constexpr int R = decltype(r)::value;
     using P = decltype(p);

@@ -148,3 +148,36 @@ def test_minhash_ranks_above_32_bits(dg, m):
             at += n
         assert at == m
         del ws
+
+
+# both sides of the number of hash functions from which their minima are a launch of their own
+@pytest.mark.parametrize("k", [16, 17, 40, 300])
+@pytest.mark.parametrize("B", [64, 5])
+def test_minhash_many_functions(dg, k, B):
+    g = torch.Generator(device=DEV).manual_seed(k)
+    N, m = 5003, 4097
+    mask = words(N, "sparse", g)
+    # all functions agree that sample 0 comes last, so that the minima differ
+    perms = torch.stack([torch.cat([torch.tensor([B - 1], device=DEV),
+                                    torch.randperm(B - 1, device=DEV, generator=g)])
+                         for _ in range(k)]).int().contiguous()
+    perms[:, 1:] = perms[:, 1:].sort(dim=1).values.roll(1, dims=1)
+    entries = torch.randint(0, N, (m,), device=DEV, generator=g).int()
+    value = torch.full((m,), 64, dtype=torch.int32, device=DEV)
+    for b in range(B):
+        has = (mask[entries.long()] >> b) & 1 == 1
+        value[has] = value[has].clamp(max=int(perms[:, b].min()))
+    order, signature = dg.minhash_order(mask, B, entries, perms)
+    assert torch.equal(order, entries[torch.sort(value, stable=True).indices])
+    assert torch.equal(signature, torch.where(value == 64, -1, value))
+    ws = torch.empty(old_bytes(m, 512), dtype=torch.uint8, device=DEV)
+    o2 = torch.full_like(order, -7)
+    dg.check(dg._L.dg_minhash_order(
+        mask.data_ptr(), N, B, entries.data_ptr(), m, perms.data_ptr(), k, o2.data_ptr(), None,
+        ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream))
+    assert torch.equal(o2, order)
+    for j, value in ((0, B), (k - 1, -1), (k // 2, 2**31 - 1), (15, -2**31)):
+        bad = perms.clone()
+        bad[j, B // 2] = value
+        with pytest.raises(dg.DGError, match="hash value"):
+            dg.minhash_order(mask, B, entries, bad)
