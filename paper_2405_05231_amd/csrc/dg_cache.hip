@@ -393,19 +393,15 @@ __global__ __launch_bounds__(CF_THREADS) void k_key_place(KeySort a) {
 // longer ones, so that the count matrix stays small.  Count, scan and place of
 // the frequency ranking (5% of the nodes cached, 10% accessed): 20M nodes 86 us
 // with 16 rounds, 99 with 64; 50M nodes 215 and 219, and a quarter of the matrix.
-int key_rounds(int64_t n) {
-  if (n >= (int64_t)8192 * 64 * 64) return 64;
-  return n >= (int64_t)8192 * 64 * 8 ? 16 : 4;
-}
+constexpr int64_t KEYS_16 = (int64_t)8192 * 64 * 8, KEYS_64 = (int64_t)8192 * 64 * 64;
+int key_rounds(int64_t n) { return n >= KEYS_64 ? 64 : n >= KEYS_16 ? 16 : 4; }
 int64_t key_cols(int64_t n, int rounds) {
   const int64_t c = (n + 64 * rounds - 1) / (64 * rounds);
   return c < 1 ? 1 : c;  // an empty list: one wave (MINHASH checks the permutations)
 }
 
-// with_keys: room for the key bytes, and the tile that suits n; without (a
-// workspace sized when the keys were read twice): the longest tile.
-int carve_keysort(KeySort &a, Carve &c, bool with_keys) {
-  const int rounds = with_keys ? key_rounds(a.n) : 64;
+// The layout with tiles of `rounds` and, with_keys, room for the key bytes.
+void carve_keysort(KeySort &a, Carve &c, int rounds, bool with_keys) {
   a.ncol = key_cols(a.n, rounds);
   a.wide = a.n > 0x7fffffffll;
   a.cnt = c.take<char>((size_t)(KEYS + 1) * (size_t)a.ncol *
@@ -413,28 +409,37 @@ int carve_keysort(KeySort &a, Carve &c, bool with_keys) {
   a.totals = c.take<int64_t>(KEYS + 1 + 64 / sizeof(int64_t));
   a.minv = a.totals ? reinterpret_cast<int8_t *>(a.totals + KEYS + 1) : nullptr;
   a.keys = with_keys ? c.take<uint8_t>((size_t)a.n) : nullptr;
-  return rounds;
 }
 
-// Carves the larger layout if ws_bytes hold it, else the smaller one; returns the
-// rounds per wave, 0 if neither fits.
-int fit_keysort(KeySort &a, void *ws, size_t ws_bytes, size_t *need) {
-  for (bool with_keys : {true, false}) {
-    Carve c(ws);
-    const int rounds = carve_keysort(a, c, with_keys);
-    if (with_keys) *need = c.used;
-    if (c.used <= ws_bytes) return rounds;
-  }
+// Carves the first layout that ws_bytes hold: the tile that suits n, longer ones (a
+// smaller matrix), then no keys, as a workspace sized when the keys were read twice
+// needs it.  Returns the rounds per wave, 0 if none fits.
+int fit_keysort(KeySort &a, void *ws, size_t ws_bytes) {
+  for (bool with_keys : {true, false})
+    for (int rounds : {4, 16, 64}) {
+      if (with_keys ? rounds < key_rounds(a.n) : rounds < 64) continue;
+      Carve c(ws);
+      carve_keysort(a, c, rounds, with_keys);
+      if (c.used <= ws_bytes) return rounds;
+    }
   return 0;
 }
 
+// What the preferred layout takes at the worst list of up to n elements (the tiles get
+// longer, and the matrix smaller, at the steps of key_rounds), so that a workspace
+// sized for the longest list suits every shorter one.
 size_t keysort_bytes(int64_t n) {
-  KeySort a;
-  memset(&a, 0, sizeof(a));
-  a.n = n;
-  Carve c(nullptr);
-  (void)carve_keysort(a, c, true);
-  return c.used;
+  size_t most = 0;
+  for (int64_t len : {n, KEYS_16 - 1, KEYS_64 - 1}) {
+    if (len > n) continue;
+    KeySort a;
+    memset(&a, 0, sizeof(a));
+    a.n = len;
+    Carve c(nullptr);
+    carve_keysort(a, c, key_rounds(len), true);
+    if (c.used > most) most = c.used;
+  }
+  return most;
 }
 
 // Count pass, scans and place pass; the totals come back to the host.
@@ -619,10 +624,10 @@ extern "C" int dg_cache_by_frequency(const uint64_t *membership, int64_t N, int3
   a.cap = cache_rows;
   a.cache_slot = cache_slot;
   a.cache_nodes = cache_nodes;
-  size_t need = 0;
-  const int rounds = fit_keysort(a, ws, ws_bytes, &need);
+  const int rounds = fit_keysort(a, ws, ws_bytes);
   if (!ws || !rounds || ((uintptr_t)ws & 255))
-    return set_error(DG_EWORKSPACE, "dg_cache_by_frequency: workspace needs %zu bytes", need);
+    return set_error(DG_EWORKSPACE, "dg_cache_by_frequency: workspace needs %zu bytes",
+                     keysort_bytes(N));
   int64_t totals[KEYS + 1];
   DG_TRY(keysort_run<FREQ>(a, rounds, totals, stream));
   int64_t accessed = 0;
@@ -653,10 +658,10 @@ extern "C" int dg_minhash_order(const uint64_t *membership, int64_t N, int32_t B
   a.B = B;
   a.order = order;
   a.signature = signature;
-  size_t need = 0;
-  const int rounds = fit_keysort(a, ws, ws_bytes, &need);
+  const int rounds = fit_keysort(a, ws, ws_bytes);
   if (!ws || !rounds || ((uintptr_t)ws & 255))
-    return set_error(DG_EWORKSPACE, "dg_minhash_order: workspace needs %zu bytes", need);
+    return set_error(DG_EWORKSPACE, "dg_minhash_order: workspace needs %zu bytes",
+                     keysort_bytes(m));
   int64_t totals[KEYS + 1];
   DG_TRY(keysort_run<MINHASH>(a, rounds, totals, stream));
   const uint32_t bits = (uint32_t)totals[KEYS];

@@ -138,10 +138,12 @@ int read_err(uint32_t *err, hipStream_t s, bool no_alloc) {
 
 size_t pack_ws_bytes(int64_t num_nodes, int32_t B, int64_t total_nodes) {
   if (num_nodes < 1 || B < 1 || B > DG_MAX_BATCHES || total_nodes < 0) return 0;
-  Carve c(nullptr);
-  PackWs w;
-  carve_pack(w, c, num_nodes, B, total_nodes, mc_rounds(num_nodes));
-  return c.used;
+  return mc_most_bytes(num_nodes, [&](int64_t n) {
+    Carve c(nullptr);
+    PackWs w;
+    carve_pack(w, c, n, B, total_nodes, mc_rounds(n));
+    return c.used;
+  });
 }
 
 namespace {

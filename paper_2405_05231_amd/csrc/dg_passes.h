@@ -30,7 +30,18 @@ __host__ __device__ inline int64_t mc_touch_bytes(int64_t N) { return mc_pad_nod
 // Rounds per tile.  A tile's rounds are one serial chain in the write passes, so
 // short tiles until about 1000 blocks (four per CU) are there, then longer ones,
 // which keep the count matrix and each block's own cost small.
-inline int mc_rounds(int64_t N) { return N >= 4000000 ? 16 : N >= 500000 ? 4 : 1; }
+constexpr int64_t MC_N4 = 500000, MC_N16 = 4000000;
+inline int mc_rounds(int64_t N) { return N >= MC_N16 ? 16 : N >= MC_N4 ? 4 : 1; }
+// The most that bytes(n) takes for a graph of up to N nodes (where the tiles get longer
+// the count matrix gets smaller), so that a workspace sized for the largest graph suits
+// every smaller one.
+template <typename F>
+inline size_t mc_most_bytes(int64_t N, F bytes) {
+  size_t most = 0;
+  for (int64_t n : {N, MC_N4 - 1, MC_N16 - 1})
+    if (n <= N && bytes(n) > most) most = bytes(n);
+  return most;
+}
 
 // Count-matrix rows: [0,B) per batch (non-cached members), then:
 __host__ __device__ inline int row_all(int B) { return B; }        // nodes with any bit set (U)

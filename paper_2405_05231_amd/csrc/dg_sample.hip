@@ -772,11 +772,12 @@ extern "C" size_t dg_sample_workspace_bytes(int64_t num_nodes, int32_t B, int64_
   (void)edge_cap;
   if (num_nodes < 1 || B < 1 || B > DG_MAX_BATCHES || node_cap < 1 || (flags & ~SAMPLE_FLAGS))
     return 0;
-  Carve c(nullptr);
-  SampleWs w;
-  carve_sample(w, c, num_nodes, B, node_cap, (flags & DG_SAMPLE_DIRECT) != 0,
-               mc_rounds(num_nodes));
-  return c.used;
+  return mc_most_bytes(num_nodes, [&](int64_t n) {
+    Carve c(nullptr);
+    SampleWs w;
+    carve_sample(w, c, n, B, node_cap, (flags & DG_SAMPLE_DIRECT) != 0, mc_rounds(n));
+    return c.used;
+  });
 }
 
 namespace dg {
@@ -1381,10 +1382,12 @@ extern "C" size_t dg_sample_pack_workspace_bytes(int64_t num_nodes, int32_t B,
   if (num_nodes < 1 || B < 1 || B > DG_MAX_BATCHES || node_cap < 1 ||
       node_cap > INT64_MAX / DG_MAX_BATCHES)
     return 0;
-  Carve c(nullptr);
-  PackInto pk;
-  carve_sample_pack(pk, c, num_nodes, B, node_cap, mc_rounds(num_nodes));
-  return c.used;
+  return mc_most_bytes(num_nodes, [&](int64_t n) {
+    Carve c(nullptr);
+    PackInto pk;
+    carve_sample_pack(pk, c, n, B, node_cap, mc_rounds(n));
+    return c.used;
+  });
 }
 
 extern "C" int dg_sample_pack_group(

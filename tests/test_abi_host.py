@@ -262,3 +262,29 @@ def test_assemble_batches_host_checks(L):
     rc = L.dg_assemble_batches(None, 0, fake, bad, fake, 8, cnt, 2, 16, outs, 1, None, None)
     assert rc == _lib.DG_EINVAL and b"bounds" in L.dg_last_error()
 
+
+
+def test_workspace_queries_never_shrink_with_the_size(L):
+    """A workspace sized for the largest graph or list suits every smaller one, on both sides
+    of each step of the tile lengths."""
+    def around(*steps):
+        out = {1, 64, 1000, 100_000}
+        for s in steps:
+            out |= {s * 99 // 100, s - 4097, s - 1, s, s + 1, s + 4097, s * 101 // 100, s * 3}
+        return sorted(out)
+
+    graphs = around(500_000, 4_000_000)
+    lists = around(8192 * 64 * 8, 8192 * 64 * 64)
+    queries = [(lambda n: L.dg_cache_workspace_bytes(n), lists),
+               (lambda n: L.dg_minhash_workspace_bytes(n), lists + [2**31 - 1, 2**31, 2**32 + 5])]
+    for B in (1, 5, 64):
+        for cap in (100, 50_000):
+            queries += [(lambda n, B=B, cap=cap: L.dg_pack_workspace_bytes(n, B, B * cap), graphs),
+                        (lambda n, B=B, cap=cap: L.dg_sample_pack_workspace_bytes(n, B, cap),
+                         graphs)]
+            queries += [(lambda n, B=B, cap=cap, f=f:
+                         L.dg_sample_workspace_bytes(n, B, cap, 2 * cap, f), graphs)
+                        for f in (0, 2)]
+    for i, (query, sizes) in enumerate(queries):
+        got = [query(n) for n in sizes]
+        assert got == sorted(got) and got[0] > 0, (i, list(zip(sizes, got)))
