@@ -50,6 +50,25 @@ __host__ __device__ inline int row_pairs(int B) { return B + 2; }  // (node, bat
 __host__ __device__ inline int row_all_pairs(int B) { return B + 3; }  // all (node, batch) pairs
 __host__ __device__ inline int mc_rows(int B) { return B + 4; }
 
+// The count matrix is row-major, [rows][nblk], on small graphs: one launch scans it, a
+// block per row.  With many blocks that layout costs a block of the count passes rows
+// stores, and one of the write passes rows loads, in a line each, and the scan's few
+// blocks walk long rows.  From MC_CHUNKED blocks on (CH) the matrix is block-major,
+// [nblk][rows], and scanned by chunks of MC_CHUNK blocks: one launch turns each chunk's
+// counts into prefixes within it, a second scans the chunks' totals.
+// Row-major against block-major, us: 100M nodes, 64 mini-batches: the scan 33 / 11, the
+// count passes 110 / 100 and 178 / 166, the fused one 442 / 426, a write pass 63 / 56;
+// 500M nodes: scan 148 / 21, count 430 / 389.  All mask kernels of a step: 8M nodes
+// 405 / 411, 16M 537 / 527 (8 mini-batches 207 / 209), 24M 683 / 666, 48M 984 / 941.
+constexpr int MC_CHUNK = 64;
+constexpr int64_t MC_CHUNKED = 4096;
+inline bool mc_chunked(int rounds, int64_t nblk) {
+  return rounds == MC_ROUNDS_MAX && nblk >= MC_CHUNKED;
+}
+template <bool CH>
+__device__ __forceinline__ size_t cnt_at(int64_t nblk, int rows, int64_t blk, int row) {
+  return CH ? (size_t)blk * rows + row : (size_t)row * nblk + blk;
+}
 struct MaskScan {
   uint64_t *mask;
   const int32_t *cache_slot;  // nullable: no node is cached
@@ -57,12 +76,15 @@ struct MaskScan {
   int B;
   int rounds;          // per tile
   int64_t nblk;        // mc_blocks(N, rounds)
-  uint32_t *cnt;       // [rows][nblk] per-block counts
+  uint32_t *cnt;       // per-block counts (cnt_at); scanned by chunk: each block's prefix
+                       // in its chunk
   uint32_t *wpre;      // [nblk][MC_WAVES][rows] each wave's exclusive prefix in its block
   uint32_t *wcnt;      // [nblk][MC_WAVES] non-empty words of each wave's tile
   uint64_t *cw_mask;   // [tile][64*rounds] those words (count pass -> write pass)
   uint16_t *cw_off;    // ... their node offsets in the tile; bit 15 = cached
-  int64_t *base;       // [rows][nblk] exclusive scans along each row
+  int64_t *base;       // exclusive scans along each row: [rows][nblk], or per chunk
+                       // [nchunk][rows]
+  uint32_t *sums;      // by chunk: [rows][nchunk] counts per chunk
   int64_t *totals;     // [rows]
   uint32_t *err;
   int64_t *err_stage;  // nullable: receives *err after the count pass (for the read-back)

@@ -129,16 +129,21 @@ void mask_scan_carve(MaskScan &m, Carve &c, int rounds) {
   m.wcnt = c.take<uint32_t>((size_t)m.nblk * MC_WAVES);
   m.cw_mask = c.take<uint64_t>(pad);
   m.cw_off = c.take<uint16_t>(pad);
-  m.base = c.take<int64_t>(rows * (size_t)m.nblk);
+  const bool chunks = mc_chunked(rounds, m.nblk);
+  const size_t nchunk = (size_t)((m.nblk + MC_CHUNK - 1) / MC_CHUNK);
+  m.base = c.take<int64_t>(rows * (chunks ? nchunk : (size_t)m.nblk));
+  m.sums = chunks ? c.take<uint32_t>(rows * nchunk) : nullptr;
   m.totals = c.take<int64_t>(rows + 1);  // + a slot for the staged error word
 }
 
-// Calls f with the rounds per tile as a compile-time constant.
+// Calls f with the rounds per tile, and whether the count matrix is block-major, as
+// compile-time constants.
 template <typename F>
-static void with_rounds(int rounds, F f) {
-  if (rounds == 16) f(std::integral_constant<int, 16>());
-  else if (rounds == 4) f(std::integral_constant<int, 4>());
-  else f(std::integral_constant<int, 1>());
+static void with_rounds(int rounds, int64_t nblk, F f) {
+  if (mc_chunked(rounds, nblk)) f(std::integral_constant<int, 16>(), std::true_type());
+  else if (rounds == 16) f(std::integral_constant<int, 16>(), std::false_type());
+  else if (rounds == 4) f(std::integral_constant<int, 4>(), std::false_type());
+  else f(std::integral_constant<int, 1>(), std::false_type());
 }
 
 // Count pass.  One wave per tile of R rounds of 64 nodes.
@@ -179,7 +184,7 @@ __device__ __forceinline__ void wait_vm_all() { __builtin_amdgcn_s_waitcnt(0x0F7
 // Eight waves per SIMD: the pass is latency-bound under load, and with the
 // prev words read in two halves it fits in 64 VGPRs (a few spill to scratch);
 // without the hint it takes 72 and runs seven.
-template <bool SAMPLE, int R>
+template <bool SAMPLE, int R, bool CH>
 __global__ __launch_bounds__(MC_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8)))
 void k_mask_count(MaskScan a) {
   constexpr int MC_ROUNDS = R, MC_TILE = 64 * R, MC_BLOCK_NODES = MC_TILE * MC_WAVES;
@@ -208,11 +213,6 @@ void k_mask_count(MaskScan a) {
     }
     live = __builtin_amdgcn_readfirstlane(l);
     lmask = lm;
-    if (a.touched_clear) {  // the marks are done with: left zero for the next hop or call
-      uint64_t *fw = reinterpret_cast<uint64_t *>(a.touched_clear + (t0 >> MC_TOUCH_SHIFT));
-      const uint64_t mine = lane < MC_ROUNDS ? f[lane] : 0ull;
-      if (mine != 0ull) fw[lane] = 0ull;
-    }
   }
 
   uint64_t m[MC_ROUNDS];
@@ -231,6 +231,10 @@ void k_mask_count(MaskScan a) {
     }
   }
   wait_vm_all();
+  if (a.touched_clear) {  // the marks are done with: left zero for the next hop or call
+    uint64_t *fw = reinterpret_cast<uint64_t *>(a.touched_clear + (t0 >> MC_TOUCH_SHIFT));
+    if (lane < MC_ROUNDS && ((live >> lane) & 1u)) fw[lane] = 0ull;
+  }
   if (!SAMPLE && a.clear_mask) {
     uint64_t *mk = a.mask + t0;
 #pragma unroll
@@ -403,23 +407,22 @@ void k_mask_count(MaskScan a) {
       pre[j * rows + i] = v;
       v += s_cnt[j][i];
     }
-    a.cnt[(size_t)i * a.nblk + blockIdx.x] = v;
+    a.cnt[cnt_at<CH>(a.nblk, rows, blockIdx.x, i)] = v;
   }
 }
 
-// Row scan: one block per row of the count matrix (of each of up to two
-// matrices), RS_ITEMS values per thread in flight.  It replaces three launches
-// (chunk sums, their scan, bases) over a block-major matrix, whose rows had to
-// be walked with a stride: 21 us to 8 us at 32M nodes, 9 to 4 at 1M.  Also
-// stages the device error word for the caller's read-back (err_stage), after
-// every kernel of the pass so far has run.
+// Row scan of a row-major count matrix: one block per row (of each of up to two
+// matrices), RS_ITEMS values per thread in flight.  Also stages the device error
+// word for the caller's read-back (err_stage), after every kernel of the pass so far
+// has run.
 constexpr int RS_ITEMS = 4;
 struct RowScan {
-  const uint32_t *cnt[2];
+  uint32_t *cnt[2];
   int64_t *base[2];
+  uint32_t *sums[2];
   int64_t *totals[2];
   int rows;
-  int64_t nblk;
+  int64_t nblk, nchunk;
   const uint32_t *err;
   int64_t *err_stage;
 };
@@ -453,23 +456,97 @@ __global__ __launch_bounds__(NT) void k_rows_scan(RowScan a) {
   }
 }
 
+// Block-major matrices, first launch: a block per chunk of MC_CHUNK blocks turns their
+// counts into exclusive prefixes within the chunk, and leaves the chunk's totals.  CS_SEGS
+// groups of 128 threads take MC_CHUNK / CS_SEGS blocks each, a thread per row.
+constexpr int CS_SEGS = 8;
+constexpr int CS_ROWS = 128;
+static_assert(DG_MAX_BATCHES + 4 <= CS_ROWS, "a thread per row");
+__global__ __launch_bounds__(CS_SEGS * CS_ROWS) void k_chunk_scan(RowScan a) {
+  constexpr int PER = MC_CHUNK / CS_SEGS;
+  __shared__ uint32_t s_sum[CS_SEGS][CS_ROWS];
+  const int view = (int64_t)blockIdx.x >= a.nchunk;
+  const int64_t chunk = (int64_t)blockIdx.x - view * a.nchunk;
+  const int row = threadIdx.x % CS_ROWS, seg = threadIdx.x / CS_ROWS;
+  const int64_t blk0 = chunk * MC_CHUNK + seg * PER;
+  uint32_t *p = (view ? a.cnt[1] : a.cnt[0]) + blk0 * a.rows + row;
+  const int n = row < a.rows ? (int)max((int64_t)0, min((int64_t)PER, a.nblk - blk0)) : 0;
+  uint32_t v[PER], sum = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) v[q] = q < n ? p[(int64_t)q * a.rows] : 0u;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) sum += v[q];
+  s_sum[seg][row] = sum;
+  __syncthreads();
+  uint32_t run = 0;
+#pragma unroll
+  for (int j = 0; j < CS_SEGS; ++j) run += j < seg ? s_sum[j][row] : 0u;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    if (q < n) p[(int64_t)q * a.rows] = run;
+    run += v[q];
+  }
+  if (seg == CS_SEGS - 1 && row < a.rows)
+    (view ? a.sums[1] : a.sums[0])[(int64_t)row * a.nchunk + chunk] = run;
+}
+
+// Second launch: the chunks' bases and the totals, a block per row; stages the error
+// word as k_rows_scan does.
+constexpr int CB_THREADS = 512;
+constexpr int CB_ITEMS = 4;
+__global__ __launch_bounds__(CB_THREADS) void k_chunk_bases(RowScan a) {
+  const int view = blockIdx.x >= (unsigned)a.rows, row = (int)blockIdx.x - view * a.rows;
+  const uint32_t *in = (view ? a.sums[1] : a.sums[0]) + (int64_t)row * a.nchunk;
+  int64_t *out = (view ? a.base[1] : a.base[0]) + row;
+  int64_t carry = 0;
+  for (int64_t c0 = 0; c0 < a.nchunk; c0 += CB_THREADS * CB_ITEMS) {
+    const int64_t i0 = c0 + (int64_t)threadIdx.x * CB_ITEMS;
+    uint32_t v[CB_ITEMS];
+    int64_t x = 0;
+#pragma unroll
+    for (int q = 0; q < CB_ITEMS; ++q) v[q] = i0 + q < a.nchunk ? in[i0 + q] : 0u;
+#pragma unroll
+    for (int q = 0; q < CB_ITEMS; ++q) x += v[q];
+    int64_t total;
+    int64_t run = carry + block_excl_scan<CB_THREADS>(x, &total);
+#pragma unroll
+    for (int q = 0; q < CB_ITEMS; ++q) {
+      if (i0 + q < a.nchunk) out[(i0 + q) * a.rows] = run;
+      run += v[q];
+    }
+    carry += total;
+  }
+  if (threadIdx.x == 0) {
+    (view ? a.totals[1] : a.totals[0])[row] = carry;
+    if (blockIdx.x == 0 && a.err_stage) *a.err_stage = (int64_t)*a.err;
+  }
+}
+
 // The row scans of one count matrix, or of two of the same shape.
 static int rows_scan(const MaskScan &m, const MaskScan *m2, hipStream_t s) {
   RowScan r{};
   r.cnt[0] = m.cnt;
   r.base[0] = m.base;
+  r.sums[0] = m.sums;
   r.totals[0] = m.totals;
   if (m2) {
     r.cnt[1] = m2->cnt;
     r.base[1] = m2->base;
+    r.sums[1] = m2->sums;
     r.totals[1] = m2->totals;
   }
   r.rows = mc_rows(m.B);
   r.nblk = m.nblk;
   r.err = m.err;
   r.err_stage = m.err_stage;
-  const dim3 g((unsigned)(r.rows * (m2 ? 2 : 1)));
-  if (m.nblk <= 256 * RS_ITEMS)
+  r.nchunk = (m.nblk + MC_CHUNK - 1) / MC_CHUNK;
+  const unsigned views = m2 ? 2 : 1;
+  const dim3 g((unsigned)r.rows * views);
+  if (mc_chunked(m.rounds, m.nblk)) {
+    hipLaunchKernelGGL(k_chunk_scan, dim3((unsigned)r.nchunk * views), dim3(CS_SEGS * CS_ROWS), 0,
+                       s, r);
+    hipLaunchKernelGGL(k_chunk_bases, g, dim3(CB_THREADS), 0, s, r);
+  } else if (m.nblk <= 256 * RS_ITEMS)
     hipLaunchKernelGGL(k_rows_scan<256>, g, dim3(256), 0, s, r);
   else
     hipLaunchKernelGGL(k_rows_scan<1024>, g, dim3(1024), 0, s, r);
@@ -505,13 +582,14 @@ int mask_scan_count(MaskScan &m, hipStream_t s) {
   if ((m.prev && (m.cache_slot || m.clear_mask)) || (m.keep_prev && m.clear_prev) ||
       (!m.prev && (m.keep_prev || m.clear_prev || m.lines_out)) || (m.lines_out && m.touched))
     return set_error(DG_EINVAL, "internal: inconsistent count-pass mode");
-  with_rounds(m.rounds, [&](auto r) {
+  with_rounds(m.rounds, m.nblk, [&](auto r, auto ch) {
     constexpr int R = decltype(r)::value;
+    constexpr bool CH = decltype(ch)::value;
     if (m.prev)
-      hipLaunchKernelGGL((k_mask_count<true, R>), dim3((unsigned)m.nblk), dim3(MC_THREADS), 0, s,
+      hipLaunchKernelGGL((k_mask_count<true, R, CH>), dim3((unsigned)m.nblk), dim3(MC_THREADS), 0, s,
                          m);
     else
-      hipLaunchKernelGGL((k_mask_count<false, R>), dim3((unsigned)m.nblk), dim3(MC_THREADS), 0, s,
+      hipLaunchKernelGGL((k_mask_count<false, R, CH>), dim3((unsigned)m.nblk), dim3(MC_THREADS), 0, s,
                          m);
   });
   DG_HIP(hipGetLastError());
@@ -575,6 +653,35 @@ __device__ __forceinline__ uint64_t wave_transpose64(uint64_t r) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// Exclusive scans along the rows at one block.  Of a row-major matrix a block's bases
+// lie in a line each, so the block fetches them once, into LDS (24414 blocks of 68 rows:
+// packing's pass 103 us, 130 with every wave fetching them; the sampling passes 92 and
+// 115); on graphs of short tiles the barrier costs more than that (10,000 nodes, the
+// whole step: 131 us against 129), and every wave fetches its own.  Of a block-major
+// matrix they lie side by side.
+template <int R, bool CH>
+struct BlockBase {
+  static constexpr bool STAGED = !CH && R == MC_ROUNDS_MAX;
+  const int64_t *b;
+  const uint32_t *c;
+  int64_t nblk;
+  __device__ __forceinline__ BlockBase(const int64_t *base, const uint32_t *cnt, int64_t n,
+                                       int rows, uint32_t blk, int64_t *stage)
+      : b(CH ? base + (size_t)(blk / MC_CHUNK) * rows : base + blk),
+        c(cnt + (size_t)blk * rows),
+        nblk(n) {
+    if constexpr (STAGED) {
+      if ((int)threadIdx.x < rows) stage[threadIdx.x] = b[threadIdx.x * nblk];
+      b = stage;
+    }
+  }
+  __device__ __forceinline__ int64_t operator()(int row) const {
+    if constexpr (CH) return b[row] + c[row];
+    if constexpr (STAGED) return b[row];
+    return b[row * nblk];
+  }
+};
+
 // Write pass, over the compact list of non-empty words the count pass left for
 // each wave (no second read of the mask).  Batch b's next rank is the block's
 // base from the row scan, plus the wave's prefix within the block, plus what
@@ -591,7 +698,7 @@ __device__ __forceinline__ uint64_t wave_transpose64(uint64_t r) {
 // at the index of its list slot: the entry of a cached node is final, the
 // others are left DG_LOC_PENDING for packing.  Each lane loads the cache slot
 // of its own word before the pairs are emitted.
-template <bool PACK, bool LOCAL, int R>
+template <bool PACK, bool LOCAL, int R, bool CH>
 __global__ __launch_bounds__(MC_THREADS) void k_mask_write(MaskScan a) {
   constexpr int MC_TILE = 64 * R, MC_BLOCK_NODES = MC_TILE * MC_WAVES;
   // per word of the chunk: first pair (packing, from run_p) << 10 | node
@@ -608,31 +715,21 @@ __global__ __launch_bounds__(MC_THREADS) void k_mask_write(MaskScan a) {
   const uint64_t *cm = a.cw_mask + gwi * MC_TILE;
   const uint16_t *co = a.cw_off + gwi * MC_TILE;
   const uint32_t *pre = a.wpre + gwi * rows;
-  if (PACK && a.ptr_out && blk == 0 && w == 0) {
-    if (lane < B) a.ptr_out[lane] = a.seg_base[lane];
-    if (lane == 0) a.ptr_out[B] = a.ptr_end;
-  }
   // The count, the bases and the first chunk are requested together: the
   // chunk's 64 entries lie inside the wave's part of the compact list
   // whatever the count.
   const uint32_t n = a.wcnt[gwi];
   uint64_t m = cm[lane];
   uint32_t off = co[lane];
-  // The block's bases lie in a line each (a column of the row-major matrix), so the
-  // block fetches them once: with every wave fetching them, packing's pass took 130 us
-  // instead of 103 at 24414 blocks of 68 rows, the sampling passes 115 instead of 92.
-  // On small graphs (R < 16) the barrier costs more than that (10,000 nodes, the
-  // whole step: 131 us against 129), and every wave fetches its own.
-  __shared__ int64_t s_base[R == MC_ROUNDS_MAX ? DG_MAX_BATCHES + 4 : 1];
-  if constexpr (R == MC_ROUNDS_MAX) {
-    if ((int)threadIdx.x < rows) s_base[threadIdx.x] = a.base[threadIdx.x * a.nblk + blk];
-    __syncthreads();
-  }
-  auto base = [&](int row) -> int64_t {
-    if constexpr (R == MC_ROUNDS_MAX) return s_base[row];
-    else return a.base[row * a.nblk + blk];
-  };
-  const int64_t run0 = lane < B ? base(lane) + pre[lane] : 0;
+  __shared__ int64_t s_base[BlockBase<R, CH>::STAGED ? DG_MAX_BATCHES + 4 : 1];
+  const BlockBase<R, CH> base(a.base, a.cnt, a.nblk, rows, blk, s_base);
+  if constexpr (BlockBase<R, CH>::STAGED) __syncthreads();
+  const int batch = lane < B ? lane : 0;  // (no branch around the loads)
+  uint32_t pre_b = pre[batch];
+  int64_t run_b = base(batch);
+  asm("" : "+v"(pre_b), "+v"(run_b));  // both loads before either is waited for
+  run_b += pre_b;
+  const int64_t run0 = lane < B ? run_b : 0;
   int64_t dest_b = lane < B ? a.seg_base[lane] + run0 : 0;  // next list slot of batch b
   const int64_t end_b = (!PACK && lane < B) ? a.seg_end[lane] : 0;
   int32_t local_b = 0;                                      // its local index
@@ -644,6 +741,12 @@ __global__ __launch_bounds__(MC_THREADS) void k_mask_write(MaskScan a) {
     run_p = base(row_pairs(B)) + pre[row_pairs(B)];
   }
   wait_vm_all();
+  // After the loads above: behind a store that may alias them, those of values that are
+  // the same across the wave are vector loads (45 VGPRs instead of 37).
+  if (PACK && a.ptr_out && blk == 0 && w == 0) {
+    if (lane < B) a.ptr_out[lane] = a.seg_base[lane];
+    if (lane == 0) a.ptr_out[B] = a.ptr_end;
+  }
   if (n == 0) return;  // wave-uniform
   const uint64_t lt = lanes_below();
   for (uint32_t c0 = 0; c0 < n; c0 += 64) {
@@ -723,14 +826,15 @@ int mask_scan_write(const MaskScan &m, hipStream_t s) {
       (pack && m.loc_out) || (!m.loc_out != !m.loc_slot))
     return set_error(DG_EINVAL, "internal: inconsistent compaction outputs");
   const dim3 g((unsigned)m.nblk), bl(MC_THREADS);
-  with_rounds(m.rounds, [&](auto r) {
+  with_rounds(m.rounds, m.nblk, [&](auto r, auto ch) {
     constexpr int R = decltype(r)::value;
+    constexpr bool CH = decltype(ch)::value;
     if (pack)
-      hipLaunchKernelGGL((k_mask_write<true, false, R>), g, bl, 0, s, m);
+      hipLaunchKernelGGL((k_mask_write<true, false, R, CH>), g, bl, 0, s, m);
     else if (m.local_out)
-      hipLaunchKernelGGL((k_mask_write<false, true, R>), g, bl, 0, s, m);
+      hipLaunchKernelGGL((k_mask_write<false, true, R, CH>), g, bl, 0, s, m);
     else
-      hipLaunchKernelGGL((k_mask_write<false, false, R>), g, bl, 0, s, m);
+      hipLaunchKernelGGL((k_mask_write<false, false, R, CH>), g, bl, 0, s, m);
   });
   DG_HIP(hipGetLastError());
   return DG_OK;
@@ -770,7 +874,7 @@ __device__ __forceinline__ void lds_count(uint32_t k, uint32_t *lo, uint32_t *hi
 // It runs eight waves per SIMD without a hint (54 VGPRs); a hint of eight
 // waves caps its scalar registers at 80 and spills 20 of them into vector
 // lanes (about 150 more vector instructions per wave).
-template <int R>
+template <int R, bool CH>
 __global__ __launch_bounds__(MC_THREADS) void k_fuse_count(FuseScan a) {
   constexpr int MC_ROUNDS = R, MC_TILE = 64 * R, MC_BLOCK_NODES = MC_TILE * MC_WAVES;
   constexpr int MC_CROUNDS = mc_crounds(R), MC_CWORDS = mc_cwords(R), FC_PART = MC_CROUNDS;
@@ -939,7 +1043,7 @@ __global__ __launch_bounds__(MC_THREADS) void k_fuse_count(FuseScan a) {
       pre[j * rows + row] = v;
       v += sv ? s_cs[j][row] : s_cp[j][row];
     }
-    (sv ? a.cnt_s : a.cnt_p)[(size_t)row * a.nblk + blockIdx.x] = v;
+    (sv ? a.cnt_s : a.cnt_p)[cnt_at<CH>(a.nblk, rows, blockIdx.x, row)] = v;
   }
 }
 
@@ -955,7 +1059,7 @@ __global__ __launch_bounds__(MC_THREADS) void k_fuse_count(FuseScan a) {
 // batch's share of the chunk, a few words where the chunk's nodes are cold,
 // instead of one step per word for every lane.  Blocks run in XCD-contiguous
 // order, as in the other write pass.
-template <int R>
+template <int R, bool CH>
 __global__ __launch_bounds__(MC_THREADS) void k_fuse_write(FuseScan a) {
   constexpr int MC_TILE = 64 * R, MC_BLOCK_NODES = MC_TILE * MC_WAVES;
   // per word of the chunk: first pair (from run_p) << 10 | node offset in the
@@ -980,25 +1084,10 @@ __global__ __launch_bounds__(MC_THREADS) void k_fuse_write(FuseScan a) {
   uint64_t m = cm[lane], nw = cn[lane];
   uint32_t off = co[lane];
   int32_t sl = csl[lane];  // the node's cache slot (for a cached node's new pairs)
-  // both views' bases of the block, fetched once as in k_mask_write (300 -> 243 us
-  // at 24414 blocks)
-  __shared__ int64_t s_base[2][R == MC_ROUNDS_MAX ? DG_MAX_BATCHES + 4 : 1];
-  static_assert(2 * (DG_MAX_BATCHES + 4) <= MC_THREADS, "a base per thread");
-  if constexpr (R == MC_ROUNDS_MAX) {
-    if ((int)threadIdx.x < 2 * rows) {
-      const int v = (int)threadIdx.x >= rows, row = (int)threadIdx.x - v * rows;
-      s_base[v][row] = (v ? a.base_p : a.base_s)[row * a.nblk + blk];
-    }
-    __syncthreads();
-  }
-  auto bs = [&](int row) -> int64_t {
-    if constexpr (R == MC_ROUNDS_MAX) return s_base[0][row];
-    else return a.base_s[row * a.nblk + blk];
-  };
-  auto bp = [&](int row) -> int64_t {
-    if constexpr (R == MC_ROUNDS_MAX) return s_base[1][row];
-    else return a.base_p[row * a.nblk + blk];
-  };
+  __shared__ int64_t s_base[2][BlockBase<R, CH>::STAGED ? DG_MAX_BATCHES + 4 : 1];
+  const BlockBase<R, CH> bs(a.base_s, a.cnt_s, a.nblk, rows, blk, s_base[0]);
+  const BlockBase<R, CH> bp(a.base_p, a.cnt_p, a.nblk, rows, blk, s_base[1]);
+  if constexpr (BlockBase<R, CH>::STAGED) __syncthreads();
   // batch `lane`: the next slot of its segment (dest_b; li within the batch's
   // node_cap entries) and the next row of its chunk of P
   int64_t dest_b = 0, pd_b = 0, packed_b = 0;
@@ -1113,9 +1202,9 @@ int fuse_scan_count(const FuseScan &f, MaskScan &vs, MaskScan &vp, hipStream_t s
       vs.B != f.B || vp.B != f.B)
     return set_error(DG_EINVAL, "internal: inconsistent fused count pass");
   if (f.nblk > 0) {
-    with_rounds(f.rounds, [&](auto r) {
-      hipLaunchKernelGGL(k_fuse_count<decltype(r)::value>, dim3((unsigned)f.nblk),
-                         dim3(MC_THREADS), 0, s, f);
+    with_rounds(f.rounds, f.nblk, [&](auto r, auto ch) {
+      hipLaunchKernelGGL((k_fuse_count<decltype(r)::value, decltype(ch)::value>),
+                         dim3((unsigned)f.nblk), dim3(MC_THREADS), 0, s, f);
     });
     DG_HIP(hipGetLastError());
   }
@@ -1126,9 +1215,9 @@ int fuse_scan_write(const FuseScan &f, hipStream_t s) {
   if (!f.seg_out || !f.loc_out || !f.unc_ids || !f.unc_off || !f.pairdest || !f.cw_slot ||
       (f.packed_cap > 0 && !f.pinfo) || !f.packed_ptr || !f.totals_p || f.nblk < 1)
     return set_error(DG_EINVAL, "internal: inconsistent fused write pass");
-  with_rounds(f.rounds, [&](auto r) {
-    hipLaunchKernelGGL(k_fuse_write<decltype(r)::value>, dim3((unsigned)f.nblk),
-                       dim3(MC_THREADS), 0, s, f);
+  with_rounds(f.rounds, f.nblk, [&](auto r, auto ch) {
+    hipLaunchKernelGGL((k_fuse_write<decltype(r)::value, decltype(ch)::value>),
+                       dim3((unsigned)f.nblk), dim3(MC_THREADS), 0, s, f);
   });
   DG_HIP(hipGetLastError());
   return DG_OK;

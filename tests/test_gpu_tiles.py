@@ -1,6 +1,8 @@
 """The mask passes at every tile length (16, 4 or 1 rounds of 64 nodes, chosen by the graph's
-size) and on both sides of its steps, against the oracle; and the longest tiles, which take the
-smaller workspaces, against the chosen ones (tolerance 0)."""
+size) and in both layouts of the count matrix, on both sides of their steps, against the oracle;
+and the longest tiles, which take the smaller workspaces, against the chosen ones (tolerance 0)."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -31,9 +33,10 @@ def dev(x):
     return torch.from_numpy(x).to(DEV)
 
 
-@pytest.mark.parametrize("n", [1, 255, 257, 4097, 499_999, 500_000, 1_000_003, 3_999_999,
-                               4_000_001])
-@pytest.mark.parametrize("B", [3, 64])
+# the matrix is block-major from 4096 blocks of 4096 nodes on, in chunks of 64 blocks
+@pytest.mark.parametrize("n,B", [(n, B) for n in (1, 255, 257, 4097, 499_999, 500_000, 1_000_003,
+                                                  3_999_999, 4_000_001) for B in (3, 64)]
+                         + [(4095 * 4096, 64), (4095 * 4096 + 1, 64), (4160 * 4096 + 1, 3)])
 def test_every_tile_length(dg, orc, n, B, monkeypatch):
     off, idx = graph(n, n + B)
     rng = np.random.default_rng(n)
@@ -78,11 +81,52 @@ def test_every_tile_length(dg, orc, n, B, monkeypatch):
     forms = [lambda: dg.sample_pack_group(*args), lambda: two_calls(True), lists_only]
     for form in forms:
         check(*form())
-    # workspaces too small for short tiles (below 4M nodes) take the longest ones
+    # workspaces of the least size take the longest tiles
     if n < 4_000_000:
-        monkeypatch.setattr(dg, "_workspace", lambda nbytes, d, ws: torch.empty(
-            nbytes - 256, dtype=torch.uint8, device=d))
-        if n <= 257:  # so small that both layouts round to the same size
-            return
         for form in forms:
-            check(*form())
+            check(*with_least(dg, form, monkeypatch))
+
+
+def with_least(dg, form, monkeypatch):
+    """form() with the smallest workspaces its calls take (sampling's, packing's)."""
+    sizes = [256, 256]
+    for _ in range(3):
+        at = iter(sizes)
+        monkeypatch.setattr(dg, "_workspace", lambda nbytes, d, ws: torch.empty(
+            next(at), dtype=torch.uint8, device=d))
+        try:
+            return form()
+        except dg.DGError as e:
+            need = re.search(r"workspace needs (\d+) bytes", str(e))
+            sizes[1 if "dg_pack_group:" in str(e) or "packing" in str(e) else 0] = int(need[1])
+    raise AssertionError(sizes)
+
+
+@pytest.mark.big
+def test_packing_of_more_chunks_than_one_step_of_their_scan(dg):
+    """540M nodes: 131,837 blocks, 2,060 chunks (a step of the chunks' scan takes 2,048)."""
+    n, B = 540_000_000, 3
+    g = torch.Generator(device=DEV).manual_seed(5)
+    lists = [torch.randint(0, n, (k,), device=DEV, generator=g).unique() for k in
+             (300_000, 5, 2_000_000)]
+    lists = [torch.cat([torch.tensor([0, n - 1], device=DEV), u]).unique() for u in lists]
+    stride = max(u.numel() for u in lists)
+    nodes = torch.zeros((B, stride), dtype=torch.int32, device=DEV)
+    order = [torch.randperm(u.numel(), device=DEV, generator=g) for u in lists]
+    for b, u in enumerate(lists):
+        nodes[b, :u.numel()] = u[order[b]].int()
+    feats = torch.randint(0, 256, (n, 1), dtype=torch.uint8, device=DEV, generator=g)
+    slot = torch.full((n,), -1, dtype=torch.int32, device=DEV)
+    slot[lists[0][::7]] = torch.arange(lists[0][::7].numel(), dtype=torch.int32, device=DEV)
+    pr = dg.pack_group(feats, slot, nodes, [u.numel() for u in lists], with_unique=True)
+    u_all = torch.cat(lists).unique()
+    assert pr.sizes["unique_nodes"] == u_all.numel()
+    assert torch.equal(pr.unique.long(), u_all)
+    for b, u in enumerate(lists):
+        lo, hi = int(pr.packed_ptr_host[b]), int(pr.packed_ptr_host[b + 1])
+        p_b = u[slot[u] < 0]
+        assert torch.equal(pr.packed_ids[lo:hi].long(), p_b), b
+        assert torch.equal(pr.packed[lo:hi], feats[p_b]), b
+        v = u[order[b]]
+        loc = torch.where(slot[v] >= 0, -slot[v].long() - 1, torch.searchsorted(p_b, v))
+        assert torch.equal(pr.loc[b, :u.numel()].long(), loc), b
