@@ -47,6 +47,7 @@ struct Hop {
   int32_t f;        // fan-out of this hop (< 0: all)
   int32_t k;        // hop number, 1-based (RNG key)
   int32_t filter;   // the draws filter their membership atomics (see emit_chunk)
+  int32_t scanned;  // the tiles' sums are scanned (see k_tile_scan)
   int32_t tstart[DG_MAX_BATCHES + 1];  // prefix of the batches' tiles
   int64_t fstart[DG_MAX_BATCHES + 1];  // prefix of frontier sizes
   int64_t fpos[DG_MAX_BATCHES];        // local position of b's first frontier node
@@ -79,9 +80,9 @@ struct SeedInit {
 
 // Frontier pass: each entry's CSR row and degree, its edge slots' exclusive scan
 // within its tile, and each tile's sum.  The draw kernel adds the sums of its
-// batch's earlier tiles itself, so the scan costs no launch of its own (three
-// scan kernels and one for the batch bounds went: 16 to 20 us a hop on short
-// frontiers, 39 us at 3.2M entries).
+// batch's earlier tiles itself, or finds them scanned (k_tile_scan).  (Scanning the
+// entries by kernels of their own took 16 to 20 us a hop on short frontiers, 39 us at
+// 3.2M entries.)
 // SEEDS: the first hop's frontier, straight from the seeds; each also enters its
 // node list, the membership words and the local indices, with loc its address-
 // table entry (final for a cached seed, pending otherwise).  degree = false: that
@@ -139,6 +140,42 @@ __global__ __launch_bounds__(THREADS) void k_frontier(Hop h, SeedInit sd, bool d
     f_eoff[i] = eoff;
   }
   if (threadIdx.x == 0) tile_sum[t] = total;
+}
+
+// Exclusive scan of each batch's tile sums in place, a block per batch, and the
+// batches' edges of the hop: for frontiers of more than TILES_DIRECT tiles in a batch.
+// Up to that many the draw kernel adds the sums of its batch's earlier tiles itself,
+// which costs no launch but grows with the square of the frontier (whole call, fan-out 1,
+// adding / scanning: one mini-batch, 1024 tiles 383 / 391 us, 4096 688 / 703, 16384
+// 1727 / 1738, 65536 5916 / 5318; 8 mini-batches, 4096 3072 / 3084, 16384 11772 / 11635;
+// fan-out 5: 8 mini-batches, 4096 7279 / 7266, 16384 26492 / 26066).
+constexpr int32_t TILES_DIRECT = 8192;
+constexpr int TS_THREADS = 1024;
+constexpr int TS_ITEMS = 8;
+__global__ __launch_bounds__(TS_THREADS) void k_tile_scan(Hop h, int64_t *tile_sum,
+                                                          int64_t *bounds) {
+  const int b = blockIdx.x;
+  const int32_t n = h.tstart[b + 1] - h.tstart[b];
+  int64_t *p = tile_sum + h.tstart[b];
+  int64_t carry = 0;
+  for (int32_t c0 = 0; c0 < n; c0 += TS_THREADS * TS_ITEMS) {
+    // a thread's items lie next to each other: one block scan per chunk
+    const int32_t i0 = c0 + (int32_t)threadIdx.x * TS_ITEMS;
+    int64_t v[TS_ITEMS], x = 0;
+#pragma unroll
+    for (int q = 0; q < TS_ITEMS; ++q) v[q] = i0 + q < n ? p[i0 + q] : 0;
+#pragma unroll
+    for (int q = 0; q < TS_ITEMS; ++q) x += v[q];
+    int64_t total;
+    int64_t run = carry + block_excl_scan<TS_THREADS>(x, &total);
+#pragma unroll
+    for (int q = 0; q < TS_ITEMS; ++q) {
+      if (i0 + q < n) p[i0 + q] = run;
+      run += v[q];
+    }
+    carry += total;
+  }
+  if (threadIdx.x == 0) bounds[b] = carry;
 }
 
 // Emits up to EMIT sampled edges whose neighbour IDs are already loaded: the
@@ -228,7 +265,9 @@ __global__ __launch_bounds__(THREADS) void k_hop_sample(
     __syncthreads();
   }
   int64_t before = 0;  // edges of the batch's earlier tiles
-  if (t > t0) {        // uniform
+  if (h.scanned) {     // uniform
+    before = tile_sum[t];
+  } else if (t > t0) {  // uniform
     int64_t x = 0;
     for (int32_t q = t0 + (int32_t)threadIdx.x; q < t; q += THREADS) x += tile_sum[q];
 #pragma unroll
@@ -239,7 +278,8 @@ __global__ __launch_bounds__(THREADS) void k_hop_sample(
 #pragma unroll
     for (int q = 0; q < THREADS / 64; ++q) before += s_x[q];
   }
-  if (threadIdx.x == 0 && part == 0 && t + 1 == h.tstart[b + 1]) bounds[b] = before + tile_sum[t];
+  if (!h.scanned && threadIdx.x == 0 && part == 0 && t + 1 == h.tstart[b + 1])
+    bounds[b] = before + tile_sum[t];
   if (!valid) return;
   const int64_t p = h.fpos[b] + j;
   const int64_t first = h.ebase[b] + before + eoff;  // local index of the 1st edge
@@ -966,6 +1006,11 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
       h.touched = (ebound <= N / 16 && !full_last) ? w.touched : nullptr;
       frontier(!seeded, true);
       seeded = true;
+      h.scanned = 0;
+      for (int b = 0; b < B; ++b) h.scanned |= h.tstart[b + 1] - h.tstart[b] > TILES_DIRECT;
+      if (h.scanned)
+        hipLaunchKernelGGL(k_tile_scan, dim3(B), dim3(TS_THREADS), 0, s, h, w.tiles,
+                           w.small + ST_BOUNDS);
       DG_HIP(hipGetLastError());
       // lanes per frontier node: up to 8 while the frontier has fewer than 2^20
       // entries (never more lanes than draws; fan-outs above FMAX keep one)
