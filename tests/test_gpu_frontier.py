@@ -1,5 +1,6 @@
 """Frontiers of thousands of tiles, on both sides of the length from which the tiles' sums are
-scanned by a launch of their own, against the oracle (tolerance 0)."""
+scanned by a launch of their own, and of the number of seeds from which those enter by one, against
+the oracle (tolerance 0)."""
 import numpy as np
 import pytest
 import torch
@@ -36,6 +37,7 @@ def graph(n, rng):
 
 @pytest.mark.parametrize("S,B,direct,layered", [(EDGE, 1, True, False), (EDGE + 1, 1, True, False),
                                                 (EDGE + 1, 3, False, False),
+                                                (EDGE, 4, True, False),  # 2^23 seeds: apart
                                                 (EDGE - 100_000, 2, True, True)])
 def test_long_frontiers(dg, orc, S, B, direct, layered):
     """The seeds fill the first hop's frontier; layered, the later hops' pass the step."""
@@ -73,3 +75,18 @@ def test_long_frontier_beside_an_empty_one(dg, orc):
             dg.sample_group(*args, edge_cap=cap)
         assert e.value.status == -2
     assert dg.sample_group(*args, edge_cap=2 * S).edge_ptr[:, -1].tolist() == [0, 2 * S]
+
+
+def test_bad_seeds_among_many(dg):
+    """2^23 seeds enter by a launch of their own: a seed out of range or repeated is reported."""
+    n, S, B = EDGE + 5, EDGE, 4
+    off = torch.zeros(n + 1, dtype=torch.int64, device=DEV)
+    idx = torch.zeros(0, dtype=torch.int32, device=DEV)
+    good = torch.randperm(n, device=DEV)[:S].int().repeat(B, 1).contiguous()
+    assert dg.sample_group(off, idx, good, [1], 5).hop_ptr[:, -1].tolist() == [S] * B
+    for at, value, text in (((3, S - 1), n, "outside"), ((0, 7), -1, "outside"),
+                            ((2, 9), int(good[2, 10]), "twice")):
+        bad = good.clone()
+        bad[at] = value
+        with pytest.raises(dg.DGError, match=text):
+            dg.sample_group(off, idx, bad, [1], 5)
