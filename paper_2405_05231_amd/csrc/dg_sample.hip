@@ -477,11 +477,11 @@ __device__ __forceinline__ int64_t older_index(const OlderNodes &o, int32_t u, i
 // parts of one launch, each a run of its blocks.  As three launches the whole step
 // took 135.5 us against 131 (10,000 nodes), 213 against 208 (one mini-batch at 1M
 // nodes) and 1092 against 1084 (32 of them).
-struct TailEdges {  // edges whose neighbours the table knows: of b, the first n[b]
+struct TailEdges {  // edges whose neighbours the table knows: of b, the first ones
   int B;
   unsigned blocks;
   int64_t start[DG_MAX_BATCHES + 1];  // prefix of the edges
-  int64_t limit[DG_MAX_BATCHES];      // local indices lie below (0: not checked)
+  int64_t limit[DG_MAX_BATCHES];      // b's local indices (of pairs too) lie below
 };
 struct TailSparse {  // the index of the last-hop segments
   unsigned blocks;
@@ -982,7 +982,6 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
       h.ebase[b] = e_b[b];
     }
   };
-  lay_out();
   bool seeded = false;
   for (int k = 1; k <= K; ++k) {
     for (int b = 0; b < B; ++b) edge_ptr[(int64_t)b * (K + 1) + (k - 1)] = e_b[b];
@@ -1541,7 +1540,11 @@ extern "C" int dg_sample_pack_group(
                      (long long)rows, (long long)sizes->unique_nodes);
   const FusedRows t{feats,  N,      row_bytes,       packed, pk.pw.unc_ids, pk.pw.unc_off,
                     pk.pw.pairdest, sizes->unique_packed, rows,   pk.err};
-  // On a second stream the row copy starts at once, beside what is left here.
+  // On a second stream the row copy starts behind the relabelling, so that it runs beside
+  // the caller's next call.  It needs the last hop's lists alone, but handed over ahead of
+  // the relabelling it slows that, which this call waits for: a loop with the copy and the
+  // assembly on a second stream, handed over here / ahead, a step: 1M nodes 943 / 1007 us,
+  // 8M 2146 / 2251 and 806 / 894, 32M 4733 / 4800, 100M about 5.6 / 5.9 ms.
   if (rows_async && (rc = pack_fused_rows(t, true, stream, rows_stream))) return rc;
   if (!pk.loc_done && rows > 0) {  // phases are timed: the address tables by themselves
     TailEdges te;
