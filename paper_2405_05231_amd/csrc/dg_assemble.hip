@@ -26,13 +26,13 @@ __device__ __forceinline__ const char *row_source(int32_t l, const char *cache, 
 
 // The rows of one batch handled by virtual block `blk` of `nblk`.  Bound by HBM:
 // plain loads (cache rows are read again by later batches) and, with NT,
-// nontemporal stores.  Short rows that are no multiple of 32 bytes take plain
-// stores, so that the lines that several rows share merge in L2 (4M rows, plain
-// against nontemporal: 48 B 136 / 182 us, 100 B 227 / 313, 112 B 233 / 244;
-// but 64 B 150 / 123, 96 B 192 / 184, 400 B 180 / 163 (1M rows), 1.5 KiB
-// 385 / 342).  Rows that are no multiple of 16 bytes used to go by narrower words, one
-// wave per row: 385 B 512 us, now 180; 1540 B 549, now 417; 200 B 190, now 91
-// (1M, 0.65M and 1M rows).
+// nontemporal stores.  Rows below 64 bytes, and those below 128 that are no multiple
+// of 32, take plain stores, so that the lines that several rows share merge in L2
+// (plain against nontemporal: 2M rows: 16 B 41 / 55 us, 32 B 49 / 61; 4M rows: 48 B
+// 136 / 182, 100 B 227 / 313, 112 B 233 / 244; but 64 B 150 / 123, 96 B 192 / 184,
+// 400 B 180 / 163 (1M rows), 1.5 KiB 385 / 342).  By narrower words, one wave per row,
+// rows that are no multiple of 16 bytes took 512 us (385 B), 549 (1540 B) and 190
+// (200 B); here they take 180, 417 and 91 (1M, 0.65M and 1M rows).
 template <int LPR, int CPL, bool NT>
 __device__ __forceinline__ void assemble16_rows(const char *cache, int64_t cache_rows,
                                                 const char *packed, int64_t packed_rows,

@@ -12,17 +12,26 @@ namespace {
 
 constexpr int THREADS = 256;
 
+// Which rows take nontemporal stores: as in the row gather, but the packed rows of a
+// node lie apart, so that fewer lines merge in L2 and the line lies lower.  Packing of
+// 8 lists, plain against nontemporal, us: 2M rows in all: 132 B 460 / 513, 192 B
+// 473 / 466, 288 B 568 / 583, 320 B 572 / 562, 400 B 653 / 672, 448 B 649 / 625, 544 B
+// 778 / 779; 1.2 GB: 672 B 766 / 757, 688 B 773 / 781, 700 B 776 / 788, 850 B 743 / 747,
+// 900 B 712 / 712, 944 B 693 / 686, 1204 B 662 / 648, 1601 B 626 / 610, 2400 B 554 / 532,
+// 4000 B 520 / 495.
+inline bool fanout_nt(int64_t R) {
+  return (R % 64 == 0 && R >= 128) || (R % 32 == 0 && R >= 640) || R >= 900;
+}
+
 // Fan-out gather, vector path: a group of LPR lanes reads the row of one U_nc
 // node once and stores it into each of its destination rows.  Every U_nc node
 // has at least one destination; its first destination index is loaded together
 // with the row, so the common single-destination case needs two dependent
 // round trips (indices, then row + destination) before its stores.  Bound by
-// HBM; nontemporal loads, and nontemporal stores (NT) where rows are whole
-// 128-byte lines: with plain stores the launch itself is up to 15% shorter
-// (512-byte rows at 1M nodes: 88 against 104 us), but the assembly that follows
-// takes that time back (whole step 1.339 against 1.332 ms).  Other rows share
-// lines with their neighbours and take plain stores (400-byte rows: packing of
-// 32 lists 550 us against 559).
+// HBM; nontemporal loads, and nontemporal stores (NT) where fanout_nt says so: for
+// 512-byte rows a launch with plain stores is up to 15% shorter (1M nodes: 88 against
+// 104 us), but the assembly that follows takes that time back (whole step 1.339
+// against 1.332 ms).
 // Items n_unc .. n_unc + n_cache - 1 fill the cache table, the cache taken as
 // one more mini-batch of the same pass: item n_unc + s copies the row of
 // cache_nodes[s] into cache row s (a slot holding -1 is left as it is; an ID
@@ -148,7 +157,7 @@ int launch16(const RowCopy &r, hipStream_t s) {
                        r.dest, (int)r.row_bytes, (char *)r.packed, r.cache_nodes, r.n_cache,
                        (char *)r.cache_table, r.err);
   };
-  if (r.row_bytes % 128 == 0) go(std::true_type());
+  if (fanout_nt(r.row_bytes)) go(std::true_type());
   else go(std::false_type());
   return DG_OK;
 }

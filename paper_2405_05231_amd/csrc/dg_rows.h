@@ -26,7 +26,12 @@ struct RowShape {
 };
 
 // Launch shapes of the vector path, by row size; false: the row takes the
-// generic path.
+// generic path.  Rows of 129 to 192 vectors take three vectors per lane only where
+// they are no multiple of 4 bytes, since a lane past the row still reads the row's
+// last vector, which costs more unaligned (3 against 4 vectors, gather / assembly of
+// 1.2 GB: 2155 B 494 / 542 and 504 / 546 us, 2601 B 481 / 505 and 482 / 503; but
+// 2064 B 470 / 455 and 555 / 531, 2408 B 488 / 474 and 513 / 490, 3000 B 492 / 487 and
+// 493 / 472).
 inline bool row_shape16(int64_t row_bytes, RowShape *s) {
   if (row_bytes < 16) return false;
   const int64_t C = (row_bytes + 15) / 16;
@@ -38,7 +43,7 @@ inline bool row_shape16(int64_t row_bytes, RowShape *s) {
   if (C <= 32) { *s = {32, 1}; return true; }
   if (C <= 64) { *s = {64, 1}; return true; }
   if (C <= 128) { *s = {64, 2}; return true; }
-  if (C <= 192) { *s = {64, 3}; return true; }
+  if (C <= 192 && row_bytes % 4 != 0) { *s = {64, 3}; return true; }
   if (C <= 256) { *s = {64, 4}; return true; }
   return false;
 }

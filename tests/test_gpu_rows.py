@@ -39,6 +39,8 @@ class Guarded:
 SIZES = [1, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65, 96, 100, 127, 128, 129, 200, 255, 256, 257,
          385, 511, 512, 513, 1023, 1024, 1025, 1540, 2047, 2049, 2408, 3071, 3073, 4095, 4096,
          4097]
+# both sides of the lines between the kinds of stores
+SIZES += [192, 576, 608, 624, 640, 899, 900, 1584, 1600, 2064, 2396, 2400]
 
 
 @pytest.mark.parametrize("R", SIZES)
