@@ -1261,7 +1261,7 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
     tl.loc = loc;
     pk->loc_done = true;
   }
-  auto launch_tail = [&] {
+  auto launch_part = [&] {
     const OlderNodes older{w.local, table};
     const unsigned grid = te.blocks + ts.blocks + tl.blocks;
     if (grid == 0) return;
@@ -1271,6 +1271,17 @@ int sample_impl(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S, int
     else
       hipLaunchKernelGGL(k_relabel_tail<false>, dim3(grid), dim3(THREADS), 0, s, te, ts, tl, nodes,
                          node_cap, edge_cap, edge_dst, older, N, w.err);
+  };
+  // One launch, unless its threads would pass the 32-bit count that a launch takes.
+  auto launch_tail = [&] {
+    const unsigned parts[3] = {te.blocks, ts.blocks, tl.blocks};
+    if ((uint64_t)parts[0] + parts[1] + parts[2] <= UINT32_MAX / THREADS) return launch_part();
+    for (int q = 0; q < 3; ++q) {
+      te.blocks = q == 0 ? parts[0] : 0;
+      ts.blocks = q == 1 ? parts[1] : 0;
+      tl.blocks = q == 2 ? parts[2] : 0;
+      launch_part();
+    }
   };
   if (any_edges && rl_search) {
     // edges of the hops before the last through the table, the last hop's by

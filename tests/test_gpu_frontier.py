@@ -90,3 +90,28 @@ def test_bad_seeds_among_many(dg):
         bad[at] = value
         with pytest.raises(dg.DGError, match=text):
             dg.sample_group(off, idx, bad, [1], 5)
+
+
+@pytest.mark.big
+def test_more_edges_and_pairs_than_threads_of_a_launch(dg):
+    """4.22e9 edges of the first hop and 1.3e8 packed pairs: each part of the relabelling fits a
+    launch of 2^32 threads, together they do not.  Every node is a seed of every mini-batch, in
+    an order rotated by the batch, so that local indices are known."""
+    n, D, B, step = 2_000_000, 33, 64, 30_011
+    assert n * D * B < 2**32 < n * (D + 1) * B
+    g = torch.Generator(device=DEV).manual_seed(1)
+    off = torch.arange(0, n * D + 1, D, dtype=torch.int64, device=DEV)
+    idx = torch.randint(0, n, (n, D), device=DEV, generator=g).int()
+    order = torch.arange(n, device=DEV)
+    seeds = torch.stack([(order + b * step) % n for b in range(B)]).int()
+    feats = torch.randint(0, 256, (n, 1), dtype=torch.uint8, device=DEV, generator=g)
+    slot = torch.full((n,), -1, dtype=torch.int32, device=DEV)
+    sr, pr = dg.sample_pack_group(off, idx.view(-1), seeds, [-1, 1], 5, feats, slot, layered=True)
+    assert sr.node_count.tolist() == [n] * B
+    assert sr.edge_ptr.tolist() == [[0, n * D, n * D + n]] * B
+    for b in range(B):
+        want = (idx.roll(-(b * step % n), 0) - b * step) % n
+        assert torch.equal(sr.edge_dst[b, :n * D].view(n, D), want), b
+        last = sr.edge_dst[b, n * D:n * D + n].view(n, 1)
+        assert bool((want == last).any(1).all()), b
+        assert torch.equal(pr.loc[b, :n], seeds[b]), b  # P_b is every node in order
