@@ -6,6 +6,7 @@ the flags, the membership output must equal theirs, and packing must leave the
 mask all-zero.  The workspaces and the mask start filled with garbage, which
 the first call (without DG_SAMPLE_ENTRY_CLEAR) must not see."""
 import random
+import re
 
 import numpy as np
 import pytest
@@ -162,3 +163,94 @@ def test_member_lines(dg, case, layered, direct):
     with pytest.raises(dg.DGError) as e:
         dg.pack_group(feats, slot, sr.nodes, counts, membership=mem, member_lines=bad)
     assert e.value.status == -1
+
+
+# (B, S, fan-outs, direct, layered, node_cap's margin, workspaces of the least size, one call)
+MIXED = [(4, 16, (3, 3, 2), True, False, 0, False, True),
+         (1, 300, (2, 2), False, False, 7, False, True),
+         (64, 16, (3, 3), True, False, 0, True, True),
+         (3, 64, (6, 6, 6, 6), False, True, 100, True, False),
+         (64, 700, (5, 5), True, False, 1, False, False),
+         (2, 16, (-1, 2), True, True, 0, True, True),
+         (5, 33, (0, 3), True, True, 3, False, True),
+         (4, 16, (3, 0), True, False, 0, True, False),
+         (4, 16, (3, 3, 2), True, False, 0, False, True)]
+
+
+@pytest.mark.parametrize("n", [70_000, 200_000, 700_000])
+def test_one_workspace_for_calls_of_every_shape(dg, n):
+    """DG_SAMPLE_ENTRY_CLEAR asks for the same number of nodes and nothing else: B, S, the
+    fan-outs, the capacities, the relabelling mode, layering, the tile length (a workspace of the
+    least size takes the longest tiles) and the form of the call change from call to call on one
+    workspace and one membership mask."""
+    rnd = random.Random(n)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    deg = torch.randint(0, 7, (n,), device=DEV, generator=g)
+    off = torch.zeros(n + 1, dtype=torch.int64, device=DEV)
+    torch.cumsum(deg, 0, out=off[1:])
+    idx = torch.randint(0, n, (int(off[-1]),), device=DEV, generator=g).int()
+    feats = torch.randint(0, 256, (n, 16), dtype=torch.uint8, device=DEV, generator=g)
+    slot = torch.full((n,), -1, dtype=torch.int32, device=DEV)
+    slot[::9] = torch.arange(slot[::9].numel(), dtype=torch.int32, device=DEV)
+    caps, most = [], [0, 0]
+    for B, S, fan, direct, layered, margin, _, _ in MIXED:
+        nc, ec = dg.sample_bounds(n, idx.numel(), S, fan, layered)
+        nc = min(nc + margin, n) if margin else nc
+        caps.append((nc, ec))
+        need = (dg._L.dg_sample_workspace_bytes(n, B, nc, ec, dg.sample_flags(layered, direct)),
+                max(dg._L.dg_sample_pack_workspace_bytes(n, B, nc),
+                    dg._L.dg_pack_workspace_bytes(n, B, B * nc)))
+        most = [max(a, b) for a, b in zip(most, need)]
+    ws, pws = (torch.full((m,), 0xA5, dtype=torch.uint8, device=DEV) for m in most)
+    mem = torch.full((n,), -1, dtype=torch.int64, device=DEV)
+    for turn, ((B, S, fan, direct, layered, _, least, one), (nc, ec)) in \
+            enumerate(zip(MIXED + MIXED[::-1], caps + caps[::-1])):
+        print(f"[n={n}] call {turn}", flush=True)
+        seeds = torch.stack([torch.randperm(n, device=DEV, generator=g)[:S]
+                             for _ in range(B)]).int()
+        kw = dict(node_cap=nc, edge_cap=ec, layered=layered, direct=direct)
+        flags = dict(membership=mem, entry_clear=turn > 0, exit_clear=True)
+        rng = rnd.randrange(2**40)
+        fresh = dg.sample_group(off, idx, seeds, fan, rng, **kw)
+        counts = fresh.node_count
+        fresh_p = dg.pack_group(feats, slot, fresh.nodes, counts, with_unique=True)
+        sizes = [ws.numel(), pws.numel()]
+
+        def call():
+            at = iter([ws[:sizes[0]], pws[:sizes[1]]])
+            with pytest.MonkeyPatch.context() as patch:
+                patch.setattr(dg, "_workspace", lambda nbytes, d, w: next(at))
+                if one:
+                    out = dg.PackResult(
+                        packed=torch.empty_like(fresh_p.packed),
+                        packed_ids=torch.empty_like(fresh_p.packed_ids),
+                        packed_ptr=torch.empty_like(fresh_p.packed_ptr),
+                        packed_ptr_host=np.zeros(B + 1, dtype=np.int64),
+                        loc=torch.empty((B, nc), dtype=torch.int32, device=DEV),
+                        unique=torch.empty_like(fresh_p.unique), sizes={}, timing=None,
+                        row_bytes=16)
+                    return dg.sample_pack_group(off, idx, seeds, fan, rng, feats, slot,
+                                                pack_out=out, **kw, **flags)
+                sr = dg.sample_group(off, idx, seeds, fan, rng, **kw, **flags)
+                return sr, dg.pack_group(feats, slot, sr.nodes, sr.node_count, with_unique=True,
+                                         membership=mem, clear_membership=True)
+
+        if least:  # refused calls touch nothing and name what they need
+            for k in (1, 0):
+                keep, sizes[k] = sizes[k], 256
+                if one or k == 0:
+                    with pytest.raises(dg.DGError, match="workspace needs") as e:
+                        call()
+                    sizes[k] = int(re.search(r"needs (\d+) bytes", str(e.value))[1])
+                else:
+                    sizes[k] = keep
+        sr, pr = call()
+        same_sample(sr, fresh)
+        rows = fresh_p.sizes["packed_rows"]
+        assert pr.sizes["packed_rows"] == rows
+        assert torch.equal(pr.packed[:rows], fresh_p.packed[:rows])
+        assert torch.equal(pr.unique[:fresh_p.sizes["unique_nodes"]],
+                           fresh_p.unique[:fresh_p.sizes["unique_nodes"]])
+        for b in range(B):
+            assert torch.equal(pr.loc[b, :int(counts[b])], fresh_p.loc[b, :int(counts[b])]), b
+        assert int(mem.count_nonzero()) == 0
