@@ -220,7 +220,12 @@ int dg_sample_bounds(int64_t num_nodes, int64_t num_edges, int32_t S,
                      const int32_t *fanouts /*[host] K*/, int32_t K, uint32_t flags,
                      int64_t *node_cap /*[host] out*/, int64_t *edge_cap /*[host] out*/);
 
-/* Workspace bytes dg_sample_group needs for N nodes, B batches, the given
+/* Workspace queries (dg_*_workspace_bytes): the size at which the call is
+ * fastest, for these sizes and every smaller number of nodes or entries.  Each
+ * call also takes less, at a cost in time (longer tiles of nodes; the cache
+ * calls: keys found twice), down to the size that its DG_EWORKSPACE message
+ * names. */
+/* Workspace bytes for dg_sample_group with N nodes, B batches, the given
  * per-batch capacities and the same flags (DG_SAMPLE_DIRECT adds 4*N*B bytes).
  * Returns 0 for arguments dg_sample_group would reject. */
 size_t dg_sample_workspace_bytes(int64_t num_nodes, int32_t B, int64_t node_cap,
@@ -297,7 +302,7 @@ int dg_sample_group(const dg_csr *g, const int32_t *seeds, int32_t B, int32_t S,
                     void *ws, size_t ws_bytes, hipStream_t stream, dg_sizes *sizes,
                     dg_timing *timing);
 
-/* Workspace bytes dg_pack_group needs for N nodes, B batches whose node lists
+/* Workspace bytes for dg_pack_group with N nodes, B batches whose node lists
  * hold `total_nodes` entries in all. */
 size_t dg_pack_workspace_bytes(int64_t num_nodes, int32_t B, int64_t total_nodes);
 
@@ -376,7 +381,7 @@ int dg_pack_group(const void *feats, int64_t N, int64_t row_bytes,
                   uint32_t flags, void *ws, size_t ws_bytes, hipStream_t stream,
                   hipStream_t rows_stream, dg_sizes *sizes, dg_timing *timing);
 
-/* Bytes of the packing workspace dg_sample_pack_group needs for N nodes, B
+/* Bytes of the packing workspace for dg_sample_pack_group with N nodes, B
  * batches and per-batch capacity node_cap (room for B*node_cap list entries).
  * Returns 0 for B outside 1..64, N < 1 or node_cap < 1. */
 size_t dg_sample_pack_workspace_bytes(int64_t num_nodes, int32_t B, int64_t node_cap);
@@ -438,9 +443,9 @@ size_t dg_pack_noalloc_scratch_bytes(void);
  * same arguments, outputs and errors, except that the call allocates nothing.
  *  - Its scratch is a fixed array inside the library, one per GPU, of
  *    dg_pack_noalloc_scratch_bytes() bytes; each GPU the library runs on holds
- *    it until the process ends.  Calls whose sizes need more
- *    (dg_pack_workspace_bytes(N, B, sum of n_b) above that) return
- *    DG_EWORKSPACE before any work is enqueued.
+ *    it until the process ends.  Calls whose sizes need more even with the
+ *    longest tiles return DG_EWORKSPACE before any work is enqueued; sizes whose
+ *    dg_pack_workspace_bytes(N, B, sum of n_b) is not above it always fit.
  *  - Every call on a GPU shares that GPU's scratch, which keeps the last
  *    call's contents; each call clears what it needs cleared.  Calls that
  *    overlap in time on one GPU race and give unspecified outputs: the caller
@@ -503,7 +508,7 @@ int dg_assemble_batches(const void *cache, int64_t cache_rows, const void *packe
                         int64_t row_bytes, void *const *outs, int32_t n_outs,
                         int32_t *status, hipStream_t stream);
 
-/* Workspace bytes dg_cache_by_frequency needs for N nodes. */
+/* Workspace bytes for dg_cache_by_frequency with N nodes. */
 size_t dg_cache_workspace_bytes(int64_t num_nodes);
 
 /* Cache configuration by access frequency (§4 "Four-level hierarchical feature
@@ -536,7 +541,7 @@ int dg_cache_by_frequency(const uint64_t *membership, int64_t N, int32_t B, int6
 int dg_gather_rows(const void *feats, int64_t N, int64_t row_bytes, const int32_t *ids,
                    int64_t n, void *out, int32_t *status, hipStream_t stream);
 
-/* Workspace bytes dg_minhash_order needs for m disk-cache entries. */
+/* Workspace bytes for dg_minhash_order with m disk-cache entries. */
 size_t dg_minhash_workspace_bytes(int64_t m);
 
 /* Disk-cache node reordering by MinHash (§5.1 "Node reordering for disk

@@ -18,7 +18,8 @@ from . import _lib
 from ._lib import (DG_ECAPACITY, DG_MAX_BATCHES, DG_OK, DGError, Csr, Sizes, Timing, check,
                    load)
 
-__all__ = ["sample_bounds", "member_lines_bytes", "sample_group", "pack_group", "assemble_batch",
+__all__ = ["sample_bounds", "member_lines_bytes", "sample_group", "pack_group",
+           "sample_pack_group", "assemble_batch",
            "assemble_batches", "cache_by_frequency",
            "gather_rows", "pack_individual", "minhash_order", "DGError", "SampleResult",
            "PackResult", "version"]

@@ -442,6 +442,13 @@ size_t keysort_bytes(int64_t n) {
   return most;
 }
 
+// What the smallest layout takes.
+size_t keysort_least(KeySort a) {
+  Carve c(nullptr);
+  carve_keysort(a, c, 64, false);
+  return c.used;
+}
+
 // Count pass, scans and place pass; the totals come back to the host.
 template <int MODE>
 int keysort_run(KeySort &a, int rounds, int64_t *totals, hipStream_t s) {
@@ -636,7 +643,7 @@ extern "C" int dg_cache_by_frequency(const uint64_t *membership, int64_t N, int3
   const int rounds = fit_keysort(a, ws, ws_bytes);
   if (!ws || !rounds || ((uintptr_t)ws & 255))
     return set_error(DG_EWORKSPACE, "dg_cache_by_frequency: workspace needs %zu bytes",
-                     keysort_bytes(N));
+                     keysort_least(a));
   int64_t totals[KEYS + 1];
   DG_TRY(keysort_run<FREQ>(a, rounds, totals, stream));
   int64_t accessed = 0;
@@ -670,7 +677,7 @@ extern "C" int dg_minhash_order(const uint64_t *membership, int64_t N, int32_t B
   const int rounds = fit_keysort(a, ws, ws_bytes);
   if (!ws || !rounds || ((uintptr_t)ws & 255))
     return set_error(DG_EWORKSPACE, "dg_minhash_order: workspace needs %zu bytes",
-                     keysort_bytes(m));
+                     keysort_least(a));
   int64_t totals[KEYS + 1];
   DG_TRY(keysort_run<MINHASH>(a, rounds, totals, stream));
   const uint32_t bits = (uint32_t)totals[KEYS];

@@ -117,3 +117,25 @@ def test_noalloc_pack_rejects_sizes_beyond_its_scratch(dg):
                                  None, None, 0, None, dg._lib.DG_PACK_ROWS_STREAM, None,
                                  ctypes.byref(sz))
     assert rc == dg._lib.DG_EINVAL
+
+
+def test_noalloc_pack_takes_the_longest_tiles_where_shorter_ones_do_not_fit(dg):
+    """Sizes whose preferred workspace is just above the scratch: the call runs with the longest
+    tiles, which need less, and gives the same outputs."""
+    n, B = 499_999, 64
+    query, cap = dg._L.dg_pack_workspace_bytes, dg._L.dg_pack_noalloc_scratch_bytes()
+    total = next(t for t in range(B * 400_000, B * n, B) if query(n, B, t) > cap)
+    assert query(n, B, total) - cap < 1 << 20  # the longest tiles save 3 MB
+    per = total // B
+    g = torch.Generator(device=DEV).manual_seed(2)
+    nodes = torch.stack([torch.randperm(n, device=DEV, generator=g)[:per] for _ in range(B)]).int()
+    counts = np.full(B, per, dtype=np.int64)
+    feats = torch.randint(0, 256, (n, 1), dtype=torch.uint8, device=DEV, generator=g)
+    slot = torch.full((n,), -1, dtype=torch.int32, device=DEV)
+    slot[::2] = torch.arange(slot[::2].numel(), dtype=torch.int32, device=DEV)
+    ref = dg.pack_group(feats, slot, nodes, counts, with_unique=True)
+    got = dg.pack_group(feats, slot, nodes, counts, with_unique=True, out=packed_out(dg, ref, 1),
+                        no_alloc=True)
+    torch.cuda.synchronize()
+    same(ref, got)
+    assert torch.equal(got.loc, ref.loc)
