@@ -13,14 +13,17 @@ namespace {
 constexpr int THREADS = 256;
 
 // Which rows take nontemporal stores: as in the row gather, but the packed rows of a
-// node lie apart, so that fewer lines merge in L2 and the line lies lower.  Packing of
-// 8 lists, plain against nontemporal, us: 2M rows in all: 132 B 460 / 513, 192 B
-// 473 / 466, 288 B 568 / 583, 320 B 572 / 562, 400 B 653 / 672, 448 B 649 / 625, 544 B
-// 778 / 779; 1.2 GB: 672 B 766 / 757, 688 B 773 / 781, 700 B 776 / 788, 850 B 743 / 747,
-// 900 B 712 / 712, 944 B 693 / 686, 1204 B 662 / 648, 1601 B 626 / 610, 2400 B 554 / 532,
-// 4000 B 520 / 495.
-inline bool fanout_nt(int64_t R) {
-  return (R % 64 == 0 && R >= 128) || (R % 32 == 0 && R >= 640) || R >= 900;
+// node lie apart, so that fewer lines merge in L2 and the line lies lower.  Nontemporal
+// over plain, the whole packing: packed rows of 232 MB (900 B) 1.13, 310 MB (1200 B) 1.00,
+// 400 MB (1540 B) 0.98, 517 MB (2000 B) 0.95.  Packing of 8 lists, plain against
+// nontemporal, us: 2M rows in all: 132 B 460 / 513, 192 B 473 / 466, 288 B 568 / 583,
+// 320 B 572 / 562, 400 B 653 / 672, 448 B 649 / 625, 544 B 778 / 779; 1.2 GB: 672 B
+// 766 / 757, 688 B 773 / 781, 700 B 776 / 788, 850 B 743 / 747, 900 B 712 / 712, 944 B
+// 693 / 686, 1204 B 662 / 648, 1601 B 626 / 610, 2400 B 554 / 532, 4000 B 520 / 495.
+inline bool fanout_nt(int64_t R, int64_t rows) {
+  if (R % 128 == 0) return true;
+  return rows * R > STREAM_BYTES &&
+         ((R % 64 == 0 && R >= 128) || (R % 32 == 0 && R >= 640) || R >= 900);
 }
 
 // Fan-out gather, vector path: a group of LPR lanes reads the row of one U_nc
@@ -157,7 +160,7 @@ int launch16(const RowCopy &r, hipStream_t s) {
                        r.dest, (int)r.row_bytes, (char *)r.packed, r.cache_nodes, r.n_cache,
                        (char *)r.cache_table, r.err);
   };
-  if (fanout_nt(r.row_bytes)) go(std::true_type());
+  if (fanout_nt(r.row_bytes, r.pairs + r.n_cache)) go(std::true_type());
   else go(std::false_type());
   return DG_OK;
 }

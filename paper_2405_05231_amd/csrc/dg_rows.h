@@ -81,6 +81,9 @@ inline int word_bytes(int64_t row_bytes, std::initializer_list<const void *> ptr
   return w;
 }
 
+// Outputs of more bytes than this leave the caches anyway (256 MB at the last level).
+constexpr int64_t STREAM_BYTES = 320 * 1000 * 1000;
+
 // 16-byte row vector as a native vector type, so the nontemporal builtins
 // apply.  Its address may have any alignment.  A nontemporal store leaves the
 // caches to reusable lines, but a row that ends inside a 128-byte line then

@@ -92,3 +92,31 @@ def test_rows_every_size_and_alignment(dg, R, shift):
     for b, o in enumerate(outs):
         assert torch.equal(o.rows, X[nodes[b].long()])
         o.check()
+
+
+@pytest.mark.parametrize("R", [192, 608, 901, 1616, 2404])
+@pytest.mark.parametrize("large", [False, True])
+def test_rows_on_both_sides_of_the_large_outputs(dg, R, large):
+    """Outputs just below and above 320 MB, where the kind of stores changes: the row gather, and
+    packing of two lists whose rows go to two chunks each."""
+    N, n = 40_000, 320_000_000 // R + (1 if large else 0)
+    g = torch.Generator(device=DEV).manual_seed(R)
+    X = torch.randint(0, 256, (N, R), dtype=torch.uint8, device=DEV, generator=g)
+    ids = torch.randint(0, N, (n,), device=DEV, generator=g).int()
+    out = Guarded(n, R, 3)
+    dg.gather_rows(X, ids, out=out.rows)
+    want = X[ids.long()]
+    assert torch.equal(out.rows, want)
+    out.check()
+    del want
+    B = n // N + 1  # every node in each batch, and the rest in the last
+    counts = [N] * (B - 1) + [n - N * (B - 1)]
+    slot = torch.full((N,), -1, dtype=torch.int32, device=DEV)
+    nodes = torch.stack([torch.randperm(N, device=DEV, generator=g) for _ in range(B)]).int()
+    packed = Guarded(n, R, 5)
+    pr = dg.pack_group(X, slot, nodes, counts, tables_only=True)
+    pr.packed, pr.packed_ids = packed.rows, pr.packed_ids[:n].contiguous()
+    pr = dg.pack_group(X, slot, nodes, counts, out=pr)
+    assert pr.sizes["packed_rows"] == n
+    assert torch.equal(packed.rows, X[pr.packed_ids.long()])
+    packed.check()
