@@ -115,13 +115,16 @@ __device__ __forceinline__ uint32_t stage_low(const KeySort &a, LowTable *t) {
     if (threadIdx.x < 64) {
       const int i = threadIdx.x;
       int m = 64;
-      const int funcs = a.min_done ? 1 : a.k;
-      if (i < a.B)
-        for (int j = 0; j < funcs; ++j) {
-          const int32_t h = a.min_done ? (int32_t)a.minv[i] : a.perms[(int64_t)j * a.B + i];
+      if (i < a.B && a.min_done) {
+        m = a.minv[i];
+        if (m < 0) bad = ERR_ROW_RANGE;
+      } else if (i < a.B) {
+        for (int j = 0; j < a.k; ++j) {
+          const int32_t h = a.perms[(int64_t)j * a.B + i];
           if (h < 0 || h >= a.B) bad = ERR_ROW_RANGE;
           else m = min(m, (int)h);
         }
+      }
       s_min[i] = (uint8_t)m;
       bad = __ballot(bad != 0) ? ERR_ROW_RANGE : 0u;
     }
@@ -465,7 +468,9 @@ int keysort_run(KeySort &a, int rounds, int64_t *totals, hipStream_t s) {
                        a);
     hipLaunchKernelGGL((k_key_place<MODE, R, P>), g, b, 0, s, a);
   };
-  if (MODE == MINHASH && a.wide) go(std::integral_constant<int, 64>(), uint64_t());  // n > 2^31
+  // (FREQ lists are never that long)
+  using Wide = std::conditional_t<MODE == MINHASH, uint64_t, uint32_t>;
+  if (a.wide) go(std::integral_constant<int, 64>(), Wide());
   else if (rounds == 64) go(std::integral_constant<int, 64>(), uint32_t());
   else if (rounds == 16) go(std::integral_constant<int, 16>(), uint32_t());
   else go(std::integral_constant<int, 4>(), uint32_t());
