@@ -40,10 +40,10 @@ constexpr int CF_FLIGHT = 16;  // rounds of 64 elements whose keys are loaded to
 //            value (64 = in no sample), ranked ascending.
 // The count pass leaves each element's key as a byte for the place pass, where
 // the workspace has room: the membership words are read once.  Bound by HBM
-// (FREQ at 50M nodes: 400 MB of words, 2 x 50 MB of keys, 200 MB of slots; the
-// whole call 393 -> 238 us) or by the scattered words (MINHASH: 1M entries
-// 275 -> 63 us).  Counting with one step per distinct key of a round had been
-// bound by issue: 120 + 207 us for the two passes at 50M nodes, now 92 + 110.
+// (FREQ at 50M nodes: 400 MB of words, 2 x 50 MB of keys, 200 MB of slots; 238 us
+// the whole call) or by the scattered words (MINHASH: 1M entries, 63 us).  With the
+// words read twice and one step per distinct key of a round the passes are bound by
+// issue: 120 + 207 us at 50M nodes against 92 + 110 (the calls: 393 and 275 us).
 enum Mode { FREQ = 0, MINHASH = 1 };
 
 struct KeySort {

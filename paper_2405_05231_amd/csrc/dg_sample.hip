@@ -193,8 +193,9 @@ __global__ __launch_bounds__(TS_THREADS) void k_tile_scan(Hop h, int64_t *tile_s
 // value; a block serves one batch) and leaves their atomics out.  The filter is
 // plain reads and writes: a lost entry costs an atomic, and an entry is only
 // ever there because its writer issues the atomic.  Last hop at 1M nodes, 32
-// mini-batches (2.1M draws): 261 -> 208 us; 32M nodes, 64 mini-batches (15M
-// draws) 755 -> 717; no difference on uniform graphs.
+// mini-batches (2.1M draws), without and with the filter: 261 and 208 us; 64
+// mini-batches: 32M nodes (15M draws) 755 and 717, 100M nodes 805 and 814 (the hop
+// before it 229 and 222); no difference on uniform graphs.
 constexpr int EMIT = 8;
 constexpr int TAG_BITS = 11;
 constexpr int64_t TAG_MIN_DRAWS = 1 << 18;
@@ -427,10 +428,9 @@ __global__ __launch_bounds__(THREADS) void k_table_insert(Segs L, const int32_t 
 // blocks are ordered so that all of a batch run on one XCD).
 //
 // The segment is read where it lies, in blocks that start at multiples of S in
-// memory, so the first and the last may reach past it.  A padded copy of every
-// segment used to be made first: 55 us for 10M entries (32M nodes, 64 batches),
-// and the index alone takes 13 us; blocks at any alignment cost the search 10 to
-// 40% (two lines per block).
+// memory, so the first and the last may reach past it.  (A padded copy of every
+// segment takes 55 us for 10M entries (32M nodes, 64 batches), the index alone 13;
+// blocks at any alignment cost the search 10 to 40%, two lines per block.)
 constexpr int RL_THREADS = 512;
 constexpr int RL_CHUNKS = 4;          // edge chunks per block (one staging of the index)
 constexpr int RL_SPARSE_MAX = 16384;  // sparse-index entries per batch (64 KB of LDS)
@@ -575,8 +575,8 @@ __device__ __forceinline__ int xor_lane(int v) {
 // S = 16: a lane reads its own 64 bytes, and lanes without a window read nothing
 // (15M last-hop edges of 64 mini-batches at 32M nodes: 228 us, 250 when they
 // read).  Longer windows are read by S/4 lanes together, 16 bytes each, so that an
-// instruction touches 256/S of them and not 64 (S = 32, 3M edges: 153 -> 115 us;
-// at S = 16 the shuffles cost what that gains, 247 us).
+// instruction touches 256/S of them and not 64 (S = 32, 3M edges: 115 us
+// against 153; at S = 16 the shuffles cost what that gains, 247 us).
 template <int S>
 __device__ __forceinline__ int window_count(const int32_t *seg, int u, int start, int pos,
                                             int lane) {

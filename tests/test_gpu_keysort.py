@@ -36,7 +36,7 @@ def words(n, kind, g):
 
 
 def old_bytes(n, extra):
-    """The workspace the calls asked for before they kept the keys."""
+    """A workspace without room for the keys (blocks of 4096 elements, 12 bytes a key)."""
     def up(x):
         return (x + 255) & ~255
     blocks = (n + 4095) // 4096
